@@ -82,8 +82,9 @@ REACTION_FLOPS = {0: 12, 1: 13, 2: 13, 3: 13, 4: 4}   # kinetics + the explicit 
 
 
 # Sources that define the fused stepper kernels (device code, launch shape).
-STEPPER_SOURCES = ["stepper.hip", "stepper_common.hpp", "stepper_quad.hpp", "stepper_quad_f32.hip",
-                   "stepper_quad_f64.hip", "stepper_quad_mixed.hip", "dct_quad.hpp", "cil_internal.hpp"]
+STEPPER_SOURCES = ["stepper.hip", "stepper_common.hpp", "stepper_mm.hpp", "stepper_mm_launch.hpp",
+                   "stepper_mm_f32.hip", "stepper_mm_f64.hip", "stepper_mm_mixed.hip", "dct_mfma.hpp",
+                   "cil_internal.hpp"]
 TRAFFIC_PROFILES = os.path.join(ROOT, "profiles", "*_hbm_bytes.md")
 
 
@@ -302,10 +303,10 @@ def main():
 
     kernels = {k: {"launches": v[0], "total_ms": round(v[1], 3)} for k, v in sorted(prof.items())}
     kernels_stat = {k: {"launches": v[0], "avg_us": round(1e3 * v[1] / v[0], 2)}
-                    for k, v in sorted(prof_stat.items()) if not k.startswith("k_fused")}
+                    for k, v in sorted(prof_stat.items()) if not k.startswith("k_mm")}
     kname = max(prof, key=lambda k: prof[k][1]) if prof else None
     roof = None
-    if kname and kname.startswith("k_fused"):
+    if kname and kname.startswith("k_mm"):
         cnt, tot_ms = prof[kname]
         per = fused_step_flops(n, REACTION_FLOPS[w["model"]])
         # the refinement form's polish steps transform in FP32 (its FP64 work,
@@ -374,7 +375,7 @@ def main():
         "config": {"workload": WORKLOAD, "model": "gierer_meinhardt_source", "solves": B, "grid": n,
                    "dt": w["dt"], "tol": w["tol"], "radii": M, "bootstrap": n_boot,
                    "pairs_per_step": pairs,
-                   "stepping": "fp32 fused persistent (quad-lane DCT); from each solve's fp32 floor to tol in the "
+                   "stepping": "fp32 fused persistent (DCT on the matrix cores); from each solve's fp32 floor to tol in the "
                                "same launch " + ("fp64 steps" if args.polish == 1 else
                                                  "in refinement form (fp64 state, fp32 correction steps)") +
                                "; fp64 residual",
@@ -629,7 +630,7 @@ def fhn32_main(args):
     # within the FP64 trajectory bar of the oracle), so its speedup compares
     # like with like
     t_f64, rep_f64, counts_f64, _ = run(torch.float64, cil.CIL_PATH_FUSED)
-    kname = "k_fused_q_f32_n32"
+    kname = "k_mm_f32_n32"
     cnt, tot_ms = prof[kname]
     flops = B * w["max_steps"] * fused_step_flops(w["n"], REACTION_FLOPS[w["model"]])
     ach = flops / (tot_ms / cnt * 1e-3) / 1e12
@@ -920,7 +921,7 @@ def mcmc_main(args):
     prof = {k: cil.cil_profile_read(k) for k in cil.cil_profile_names()}
     cil.cil_profile(False)
     K = args.steps
-    kname = "k_fused_q_f32_n128"
+    kname = "k_mm_f32_n128"
     roof = None
     if kname in prof:
         cnt, tot_ms = prof[kname]

@@ -15,9 +15,10 @@
 //          state streamed through HBM, host-driven step loop; any n >= 2.
 //   fused  one persistent workgroup per solve, the whole n x n x 2 state
 //          resident in LDS from the first step to the last; every line
-//          transformed in registers by one lane (dct_reg.hpp) or a quad of
-//          lanes (dct_quad.hpp); the workgroup evaluates its own stop rule
-//          and retires; n in {32, 64, 128} (FP32), {32, 64} (FP64).
+//          transformed in registers, on the matrix cores (dct_mfma.hpp; any n
+//          up to 128 in FP32, 96 in FP64), by one lane (dct_reg.hpp) or by a
+//          quad of lanes (dct_quad.hpp; n in {32, 64, 128} in FP32, {32, 64}
+//          in FP64); the workgroup evaluates its own stop rule and retires.
 // Both evaluate the stationarity residual max |u^s - u^{s-1}| / dt in FP64
 // every check_every steps (and at max_steps), per solve.  FP32 solves whose
 // residual falls below the FP32 floor continue in FP64 (phase 2).
@@ -434,9 +435,6 @@ __global__ __launch_bounds__(2 * N) void k_fused_sbdf2(const DevSolve *S, const 
 
 // Spectral tables for the fused back-end:
 // tab[s][k][l] = 1 / (4 N^2 (1 + dt nu_s (lam_k + lam_l) / h^2)), in FP64 then T.
-struct TabSpec {
-    double inv_h2, nu0, nu1;
-};
 template <typename T>
 __global__ void k_make_tables(const TabSpec *specs, int ntab, int n, double dt, T *out)
 {
@@ -562,17 +560,17 @@ struct AuxStreams {
 };
 std::map<int, AuxStreams> g_aux;
 
-int aux_streams(int count, AuxStreams **out)
+int aux_streams(int streams, int joins, AuxStreams **out)
 {
     int dev;
     CIL_TRY(current_device(&dev));
     AuxStreams &a = g_aux[dev];
-    while ((int)a.st.size() < count) {
+    while ((int)a.st.size() < streams) {
         hipStream_t s;
         CIL_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
         a.st.push_back(s);
     }
-    while ((int)a.ev.size() < count + 1) {
+    while ((int)a.ev.size() < joins + 1) {
         hipEvent_t e;
         CIL_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         a.ev.push_back(e);
@@ -580,6 +578,10 @@ int aux_streams(int count, AuxStreams **out)
     *out = &a;
     return CIL_OK;
 }
+
+// How a persistent group runs: one lane or a quad of lanes per grid line, or
+// the matrix cores.
+enum FusedKind { KIND_LINE = 0, KIND_QUAD, KIND_MM };
 
 int fused_supported(int n, bool f32)
 {
@@ -592,6 +594,30 @@ int g_polish_separate = 0;         // 1: the polish always in a launch of its ow
 // batch (FP64, residual 1e-8): off 30.5 ms; base 3: 30.2; 10: 29.9; 100: 29.5;
 // 1000: 29.4.
 double g_wave_priority = 100.0;
+
+// The kernel a path selects.  AUTO and FUSED run on the matrix cores, which
+// measured faster than the quad-lane kernels at every side and batch size (us
+// per step, matrix cores / quad: 128 FHN 32^2 solves FP32 1.03 / 2.12, FP64
+// 1.63 / 2.95; one 64^2 solve FP32 3.4 / 6.3, FP64 5.7 / 11.4, 512 of them 7.2 /
+// 9.7 and 12.4 / 17.7; 256 128^2 solves FP32 14.1 / 21.2); a quad-lane code
+// shape chosen by option keeps the quad kernel.
+FusedKind fused_kind(int path)
+{
+    if (path == CIL_PATH_FUSED_LINE) return KIND_LINE;
+    if (path == CIL_PATH_FUSED_QUAD || g_quad_shape_option >= 0) return KIND_QUAD;
+    return KIND_MM;
+}
+
+// Whether side n has a persistent kernel on this path.  AUTO takes the matrix
+// cores for any side whose field fits the LDS (192 FP64 solves of sides 20 to
+// 96: 34 us a step against 378 for the plain path); an explicit path has the
+// sides it names.
+bool persistent_supported(int n, bool f32, int path)
+{
+    if (path == CIL_PATH_PLAIN) return false;
+    if (fused_supported(n, f32)) return true;
+    return path == CIL_PATH_AUTO && n >= 2 && n <= mm_max_side(f32);
+}
 
 int quad_shape(bool f32, int n)
 {
@@ -680,6 +706,25 @@ int set_quad_shape(int64_t v)
 }
 
 namespace {
+
+// Matrix-core launch; the kernel's name in the profiler goes by side where the
+// side has a kernel of its own.
+template <typename T>
+int launch_mm_named(int n, int scheme, int nl, const DevSolve *S, const int *list, T *state, const T *tab,
+                    const T *tab2, const T *cst, int model, double dt, const PersistArgs &pa, hipStream_t st)
+{
+    static const char *names[2][2][4] = {
+        {{"k_mm_f64", "k_mm_f64_n32", "k_mm_f64_n64", "k_mm_f64_n128"},
+         {"k_mm_f32", "k_mm_f32_n32", "k_mm_f32_n64", "k_mm_f32_n128"}},
+        {{"k_mm_sbdf2_f64", "k_mm_sbdf2_f64_n32", "k_mm_sbdf2_f64_n64", "k_mm_sbdf2_f64_n128"},
+         {"k_mm_sbdf2_f32", "k_mm_sbdf2_f32_n32", "k_mm_sbdf2_f32_n64", "k_mm_sbdf2_f32_n128"}}};
+    const char *name = names[scheme][sizeof(T) == 4][n == 32 ? 1 : n == 64 ? 2 : n == 128 ? 3 : 0];
+    const ProfMark pm = prof_begin(name, st);
+    const int rc = launch_mm<T>(n, scheme, nl, S, list, state, tab, tab2, cst, model, dt, pa, st);
+    prof_end(pm, st);
+    if (rc) return set_error(rc, "no matrix-core kernel for n = %d", n);
+    return check_launch(name);
+}
 
 template <typename T>
 int launch_persistent(int n, bool quad, int shape, int nl, const DevSolve *S, const int *list, T *state, const T *tables,
@@ -834,18 +879,16 @@ struct MixedArgs {
     int refine;                   // 1: the continuation is the refinement form, else FP64 steps
 };
 
-bool mixed_supported(int n, bool quad)
+bool mixed_supported(int n, FusedKind kind)
 {
-    return quad && g_quad_shape_option < 0 && (n == 32 || n == 64);
+    return kind != KIND_LINE && g_quad_shape_option < 0 && (n == 32 || n == 64);
 }
 
 // Spectral tables for the solves in `ids` (side n): one per distinct (h, nu);
-// sets hs[b].tab.  Returns the device table buffer.
-template <typename T>
-int make_tables(SimCtx &c, int n, const std::vector<int> &ids, std::vector<DevSolve> &hs, void **tables, bool vform,
-                double dt_tab = 0.0)
+// sets hs[b].tab.  make_specs uploads the distinct ones, make_tables and
+// make_mm_tables build from them.
+int make_specs(SimCtx &c, const std::vector<int> &ids, std::vector<DevSolve> &hs, void **dspecs, int *count)
 {
-    const double dtt = dt_tab > 0.0 ? dt_tab : c.dt;
     std::map<std::tuple<double, double, double>, int> uniq;
     std::vector<TabSpec> specs;
     for (int b : ids) {
@@ -857,22 +900,60 @@ int make_tables(SimCtx &c, int n, const std::vector<int> &ids, std::vector<DevSo
         }
         hs[b].tab = it->second;
     }
+    *count = (int)specs.size();
+    CIL_TRY(c.cb->alloc(dspecs, sizeof(TabSpec) * specs.size()));
+    CIL_HIP(hipMemcpyAsync(*dspecs, specs.data(), sizeof(TabSpec) * specs.size(), hipMemcpyHostToDevice, c.st));
+    return CIL_OK;
+}
+
+template <typename T>
+int make_tables(SimCtx &c, int n, const std::vector<int> &ids, std::vector<DevSolve> &hs, void **tables, bool vform,
+                double dt_tab = 0.0)
+{
+    const double dtt = dt_tab > 0.0 ? dt_tab : c.dt;
     void *dspecs;
-    CIL_TRY(c.cb->alloc(&dspecs, sizeof(TabSpec) * specs.size()));
-    CIL_HIP(hipMemcpyAsync(dspecs, specs.data(), sizeof(TabSpec) * specs.size(), hipMemcpyHostToDevice, c.st));
+    int count;
+    CIL_TRY(make_specs(c, ids, hs, &dspecs, &count));
     if (vform) {
         const size_t per = (size_t)2 * 3 * (n / 2 + 1) * n;
-        CIL_TRY(c.cb->alloc(tables, sizeof(T) * per * specs.size()));
-        dim3 grid((unsigned)((2 * (n / 2 + 1) * n + 255) / 256), (unsigned)specs.size());
-        hipLaunchKernelGGL(k_make_vtables<T>, grid, dim3(256), 0, c.st, (const TabSpec *)dspecs, (int)specs.size(), n,
-                           dtt, (T *)*tables);
+        CIL_TRY(c.cb->alloc(tables, sizeof(T) * per * count));
+        dim3 grid((unsigned)((2 * (n / 2 + 1) * n + 255) / 256), (unsigned)count);
+        hipLaunchKernelGGL(k_make_vtables<T>, grid, dim3(256), 0, c.st, (const TabSpec *)dspecs, count, n, dtt,
+                           (T *)*tables);
         return check_launch("k_make_vtables");
     }
-    CIL_TRY(c.cb->alloc(tables, sizeof(T) * (size_t)2 * n * n * specs.size()));
-    dim3 grid((2 * n * n + 255) / 256, (unsigned)specs.size());
-    hipLaunchKernelGGL(k_make_tables<T>, grid, dim3(256), 0, c.st, (const TabSpec *)dspecs, (int)specs.size(), n, dtt,
+    CIL_TRY(c.cb->alloc(tables, sizeof(T) * (size_t)2 * n * n * count));
+    dim3 grid((2 * n * n + 255) / 256, (unsigned)count);
+    hipLaunchKernelGGL(k_make_tables<T>, grid, dim3(256), 0, c.st, (const TabSpec *)dspecs, count, n, dtt,
                        (T *)*tables);
     return check_launch("k_make_tables");
+}
+
+// The matrix-core stepper's divisors (second != nullptr: a second set for the
+// second-order scheme's later steps, dt2) and, for sides without a folding of
+// their own, its constant blocks.
+struct MmTables {
+    void *tab = nullptr, *tab2 = nullptr, *cst = nullptr;
+};
+template <typename T>
+int make_mm_tables(SimCtx &c, int n, const std::vector<int> &ids, std::vector<DevSolve> &hs, MmTables *out,
+                   double dt2 = 0.0)
+{
+    void *dspecs;
+    int count;
+    CIL_TRY(make_specs(c, ids, hs, &dspecs, &count));
+    const size_t bytes = sizeof(T) * mm_table_elems(n) * count;
+    CIL_TRY(c.cb->alloc(&out->tab, bytes));
+    CIL_TRY(mm_make_tables<T>(n, (const TabSpec *)dspecs, count, c.dt, (T *)out->tab, c.st));
+    if (dt2 > 0.0) {
+        CIL_TRY(c.cb->alloc(&out->tab2, bytes));
+        CIL_TRY(mm_make_tables<T>(n, (const TabSpec *)dspecs, count, dt2, (T *)out->tab2, c.st));
+    }
+    if (mm_const_elems(n)) {
+        CIL_TRY(c.cb->alloc(&out->cst, sizeof(T) * mm_const_elems(n)));
+        CIL_TRY(mm_make_consts<T>(n, (T *)out->cst, c.st));
+    }
+    return CIL_OK;
 }
 
 // Per-solve results of fused launches (steps, last residual, status and, for
@@ -901,23 +982,62 @@ int fetch_results(SimCtx &c, int B, const long long *dsteps, const double *dres,
     return stream_wait(c.st);
 }
 
+// FP64 tables of the FP64-step polish, and the mixed launch, for either kind of
+// kernel.  mode as launch_quad_mixed's.
+int polish_tables(SimCtx &c, int n, const std::vector<int> &ids, std::vector<DevSolve> &hs, FusedKind kind, void **tab)
+{
+    if (kind != KIND_MM) return make_tables<double>(c, n, ids, hs, tab, kQuadShape[quad_shape(false, n)].vform);
+    MmTables mt;
+    CIL_TRY(make_mm_tables<double>(c, n, ids, hs, &mt));
+    *tab = mt.tab;
+    return CIL_OK;
+}
+
+int launch_mixed_named(FusedKind kind, int n, int nl, const DevSolve *S, const int *list, float *state,
+                       double *state64, const float *tab32, const double *tab64, int model, double dt,
+                       const PersistArgs &pa32, const PersistArgs &pa64, long long *sw, int refine, int mode,
+                       hipStream_t st)
+{
+    static const char *names[2][2][3] = {
+        {{"k_fused_q_mixed_n32", "k_fused_q_mixed_n32_phase1", "k_fused_q_mixed_n32_phase2"},
+         {"k_fused_q_mixed_n64", "k_fused_q_mixed_n64_phase1", "k_fused_q_mixed_n64_phase2"}},
+        {{"k_mm_mixed_n32", "k_mm_mixed_n32_phase1", "k_mm_mixed_n32_phase2"},
+         {"k_mm_mixed_n64", "k_mm_mixed_n64_phase1", "k_mm_mixed_n64_phase2"}}};
+    const char *name = names[kind == KIND_MM][n == 64][mode];
+    const ProfMark pm = prof_begin(name, st);
+    const int rc = kind == KIND_MM ? launch_mm_mixed(n, nl, S, list, state, state64, tab32, tab64, model, dt, pa32,
+                                                     pa64, sw, refine, mode, st)
+                                   : launch_quad_mixed(n, nl, S, list, state, state64, tab32, tab64, model, dt, pa32,
+                                                       pa64, sw, refine, mode, st);
+    prof_end(pm, st);
+    if (rc) return set_error(rc, "no mixed-precision kernel for n = %d", n);
+    return check_launch(name);
+}
+
 // Fused solves, all sides in one go: every workgroup runs its solve from
 // steps[b] until its stop rule fires.  `dsteps/dres/dstat` are per-solve
 // device arrays; the host copies are refreshed after the launches.
 template <typename T>
 int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, DevSolve *dS, T *state,
-              bool quad, double floor_coef, long long *dsteps, double *dres, int *dstat, const MixedArgs *mx = nullptr)
+              FusedKind kind, double floor_coef, long long *dsteps, double *dres, int *dstat,
+              const MixedArgs *mx = nullptr)
 {
     if (byn.empty()) return CIL_OK;
+    const bool quad = kind != KIND_LINE;
     std::vector<void *> tabs, tabs64;
+    std::vector<MmTables> mms;
     std::vector<char> mixed;
     for (auto &kv : byn) {
-        void *t, *t64 = nullptr;
-        CIL_TRY(make_tables<T>(c, kv.first, kv.second, hs, &t,
-                               quad && kQuadShape[quad_shape(std::is_same<T, float>::value, kv.first)].vform));
-        const bool mix = mx && mixed_supported(kv.first, quad);
-        if (mix && !mx->refine && !g_polish_separate)
-            CIL_TRY(make_tables<double>(c, kv.first, kv.second, hs, &t64, kQuadShape[quad_shape(false, kv.first)].vform));
+        void *t = nullptr, *t64 = nullptr;
+        MmTables mt;
+        const bool mix = mx && mixed_supported(kv.first, kind);
+        if (kind == KIND_MM)
+            CIL_TRY(make_mm_tables<T>(c, kv.first, kv.second, hs, &mt));
+        else
+            CIL_TRY(make_tables<T>(c, kv.first, kv.second, hs, &t,
+                                   quad && kQuadShape[quad_shape(std::is_same<T, float>::value, kv.first)].vform));
+        mms.push_back(mt);
+        if (mix && !mx->refine && !g_polish_separate) CIL_TRY(polish_tables(c, kv.first, kv.second, hs, kind, &t64));
         tabs.push_back(t);
         tabs64.push_back(t64);
         mixed.push_back(mix);
@@ -948,8 +1068,10 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
     }
     AuxStreams *aux = nullptr;
     const int ng = (int)byn.size();
+    // a side per stream, at most eight streams (a batch may hold a hundred sides; four hardware queues serve them)
+    const int nst = std::min(ng, 8);
     if (ng > 1) {
-        CIL_TRY(aux_streams(ng, &aux));
+        CIL_TRY(aux_streams(nst, ng, &aux));
         CIL_HIP(hipEventRecord(aux->ev[0], c.st));
     }
     std::vector<const std::pair<const int, std::vector<int>> *> groups;
@@ -959,7 +1081,7 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
         const auto &kv = *groups[gi];
         hipStream_t gst = c.st;
         if (aux) {
-            gst = aux->st[gi];
+            gst = aux->st[gi % nst];
             CIL_HIP(hipStreamWaitEvent(gst, aux->ev[0], 0));
         }
         const int shape = quad_shape(std::is_same<T, float>::value, kv.first);
@@ -970,15 +1092,10 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
                 // separate polish: the FP32 phase here, the continuation in a
                 // launch of its own over the solves at their floor (run_phase2)
                 const int mode = g_polish_separate ? 1 : 0;
-                const ProfMark pm = prof_begin(kv.first == 32 ? (mode ? "k_fused_q_mixed_n32_phase1" : "k_fused_q_mixed_n32")
-                                                              : (mode ? "k_fused_q_mixed_n64_phase1" : "k_fused_q_mixed_n64"),
-                                               gst);
-                const int rc = launch_quad_mixed(kv.first, (int)kv.second.size(), dS, dls[gi], state, mx->state64,
-                                                 (const float *)tabs[gi], (const double *)tabs64[gi], c.model, c.dt,
-                                                 pa, pa64, mx->sw, mx->refine, mode, gst);
-                prof_end(pm, gst);
-                if (rc) return set_error(rc, "no mixed-precision kernel for n = %d", kv.first);
-                CIL_TRY(check_launch("k_fused_q_mixed"));
+                CIL_TRY(launch_mixed_named(kind, kv.first, (int)kv.second.size(), dS, dls[gi], state, mx->state64,
+                                           (const float *)(kind == KIND_MM ? mms[gi].tab : tabs[gi]),
+                                           (const double *)tabs64[gi], c.model, c.dt, pa, pa64, mx->sw, mx->refine,
+                                           mode, gst));
                 if (aux) {
                     CIL_HIP(hipEventRecord(aux->ev[1 + gi], gst));
                     CIL_HIP(hipStreamWaitEvent(c.st, aux->ev[1 + gi], 0));
@@ -986,8 +1103,12 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
                 continue;
             }
         }
-        CIL_TRY(launch_persistent<T>(kv.first, quad, shape, (int)kv.second.size(), dS, dls[gi], state,
-                                     (const T *)tabs[gi], c.model, c.dt, pa, gst));
+        if (kind == KIND_MM)
+            CIL_TRY(launch_mm_named<T>(kv.first, 0, (int)kv.second.size(), dS, dls[gi], state, (const T *)mms[gi].tab,
+                                       nullptr, (const T *)mms[gi].cst, c.model, c.dt, pa, gst));
+        else
+            CIL_TRY(launch_persistent<T>(kv.first, quad, shape, (int)kv.second.size(), dS, dls[gi], state,
+                                         (const T *)tabs[gi], c.model, c.dt, pa, gst));
         if (aux) {
             CIL_HIP(hipEventRecord(aux->ev[1 + gi], gst));
             CIL_HIP(hipStreamWaitEvent(c.st, aux->ev[1 + gi], 0));
@@ -1010,16 +1131,22 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
 // or the refinement form with `refine`.  state64: same element layout as
 // `state`.
 int run_phase2(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, DevSolve *dS,
-               float *state, double *state64, long long *sw, bool refine, long long *dsteps, double *dres, int *dstat)
+               FusedKind kind, float *state, double *state64, long long *sw, bool refine, long long *dsteps,
+               double *dres, int *dstat)
 {
     if (byn.empty()) return CIL_OK;
     const int B = (int)hs.size();
     std::vector<void *> tabs, tabs64;
     for (auto &kv : byn) {
         void *t, *t64 = nullptr;
-        CIL_TRY(make_tables<float>(c, kv.first, kv.second, hs, &t, kQuadShape[quad_shape(true, kv.first)].vform));
-        if (!refine)
-            CIL_TRY(make_tables<double>(c, kv.first, kv.second, hs, &t64, kQuadShape[quad_shape(false, kv.first)].vform));
+        if (kind == KIND_MM) {
+            MmTables mt;
+            CIL_TRY(make_mm_tables<float>(c, kv.first, kv.second, hs, &mt));
+            t = mt.tab;
+        } else {
+            CIL_TRY(make_tables<float>(c, kv.first, kv.second, hs, &t, kQuadShape[quad_shape(true, kv.first)].vform));
+        }
+        if (!refine) CIL_TRY(polish_tables(c, kv.first, kv.second, hs, kind, &t64));
         tabs.push_back(t);
         tabs64.push_back(t64);
     }
@@ -1032,15 +1159,10 @@ int run_phase2(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vecto
         int *dl;
         CIL_TRY(c.cb->alloc((void **)&dl, sizeof(int) * kv.second.size()));
         CIL_HIP(hipMemcpyAsync(dl, kv.second.data(), sizeof(int) * kv.second.size(), hipMemcpyHostToDevice, c.st));
-        const ProfMark pm =
-            prof_begin(kv.first == 32 ? "k_fused_q_mixed_n32_phase2" : "k_fused_q_mixed_n64_phase2", c.st);
-        const int rc = launch_quad_mixed(kv.first, (int)kv.second.size(), dS, dl, state, state64,
-                                         (const float *)tabs[gi], (const double *)tabs64[gi], c.model, c.dt, pa, pa,
-                                         sw, refine, 2, c.st);
+        CIL_TRY(launch_mixed_named(kind, kv.first, (int)kv.second.size(), dS, dl, state, state64,
+                                   (const float *)tabs[gi], (const double *)tabs64[gi], c.model, c.dt, pa, pa, sw,
+                                   refine, 2, c.st));
         ++gi;
-        prof_end(pm, c.st);
-        if (rc) return set_error(rc, "no mixed-precision kernel for n = %d", kv.first);
-        CIL_TRY(check_launch("k_fused_q_mixed"));
     }
     HostResults h;
     CIL_TRY(fetch_results(c, B, dsteps, dres, dstat, nullptr, &h));
@@ -1210,7 +1332,7 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     c.status.assign(B, CIL_SOLVE_OK);
     const bool polish = f32 && stp->polish && stp->tol > 0.0;
     c.polish = polish ? stp->polish : 0;
-    const bool quad = stp->path != CIL_PATH_FUSED_LINE;
+    const FusedKind kind = fused_kind(stp->path);
     if (scheme) {
         if (stp->path == CIL_PATH_FUSED_QUAD)
             return set_error(CIL_EUNSUPPORTED, "the second-order stepper has no quad-lane kernel");
@@ -1241,11 +1363,12 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     std::map<int, std::vector<int>> fused_byn, plain_byn;
     for (int b = 0; b < B; ++b) {
         const int n = hs[b].n;
-        const bool fs = scheme ? sbdf2_fused_supported(n, f32) : fused_supported(n, f32);
+        const bool fs = scheme ? sbdf2_fused_supported(n, f32) && stp->path != CIL_PATH_PLAIN
+                               : persistent_supported(n, f32, stp->path);
         if (stp->path >= CIL_PATH_FUSED && !fs)
             return set_error(CIL_EUNSUPPORTED, "no fused %sstepper for n = %d in %s", scheme ? "second-order " : "", n,
                              f32 ? "FP32" : "FP64");
-        if (fs && stp->path != CIL_PATH_PLAIN) fused_byn[n].push_back(b);
+        if (fs) fused_byn[n].push_back(b);
         else plain_byn[n].push_back(b);
     }
     if (scheme && !plain_byn.empty()) {              // the plain back-end keeps the history in HBM
@@ -1273,7 +1396,7 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     MixedArgs mx{nullptr, nullptr, c.polish == 2};
     bool use_mixed = false;
     if (polish)
-        for (auto &kv : fused_byn) use_mixed |= mixed_supported(kv.first, quad);
+        for (auto &kv : fused_byn) use_mixed |= mixed_supported(kv.first, kind);
     if (use_mixed) {
         int64_t end = 0;
         for (int b = 0; b < B; ++b) end = std::max<int64_t>(end, hs[b].off + elems[b]);
@@ -1284,10 +1407,10 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         if (f32) CIL_TRY(run_fused_sbdf2<float>(c, fused_byn, hs, dS, (float *)state, c.floor_coef32, dsteps, dres, dstat));
         else CIL_TRY(run_fused_sbdf2<double>(c, fused_byn, hs, dS, (double *)state, 0.0, dsteps, dres, dstat));
     } else if (f32) {
-        CIL_TRY(run_fused<float>(c, fused_byn, hs, dS, (float *)state, quad, c.floor_coef32, dsteps, dres, dstat,
+        CIL_TRY(run_fused<float>(c, fused_byn, hs, dS, (float *)state, kind, c.floor_coef32, dsteps, dres, dstat,
                                  use_mixed ? &mx : nullptr));
     } else {
-        CIL_TRY(run_fused<double>(c, fused_byn, hs, dS, (double *)state, quad, 0.0, dsteps, dres, dstat));
+        CIL_TRY(run_fused<double>(c, fused_byn, hs, dS, (double *)state, kind, 0.0, dsteps, dres, dstat));
     }
     if (!plain_byn.empty()) {
         CIL_HIP(hipMemcpyAsync(dS, hs.data(), sizeof(DevSolve) * B, hipMemcpyHostToDevice, st));
@@ -1316,7 +1439,7 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     if (!cont_byn.empty()) {
         for (auto &kv : cont_byn)
             for (int b : kv.second) c.status[b] = CIL_SOLVE_OK;
-        CIL_TRY(run_phase2(c, cont_byn, hs, dS, (float *)state, mx.state64, mx.sw, c.polish == 2, dsteps, dres,
+        CIL_TRY(run_phase2(c, cont_byn, hs, dS, kind, (float *)state, mx.state64, mx.sw, c.polish == 2, dsteps, dres,
                            dstat));
         for (auto &kv : cont_byn)
             for (int b : kv.second) steps64[b] = c.steps[b] - c.sw[b];
@@ -1346,10 +1469,10 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         std::map<std::pair<int, int64_t>, std::vector<int>> pz;        // (n, start) -> solves (plain FP64)
         for (int b : promoted) {
             c.status[b] = CIL_SOLVE_OK;
-            if (fused_supported(hs[b].n, false) && stp->path != CIL_PATH_PLAIN) fz[hs[b].n].push_back(b);
+            if (persistent_supported(hs[b].n, false, stp->path)) fz[hs[b].n].push_back(b);
             else pz[std::make_pair(hs[b].n, c.steps[b])].push_back(b);
         }
-        CIL_TRY(run_fused<double>(c, fz, hs64, dS64, state64, quad, 0.0, dsteps, dres, dstat));
+        CIL_TRY(run_fused<double>(c, fz, hs64, dS64, state64, kind, 0.0, dsteps, dres, dstat));
         if (!pz.empty()) CIL_HIP(hipMemcpyAsync(dS64, hs64.data(), sizeof(DevSolve) * B, hipMemcpyHostToDevice, st));
         for (auto &kv : pz) {
             std::map<int, std::vector<int>> one;
@@ -1393,13 +1516,15 @@ struct SimPlan {
         int n = 0;
         std::vector<int> ids;
         int shape = 0;
-        void *tab[2] = {nullptr, nullptr};    // X-form, V-form divisor tables
+        void *tab[2] = {nullptr, nullptr};    // X-form, V-form divisor tables (line and quad kernels)
+        MmTables mm;                          // matrix-core kernel's
+        bool use_mm = false;
         int *dl = nullptr;
         double tuned_ms[kQuadShapes] = {};
     };
     int dev = 0;
     int model = 0;
-    bool f32 = false, quad = true;
+    bool f32 = false, quad = true, mm = false;    // mm: groups run on the matrix cores unless tuning finds a faster shape
     double dt = 0.0;
     PersistArgs pa{};
     void *state = nullptr;
@@ -1442,8 +1567,30 @@ int plan_tables(SimPlan &p, SimPlan::Group &g, int shape, hipStream_t st)
     return CIL_OK;
 }
 
+int plan_mm_tables(SimPlan &p, SimPlan::Group &g, hipStream_t st)
+{
+    SimCtx c;
+    c.model = p.model;
+    c.dt = p.dt;
+    c.st = st;
+    c.cb = &p.bufs;
+    if (p.f32) CIL_TRY(make_mm_tables<float>(c, g.n, g.ids, p.hs, &g.mm));
+    else CIL_TRY(make_mm_tables<double>(c, g.n, g.ids, p.hs, &g.mm));
+    CIL_HIP(hipMemcpyAsync(p.dS, p.hs.data(), sizeof(DevSolve) * p.B, hipMemcpyHostToDevice, st));
+    return CIL_OK;
+}
+
+// shape < 0: the matrix-core kernel
 int plan_launch_group(SimPlan &p, SimPlan::Group &g, int shape, void *state, const PersistArgs &pa, hipStream_t st)
 {
+    if (shape < 0) {
+        if (p.f32)
+            return launch_mm_named<float>(g.n, 0, (int)g.ids.size(), p.dS, g.dl, (float *)state, (const float *)g.mm.tab,
+                                          nullptr, (const float *)g.mm.cst, p.model, p.dt, pa, st);
+        return launch_mm_named<double>(g.n, 0, (int)g.ids.size(), p.dS, g.dl, (double *)state,
+                                       (const double *)g.mm.tab, nullptr, (const double *)g.mm.cst, p.model, p.dt, pa,
+                                       st);
+    }
     const int vf = (p.quad && kQuadShape[shape].vform) ? 1 : 0;
     if (p.f32)
         return launch_persistent<float>(g.n, p.quad, shape, (int)g.ids.size(), p.dS, g.dl, (float *)state,
@@ -1462,7 +1609,10 @@ int plan_enqueue(SimPlan &p)
     const int ng = (int)p.groups.size();
     if (ng > 1) CIL_HIP(hipEventRecord(p.ev[0], cs));
     for (int g = 1; g < ng; ++g) CIL_HIP(hipStreamWaitEvent(p.st[g], p.ev[0], 0));
-    for (int g = 0; g < ng; ++g) CIL_TRY(plan_launch_group(p, p.groups[g], p.groups[g].shape, p.state, p.pa, p.st[g]));
+    for (int g = 0; g < ng; ++g) {
+        SimPlan::Group &gr = p.groups[g];
+        CIL_TRY(plan_launch_group(p, gr, gr.use_mm ? -1 : gr.shape, p.state, p.pa, p.st[g]));
+    }
     for (int g = 1; g < ng; ++g) {
         CIL_HIP(hipEventRecord(p.ev[g], p.st[g]));
         CIL_HIP(hipStreamWaitEvent(cs, p.ev[g], 0));
@@ -1503,7 +1653,9 @@ int plan_create(cil_model model, cil_precision prec, const cil_problem *probs, i
     CIL_TRY(current_device(&p->dev));
     p->model = (int)model;
     p->f32 = f32;
-    p->quad = stp->path != CIL_PATH_FUSED_LINE;
+    const FusedKind kind = fused_kind(stp->path);
+    p->quad = kind != KIND_LINE;
+    p->mm = kind == KIND_MM;
     p->dt = stp->dt;
     p->state = state;
     p->B = B;
@@ -1550,11 +1702,12 @@ int plan_create(cil_model model, cil_precision prec, const cil_problem *probs, i
         g.n = o.second;
         g.ids = byn[g.n];
         g.shape = p->quad ? quad_shape(f32, g.n) : 0;
+        g.use_mm = p->mm;
         CIL_TRY(p->bufs.alloc((void **)&g.dl, sizeof(int) * g.ids.size()));
         CIL_HIP(hipMemcpyAsync(g.dl, g.ids.data(), sizeof(int) * g.ids.size(), hipMemcpyHostToDevice, st));
         p->groups.push_back(g);
     }
-    for (auto &g : p->groups) CIL_TRY(plan_tables(*p, g, g.shape, st));
+    for (auto &g : p->groups) CIL_TRY(p->mm ? plan_mm_tables(*p, g, st) : plan_tables(*p, g, g.shape, st));
     const int ng = (int)p->groups.size();
     for (int g = 0; g < std::max(ng, 1); ++g) {
         hipStream_t s;
@@ -1594,9 +1747,12 @@ int plan_tune(SimPlan *p, int64_t steps, hipStream_t st)
     CIL_HIP(hipEventCreate(&b));
     int rc = CIL_OK;
     for (auto &g : p->groups) {
+        // the quad-lane shapes, then (shape -1) the matrix-core kernel where the plan's path includes it
         int best = -1;
-        for (int s = 0; s < kQuadShapes && rc == CIL_OK; ++s) {
-            rc = plan_tables(*p, g, s, st);
+        for (int s = 0; s <= kQuadShapes && rc == CIL_OK; ++s) {
+            const bool mm = s == kQuadShapes;
+            if (mm && !p->mm) break;
+            if (!mm) rc = plan_tables(*p, g, s, st);
             float ms = 0.0f;
             for (int rep = 0; rep < 2 && rc == CIL_OK; ++rep) {
                 // every trial starts from the same states (a copy of the bound state)
@@ -1606,12 +1762,16 @@ int plan_tune(SimPlan *p, int64_t steps, hipStream_t st)
                     if (rc == CIL_OK) rc = set_error(CIL_EDEVICE, "tuning copy failed");
                     break;
                 }
-                rc = plan_launch_group(*p, g, s, scratch, pa, st);
+                rc = plan_launch_group(*p, g, mm ? -1 : s, scratch, pa, st);
                 if (rc == CIL_OK && (hipEventRecord(b, st) != hipSuccess || hipEventSynchronize(b) != hipSuccess ||
                                      hipEventElapsedTime(&ms, a, b) != hipSuccess))
                     rc = set_error(CIL_EDEVICE, "tuning timing failed");
             }
             if (rc != CIL_OK) break;
+            if (mm) {
+                g.use_mm = ms <= g.tuned_ms[best];
+                break;
+            }
             g.tuned_ms[s] = ms;
             if (best < 0 || ms < g.tuned_ms[best]) best = s;
         }

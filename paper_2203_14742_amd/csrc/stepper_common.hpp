@@ -147,6 +147,38 @@ __device__ __forceinline__ void set_issue_priority(double ratio, double base)
     else __builtin_amdgcn_s_setprio(0);
 }
 
+// Steps between two re-basings of the refinement form (U += v, v = 0).
+constexpr int kRebase = 200;
+
+// One spectral table: 1/h^2 and the two diffusion coefficients.
+struct TabSpec {
+    double inv_h2, nu0, nu1;
+};
+
+// Matrix-core stepper, one translation unit per precision (stepper_mm_*.hip).
+// Sides 32, 64 and 128 fold down to 16-point blocks; any other side up to 128
+// takes one fold and dense products, padded to a multiple of 32.  FP64 needs
+// the field of both species in LDS, which holds a side of at most 96.
+constexpr bool mm_exact(int n) { return n == 32 || n == 64 || n == 128; }
+constexpr int mm_padded(int n) { return 32 * (((n + 1) / 2 + 15) / 16); }
+constexpr int mm_max_side(bool f32) { return f32 ? 128 : 96; }
+// divisor table elements per spec, and elements of the constant blocks (0: none)
+constexpr size_t mm_table_elems(int n) { return (size_t)2 * mm_padded(n) * mm_padded(n); }
+constexpr size_t mm_const_elems(int n) { return mm_exact(n) ? 0 : (size_t)3 * (mm_padded(n) / 32) * (mm_padded(n) / 32) * 256; }
+template <typename T>
+int mm_make_tables(int n, const TabSpec *specs, int ntab, double dt, T *out, hipStream_t st);
+template <typename T>
+int mm_make_consts(int n, T *out, hipStream_t st);
+// scheme 0: IMEX Euler (tab), 1: second order (tab for the first step, tab2 for the others)
+template <typename T>
+int launch_mm(int n, int scheme, int nl, const DevSolve *S, const int *list, T *state, const T *tab, const T *tab2,
+              const T *cst, int model, double dt, const PersistArgs &pa, hipStream_t st);
+
+// FP32 steps and the polish in one launch (or two, by mode), n = 32 and 64.
+int launch_mm_mixed(int n, int nl, const DevSolve *S, const int *list, float *state, double *state64,
+                    const float *tab32, const double *tab64, int model, double dt, const PersistArgs &pa32,
+                    const PersistArgs &pa64, long long *switch_step, int refine, int mode, hipStream_t st);
+
 // Mixed-precision quad launch (stepper_quad_mixed.hip): n = 32 and 64 with the
 // default shapes (FP32 shape 1 / FP64 shape 1 at n = 32, 2 / 0 at n = 64).
 // refine = 1: the continuation is the refinement form (FP64 state in state64,

@@ -1,0 +1,533 @@
+// The matrix-core persistent stepper (templates): one workgroup per solve,
+// every grid line transformed on the matrix cores (dct_mfma.hpp).
+//
+// Work split.  A wavefront owns eight grid lines of both species - the 16
+// columns of its MFMA tiles, lanes with l % 16 < 8 species v, the others w, so
+// that lane l ^ 8 (a rotation by eight within the row of 16 lanes) holds the
+// other species at the same points.  n/8 wavefronts cover the grid.  The field
+// lives in LDS in slot order, [species][row slot][column slot], rows padded by
+// four values: the row pass's 16-byte accesses and the column pass's strided
+// ones are then both free of bank conflicts (a half wavefront's addresses
+// fall on distinct banks; the species' planes are eight values apart).
+// One step is two passes, each in place on the wavefront's own lines and each
+// ending with the workgroup barrier:
+//   row pass     row inverse (u^s in registers), stop rule and snapshot at
+//                evaluation steps, explicit reaction, row forward;
+//   column pass  column forward, spectral divide, column inverse.
+// The constants of the transforms and (where they fit) the divisors stay in
+// registers from the first step to the last.
+//
+// What bounds it: the matrix cores' issue.  A step of a 64^2 solve is 64
+// products of 32 cycles (FP32) per wavefront and two wavefronts a SIMD, 4096
+// cycles, with the folds, rotations and reaction issued beside them by the
+// other wavefront.
+#pragma once
+
+#include "dct_mfma.hpp"
+#include "dct_quad.hpp"
+#include "stepper_common.hpp"
+
+namespace cil {
+
+// The reaction of the lane's own species, F = f (sp = 0) or g (sp = 1), from
+// its own value and the other species', with per-lane coefficients so that
+// both kinds of lane run the same instructions.
+template <int MODEL, typename T>
+struct OwnReaction {
+    T A, B, C;
+    bool w;
+    __device__ __forceinline__ void init(const double *p, int sp)
+    {
+        w = sp != 0;
+        A = B = C = T(0);
+        if constexpr (MODEL == CIL_FHN) {               // A other + (B + C own^2) own
+            A = w ? T(-1) : T(p[1]);
+            B = w ? T(p[0]) : T(-p[1] * p[2]);
+            C = w ? T(-1) : T(0);
+        } else if constexpr (MODEL == CIL_GM) {         // B own + v^2 (1/w or 1)
+            B = w ? T(-p[1]) : T(-p[0]);
+        } else if constexpr (MODEL == CIL_GM_SOURCE) {  // A + B own + v^2 (1/w or 1)
+            A = w ? T(0) : T(p[0]);
+            B = w ? T(-1) : T(-p[1]);
+        } else if constexpr (MODEL == CIL_BRUSSELATOR) {   // A + B v + C v^2 w
+            A = w ? T(0) : T(p[0]);
+            B = w ? T(p[1]) : T(-(p[1] + 1.0));
+            C = w ? T(-1) : T(1);
+        }
+    }
+    __device__ __forceinline__ T operator()(T own, T oth) const
+    {
+        if constexpr (MODEL == CIL_FHN) {
+            return fma(own, fma(C, own * own, B), A * oth);   // (explicit: every kernel rounds it alike)
+        } else if constexpr (MODEL == CIL_GM || MODEL == CIL_GM_SOURCE) {
+            const T v = w ? oth : own;
+            const T r = w ? T(1) : recip(oth);
+            return fma(v * v, r, fma(B, own, A));
+        } else if constexpr (MODEL == CIL_BRUSSELATOR) {
+            const T v = w ? oth : own, z = w ? own : oth;
+            return fma(C, v * v * z, fma(B, v, A));
+        } else {
+            return T(0);
+        }
+    }
+};
+
+// The homogeneous steady state of the lane's species (Sec. 4.1), or 0.  The
+// diffusion solve leaves a constant as it is, so FP32 transforms act on
+// u - u* instead of u: their rounding is then relative to the pattern's
+// amplitude and not to its mean (0 where the state is far smaller than u*,
+// which would cost digits instead).
+template <int MODEL>
+__device__ __forceinline__ double steady_value(const double *p, int sp)
+{
+    double v = 0.0, w = 0.0;
+    if constexpr (MODEL == CIL_GM) {
+        v = p[1] / p[0];
+        w = p[1] / (p[0] * p[0]);
+    } else if constexpr (MODEL == CIL_GM_SOURCE) {
+        v = (p[0] + 1.0) / p[1];
+        w = v * v;
+    } else if constexpr (MODEL == CIL_BRUSSELATOR) {
+        v = p[0];
+        w = p[1] / p[0];
+    }
+    return sp ? w : v;
+}
+
+// TPW: tiles of eight lines per wavefront (tile = wavefront + WAVES k).  Two
+// tiles share one copy of the constants and give the matrix cores independent
+// products from one wavefront.
+template <typename T, typename Line, int TPW>
+struct MmShape {
+    static constexpr int N = Line::N, NS = Line::NS;          // N: padded side
+    static constexpr int WAVES = N / (8 * TPW), THREADS = 64 * WAVES;
+    static constexpr int LD = N + 4, SP = N * LD + 8;         // LDS strides, in values
+    static constexpr int LDS = 2 * SP;
+    // divisors in registers: 4 NS values a lane, where that is at most 16 VGPRs
+    static constexpr bool DREG = TPW * NS * sizeof(T) <= 16;
+};
+
+// One solve.  SCHEME 0: IMEX Euler (divisors dtab); 1: the second-order scheme
+// (dtab for the first step of the call, dtab2, built with 2 dt / 3, for the
+// others; u^{s-2} and F(u^{s-2}) in registers).  The lane's values of u live in
+// x: loaded from `state` first when LOAD, stored to `out` (element type TS) at
+// the end.  `step` enters as the first step and leaves as the last; returns
+// the status of the last evaluation (-1 if none ran).
+//
+// RF: the refinement form u = U + v (k_fused_q's, stepper_quad.hpp): U in FP64
+// in u64, the FP32 correction v in x, R = f(U) + nu Lap U rounded to FP32 in
+// LDS behind the field (lane-major, 16 bytes a lane).  Lap U is formed in FP64
+// from one species' U at a time, staged in the LDS of the field.
+template <typename T, typename Line, int TPW, int MODEL, int SCHEME, bool RF, bool LOAD, typename TS>
+__device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const DevSolve &s, int b, T *state, TS *out,
+                                        const T *dtab, const T *dtab2, const T *cst, double dt, const PersistArgs &pa,
+                                        long long &step, Vec4<T> (&x)[TPW][Line::NS], double *u64 = nullptr)
+{
+    static_assert(!RF || (std::is_same<T, float>::value && SCHEME == 0 && !Line::kRagged), "");
+    using V = Vec4<T>;
+    using SH = MmShape<T, Line, TPW>;
+    constexpr int NS = Line::NS, LD = SH::LD, SP = SH::SP, WAVES = SH::WAVES, THREADS = SH::THREADS;
+    constexpr bool RAG = Line::kRagged;
+    constexpr int ROR8 = 0x128;                               // DPP: rotate by 8 within 16 lanes
+    constexpr int STEP = 8 * WAVES;                           // lines between a wavefront's tiles
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int c = lane & 15, sp = c >> 3, g4 = 4 * (lane >> 4);
+    const int line = 8 * wave + (c & 7);                      // the lane's row (and column) slot in its first tile
+    const int n = RAG ? s.n : Line::N;
+    const int NN = n * n;
+    Line L;
+    L.init(cst, lane);
+    OwnReaction<MODEL, T> react;
+    react.init(s.p, sp);
+    const T tdt = T(dt);
+    T *const row = sm + sp * SP + line * LD + g4;             // slots hb * 16 + g4 + i of the lane's row
+    T *const col = sm + sp * SP + g4 * LD + line;             // the same of its column, stride LD
+    const size_t dsz = (size_t)2 * SH::N * SH::N;
+    const T *dp = dtab + s.tab * dsz + (size_t)wave * NS * 256 + lane * 4;
+    const T *dp2 = SCHEME ? dtab2 + s.tab * dsz + (size_t)wave * NS * 256 + lane * 4 : dp;
+    const auto ub = make_rsrc(state + s.off, 2u * NN * sizeof(T));
+
+    // Element offset of slot (hb, i) of tile k within the solve's state; -1:
+    // padding.  `at` is the lane's base, taken anew by each user: the offsets
+    // are then formed where they are used instead of being kept in registers
+    // across the step loop.
+    struct Base {
+        int e, g, rn;
+        bool ok;
+    };
+    auto element_base = [&](int k) __attribute__((always_inline)) {
+        int ln = line + STEP * k, g = g4;
+        asm volatile("" : "+v"(ln), "+v"(g));
+        const int rn = slot_pos<Line>(ln >> 4, ln & 15, n);   // the lane's grid row
+        return Base{(sp * n + rn) * n, g, rn, slot_valid<Line>(ln >> 4, ln & 15, n)};
+    };
+    auto elem = [&](const Base &at, int hb, int i) __attribute__((always_inline)) -> int {
+        const int e = at.e + slot_pos<Line>(hb, at.g + i, n);
+        if constexpr (RAG) return at.ok && slot_valid<Line>(hb, at.g + i, n) ? e : -1;
+        else return e;
+    };
+    // padding carries no value (and no NaN) into the transforms: masks of the lane's real slots
+    unsigned real[TPW] = {};
+    if constexpr (RAG) {
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) {
+            const Base at = element_base(k);
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) real[k] |= (elem(at, hb, i) >= 0 ? 1u : 0u) << (hb * 4 + i);
+        }
+    }
+    auto masked = [&](T v, unsigned bits, int j) __attribute__((always_inline)) -> T {
+        const int m = __builtin_amdgcn_sbfe((int)bits, j, 1);
+        if constexpr (sizeof(T) == 8)
+            return __hiloint2double(__double2hiint(v) & m, __double2loint(v) & m);
+        else
+            return __int_as_float(__float_as_int(v) & m);
+    };
+    // f(k, hb, i, element) over the lane's slots
+    auto each = [&](auto &&f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) {
+            const Base at = element_base(k);
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f(k, hb, i, elem(at, hb, i));
+        }
+    };
+    // padding reads 0 and is not written (its offset lies past the resource)
+    auto ld = [&](auto rsrc, auto type, int e) __attribute__((always_inline)) {
+        using E = decltype(type);
+        return buf_load<E>(rsrc, e < 0 ? 0xFFFFFF00u : (unsigned)e * (unsigned)sizeof(E), 0);
+    };
+    auto stv = [&](auto rsrc, auto v, int e) __attribute__((always_inline)) {
+        using E = decltype(v);
+        buf_store<E>(v, rsrc, e < 0 ? 0xFFFFFF00u : (unsigned)e * (unsigned)sizeof(E), 0);
+    };
+    if constexpr (LOAD) each([&](int k, int hb, int i, int e) { x[k][hb][i] = ld(ub, T(0), e); });
+    // constant the transforms leave out (FP32 without a correction form)
+    T c0 = T(0);
+    if constexpr (sizeof(T) == 4 && !RF && MODEL != CIL_FHN && MODEL != CIL_HEAT) {
+        double a = 0.0;
+#pragma unroll
+        for (int k = 0; k < TPW; ++k)
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a = fmax(a, fabs((double)x[k][hb][i]));
+        // over the lanes of one species, then over the wavefronts
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1)
+            if (o != 8) a = fmax(a, __shfl_xor(a, o, 64));
+        __syncthreads();
+        if ((lane & ~8) == 0) red[sp * WAVES + wave] = a;
+        __syncthreads();
+        a = 0.0;
+        for (int w = 0; w < WAVES; ++w) a = fmax(a, red[sp * WAVES + w]);
+        const double u0 = steady_value<MODEL>(s.p, sp);
+        c0 = fabs(u0) <= 4.0 * a ? T(u0) : T(0);              // (NaN compares false)
+        __syncthreads();
+    }
+    constexpr int DT = WAVES * NS * 256;                      // divisors between a wavefront's tiles
+    V dv[TPW][NS];
+    auto load_div = [&](const T *p, int k) __attribute__((always_inline)) {
+#pragma unroll
+        for (int hb = 0; hb < NS; ++hb) dv[k][hb] = mm_load(p + k * DT + hb * 256);
+    };
+    if constexpr (SH::DREG) {
+#pragma unroll
+        for (int k = 0; k < TPW; ++k) load_div(dp, k);
+    }
+    // refinement form
+    V u32[RF ? TPW : 1][RF ? NS : 1];
+    V *const rq = RF ? reinterpret_cast<V *>(sm + SH::LDS) + tid : nullptr;
+    const auto u64r = make_rsrc(RF ? u64 + s.off : nullptr, RF ? 2u * NN * sizeof(double) : 0);
+    auto rebase = [&](bool first) __attribute__((always_inline)) {
+        if constexpr (RF) {
+            constexpr int DL = Line::N + 1;                   // row stride of the staged FP64 field
+            static_assert(Line::N * DL * sizeof(double) <= SH::LDS * sizeof(T), "one FP64 species fits the field");
+            double *const sd = reinterpret_cast<double *>(sm);
+            double U[TPW][NS][4], lap[TPW][NS][4];
+            each([&](int k, int hb, int i, int e) {
+                U[k][hb][i] = (double)x[k][hb][i];
+                if (!first) U[k][hb][i] += ld(u64r, 0.0, e);
+                stv(u64r, U[k][hb][i], e);
+                x[k][hb][i] = T(0);
+            });
+            for (int q = 0; q < 2; ++q) {
+                __syncthreads();                              // the LDS's last readers are done
+                if (sp == q) {
+#pragma unroll
+                    for (int k = 0; k < TPW; ++k) {
+                        const Base at = element_base(k);
+#pragma unroll
+                        for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                sd[at.rn * DL + slot_pos<Line>(hb, at.g + i, n)] = U[k][hb][i];
+                    }
+                }
+                __syncthreads();
+                if (sp == q) {
+#pragma unroll
+                    for (int k = 0; k < TPW; ++k) {
+                        const Base at = element_base(k);
+                        const int rn = at.rn, ru = rn > 0 ? rn - 1 : 0, rd = rn < n - 1 ? rn + 1 : n - 1;
+#pragma unroll
+                        for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) {
+                                const int p = slot_pos<Line>(hb, at.g + i, n);
+                                const int pl = p > 0 ? p - 1 : 0, pr = p < n - 1 ? p + 1 : n - 1;
+                                lap[k][hb][i] = (sd[rn * DL + pl] + sd[rn * DL + pr] + sd[ru * DL + p] +
+                                                 sd[rd * DL + p] - 4.0 * U[k][hb][i]) * s.inv_h2;
+                            }
+                    }
+                }
+            }
+            const double pd[4] = {s.p[0], s.p[1], s.p[2], s.p[3]}, nu = sp ? s.nu[1] : s.nu[0];
+#pragma unroll
+            for (int k = 0; k < TPW; ++k)
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb) {
+                    V r;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const double Us = U[k][hb][i], Uo = dpp_mov<ROR8>(U[k][hb][i]);
+                        double f, gg;
+                        kinetics<MODEL>(pd, sp ? Uo : Us, sp ? Us : Uo, f, gg);
+                        r[i] = (T)((sp ? gg : f) + nu * lap[k][hb][i]);
+                        u32[k][hb][i] = (T)Us;
+                    }
+                    rq[(k * NS + hb) * THREADS] = r;          // read back by this lane alone
+                }
+            __syncthreads();                                  // the FP64 field's last readers are done
+        }
+    };
+    V uh[SCHEME ? TPW : 1][SCHEME ? NS : 1], fh[SCHEME ? TPW : 1][SCHEME ? NS : 1];
+    bool second = false;                                      // a step with history
+    const T c23 = T(2.0 * dt / 3.0), third = T(1.0 / 3.0);
+    long long last_rebase = step;
+    if constexpr (RF) rebase(true);
+    int fin = -1;
+    while (step < pa.max_steps) {
+        // up to the next evaluation step, whose predecessor is kept as the stop rule's snapshot
+        const long long stop = (step / pa.check + 1) * pa.check;
+        const long long upto = stop < pa.max_steps ? stop : pa.max_steps;
+        int left = (int)(upto - step);                        // at most check_every
+        step = upto;
+        while (true) {
+            if (left == 1) each([&](int k, int hb, int i, int e) { stv(ub, (T)x[k][hb][i], e); });
+#pragma unroll
+            for (int k = 0; k < TPW; ++k) {
+                // explicit reaction
+                V X[NS];
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb) {
+                    V r;
+                    if constexpr (RF) r = rq[(k * NS + hb) * THREADS];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const T own = x[k][hb][i], oth = dpp_mov<ROR8>((T)x[k][hb][i]);
+                        T q;
+                        if constexpr (RF) {                   // v + dt (R + f(U + v) - f(U))
+                            const T ua = u32[k][hb][i], uo = dpp_mov<ROR8>((T)u32[k][hb][i]);
+                            T f, gg;
+                            const T p[4] = {T(s.p[0]), T(s.p[1]), T(s.p[2]), T(s.p[3])};
+                            kinetics_delta<MODEL>(p, sp ? uo : ua, sp ? ua : uo, sp ? oth : own, sp ? own : oth, f, gg);
+                            q = own + tdt * (r[i] + (sp ? gg : f));
+                        } else if constexpr (SCHEME == 1) {
+                            const T F = react(own, oth), ud = own - c0;
+                            q = second ? fma(c23, fma(T(2), F, -fh[k][hb][i]), fma(T(4), ud, -uh[k][hb][i]) * third)
+                                       : fma(tdt, F, ud);
+                            uh[k][hb][i] = ud;
+                            fh[k][hb][i] = F;
+                        } else {
+                            q = fma(tdt, react(own, oth), own - c0);
+                        }
+                        if constexpr (RAG) q = masked(q, real[k], hb * 4 + i);
+                        x[k][hb][i] = q;
+                    }
+                }
+                L.fwd(x[k], X);
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb) *reinterpret_cast<V *>(row + STEP * LD * k + hb * 16) = X[hb];
+            }
+            if constexpr (!SH::DREG) load_div(second ? dp2 : dp, 0);     // ahead of the barrier and the forward
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < TPW; ++k) {
+                V X[NS];
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[k][hb][i] = col[STEP * k + (hb * 16 + i) * LD];
+                if constexpr (!SH::DREG) {
+                    if (k > 0) load_div(second ? dp2 : dp, k);
+                }
+                L.fwd(x[k], X);
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb) X[hb] *= dv[k][hb];
+                L.inv(X, x[k]);
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) col[STEP * k + (hb * 16 + i) * LD] = x[k][hb][i];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < TPW; ++k) {
+                V X[NS];
+#pragma unroll
+                for (int hb = 0; hb < NS; ++hb) X[hb] = *reinterpret_cast<const V *>(row + STEP * LD * k + hb * 16);
+                L.inv(X, x[k]);
+                if constexpr (sizeof(T) == 4 && !RF && MODEL != CIL_FHN && MODEL != CIL_HEAT) {
+#pragma unroll
+                    for (int hb = 0; hb < NS; ++hb) x[k][hb] += V(c0);
+                }
+            }
+            if constexpr (SCHEME == 1) {
+                if (!second) {
+                    second = true;
+                    if constexpr (SH::DREG) {
+#pragma unroll
+                        for (int k = 0; k < TPW; ++k) load_div(dp2, k);
+                    }
+                }
+            }
+            if (--left == 0) break;
+        }
+        // stop rule on u^step against the snapshot of u^(step-1)
+        double d = 0.0, a = 0.0;
+        int bad = 0;
+        each([&](int k, int hb, int i, int e) {
+            const double v = (double)x[k][hb][i];
+            const double dd = fabs(v - (double)ld(ub, T(0), e));
+            if (!RAG || e >= 0) {
+                bad |= !isfinite(v);
+                d = fmax(d, isnan(dd) ? 0.0 : dd);
+                if constexpr (!RF) a = fmax(a, isnan(v) ? 0.0 : fabs(v));
+            }
+        });
+        d = wave_max(d);
+        a = wave_max(a);
+        bad = wave_or(bad);
+        if (lane == 0) {
+            red[wave] = d;
+            red[WAVES + wave] = a;
+            sbad[wave] = bad;
+        }
+        __syncthreads();
+        double dm = 0.0, am = 0.0;
+        int anybad = 0;
+        for (int w = 0; w < WAVES; ++w) {
+            dm = fmax(dm, red[w]);
+            am = fmax(am, red[WAVES + w]);
+            anybad |= sbad[w];
+        }
+        const double r = dm / dt;
+        int st = -1;
+        if (anybad) st = CIL_SOLVE_NONFINITE;
+        else if (pa.tol > 0.0 && r < pa.tol) st = CIL_SOLVE_OK;
+        else if (pa.tol > 0.0 && pa.floor_coef > 0.0 && r < pa.floor_coef * am) st = CIL_SOLVE_FP32_FLOOR;
+        else if (step == pa.max_steps) st = pa.tol > 0.0 ? CIL_SOLVE_MAXSTEPS : CIL_SOLVE_OK;
+        if (tid == 0) {
+            pa.resid[b] = anybad ? (double)NAN : r;
+            if (st >= 0) pa.status[b] = st;
+        }
+        fin = st;
+        if (st >= 0) break;
+        if (pa.prio > 1.0 && pa.tol > 0.0) set_issue_priority(r / pa.tol, pa.prio);
+        if constexpr (RF) {
+            if (step - last_rebase >= kRebase) {          // uniform over the workgroup
+                rebase(false);
+                last_rebase = step;
+            }
+        }
+    }
+    const auto ob = make_rsrc(out + s.off, 2u * NN * sizeof(TS));
+    each([&](int k, int hb, int i, int e) {
+        if constexpr (RF) x[k][hb][i] = T(ld(u64r, 0.0, e) + (double)x[k][hb][i]);     // u = U + v
+        stv(ob, TS(x[k][hb][i]), e);
+    });
+    if (tid == 0) pa.steps[b] = step;
+    return fin;
+}
+
+// One kernel per model (the host picks it).  WPE: wavefronts per SIMD that the
+// register allocation aims at.
+template <int MODEL, typename T, typename Line, int SCHEME, int TPW, int WPE>
+__global__ __launch_bounds__((MmShape<T, Line, TPW>::THREADS)) __attribute__((amdgpu_waves_per_eu(WPE))) void k_mm(
+    const DevSolve *S, const int *list, T *state, const T *dtab, const T *dtab2, const T *cst, double dt,
+    PersistArgs pa)
+{
+    using SH = MmShape<T, Line, TPW>;
+    __shared__ __align__(16) T sm[SH::LDS];
+    __shared__ double red[2 * SH::WAVES];
+    __shared__ int sbad[SH::WAVES];
+    const int b = list[blockIdx.x];
+    const DevSolve s = S[b];
+    long long step = pa.steps[b];
+    Vec4<T> x[TPW][Line::NS];
+    mm_solve<T, Line, TPW, MODEL, SCHEME, false, true, T>(sm, red, sbad, s, b, state, state, dtab, dtab2, cst, dt, pa, step,
+                                                     x);
+}
+
+// FP32 steps, then from the FP32 floor to the tolerance the refinement form
+// (RF) or FP64 steps, in one launch or two: modes and arguments as
+// k_fused_q_mixed (stepper_quad.hpp), whose two phases these are on the matrix
+// cores.
+template <int MODEL, typename LineF, typename LineD, int TPW, int WPE, bool RF>
+__global__ __launch_bounds__((MmShape<float, LineF, TPW>::THREADS)) __attribute__((amdgpu_waves_per_eu(WPE)))
+void k_mm_mixed(const DevSolve *S, const int *list, float *state, double *state64, const float *tab32,
+                const double *tab64, double dt, PersistArgs pa32, PersistArgs pa64, long long *switch_step, int mode)
+{
+    using SF = MmShape<float, LineF, TPW>;
+    using SD = MmShape<double, LineD, TPW>;
+    constexpr int N = LineF::N, NS = LineF::NS;
+    // the refinement form keeps R behind the field
+    __shared__ __align__(16) double sm[RF ? SF::LDS / 2 + N * N : SD::LDS];
+    __shared__ double red[2 * SF::WAVES];
+    __shared__ int sbad[SF::WAVES];
+    const int b = list[blockIdx.x];
+    const DevSolve s = S[b];
+    long long step = pa32.steps[b];
+    if (mode == 2) pa32.max_steps = step;
+    Vec4<float> x[TPW][NS];
+    const int fin = mm_solve<float, LineF, TPW, MODEL, 0, false, true, float>(
+        reinterpret_cast<float *>(sm), red, sbad, s, b, state, state, tab32, nullptr, nullptr, dt, pa32, step, x);
+    const long long sw = step;
+    const bool go = mode == 2 || (mode == 0 && fin == CIL_SOLVE_FP32_FLOOR);       // uniform over the workgroup
+    if constexpr (RF) {
+        if (go)
+            mm_solve<float, LineF, TPW, MODEL, 0, true, false, float>(reinterpret_cast<float *>(sm), red, sbad, s, b,
+                                                                      state, state, tab32, nullptr, nullptr, dt, pa64,
+                                                                      step, x, state64);
+    } else if (go) {
+        Vec4<double> v[TPW][NS];
+#pragma unroll
+        for (int k = 0; k < TPW; ++k)
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[k][hb][i] = (double)x[k][hb][i];
+        __syncthreads();                                      // the LDS is reused at double width
+        mm_solve<double, LineD, TPW, MODEL, 0, false, false, float>(sm, red, sbad, s, b, state64, state, tab64,
+                                                                    nullptr, nullptr, dt, pa64, step, v);
+    }
+    if (threadIdx.x == 0 && mode != 2) switch_step[b] = sw;
+}
+
+template <typename T, typename Line, int SCHEME, int TPW, int WPE>
+void launch_mm_line(int nl, const DevSolve *S, const int *list, T *state, const T *dtab, const T *dtab2, const T *cst,
+                    int model, double dt, const PersistArgs &pa, hipStream_t st)
+{
+    constexpr int threads = MmShape<T, Line, TPW>::THREADS;
+    dispatch_model(model, [&](auto MD) {
+        hipLaunchKernelGGL((k_mm<decltype(MD)::value, T, Line, SCHEME, TPW, WPE>), dim3(nl), dim3(threads), 0, st, S, list,
+                           state, dtab, dtab2, cst, dt, pa);
+    });
+}
+
+}  // namespace cil

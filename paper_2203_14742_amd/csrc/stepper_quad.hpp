@@ -31,8 +31,6 @@ namespace cil {
 // the size of the motion over that many steps (each re-basing costs about one
 // FP64 step).  The stop rule compares v with its snapshot taken since, which
 // is u^s - u^(s-1).  sm must then hold 2 N (N + 1) doubles.
-constexpr int kRebase = 200;
-
 template <typename T, int N, int SPL, bool VF, typename MD, bool LOAD, typename TS, bool RF = false>
 __device__ __forceinline__ int fused_q_solve(T *sm, double *red, int *sbad, const DevSolve &s, int b, T *state,
                                              TS *out, const T *tables, double dt, const PersistArgs &pa,
