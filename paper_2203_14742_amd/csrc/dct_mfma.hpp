@@ -363,20 +363,42 @@ struct LineDense {
     static constexpr bool kHeld = NB == 1;
     static constexpr int kMats = 3 * NB * NB;
     V held[kHeld ? kMats : 1];
-    const T *cst;
+    __amdgpu_buffer_rsrc_t cst;
+    unsigned at;
     __device__ __forceinline__ void init(const T *c, int lane)
     {
-        cst = c + 4 * lane;
+        cst = make_rsrc(c, kMats * 256 * sizeof(T));
+        at = 4 * lane * sizeof(T);
         if constexpr (kHeld) {
 #pragma unroll
-            for (int k = 0; k < kMats; ++k) held[k] = mm_load(cst + k * 256);
+            for (int k = 0; k < kMats; ++k) held[k] = read(k);
+        }
+    }
+    // one uniform base and an immediate per block (a 64-bit address for each would be kept in scalars)
+    __device__ __forceinline__ V read(int k) const
+    {
+        using U4 = __attribute__((ext_vector_type(4))) unsigned;
+        const int bytes = k * 256 * (int)sizeof(T), so = bytes & ~4095, im = bytes & 4095;
+        if constexpr (sizeof(T) == 4) {
+            return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(cst, at + im, so, 0));
+        } else {
+            struct {
+                U4 a, b;
+            } r{__builtin_amdgcn_raw_buffer_load_b128(cst, at + im, so, 0),
+                __builtin_amdgcn_raw_buffer_load_b128(cst, at + im + 16, so, 0)};
+            return __builtin_bit_cast(V, r);
         }
     }
     __device__ __forceinline__ V mat(int m, int bo, int bi) const
     {
         const int k = (m * NB + bo) * NB + bi;
         if constexpr (kHeld) return held[k];
-        else return mm_load(cst + k * 256);
+        else return read(k);
+    }
+    // keeps the reads of a later output block from being issued early, all at once
+    __device__ __forceinline__ static void fence()
+    {
+        if constexpr (NB >= 3) __builtin_amdgcn_sched_barrier(0);
     }
     __device__ __forceinline__ void fwd(const V (&x)[NS], V (&X)[NS]) const
     {
@@ -387,6 +409,7 @@ struct LineDense {
 #pragma unroll
             for (int b = 0; b < NB; ++b)
                 block2<T>(mat(0, bo, b), x[b] + x[NB + b], X[bo], mat(2, bo, b), x[b] - x[NB + b], X[NB + bo]);
+            fence();
         }
     }
     __device__ __forceinline__ void inv(const V (&X)[NS], V (&x)[NS]) const
@@ -398,6 +421,7 @@ struct LineDense {
             for (int b = 0; b < NB; ++b) block2<T>(mat(1, bo, b), X[b], e, mat(2, bo, b), X[NB + b], o);
             x[bo] = e + o;
             x[NB + bo] = e - o;
+            fence();
         }
     }
     __host__ __device__ static constexpr bool desc(int hb) { return hb >= NB; }

@@ -103,8 +103,10 @@ struct MmShape {
     static constexpr int WAVES = N / (8 * TPW), THREADS = 64 * WAVES;
     static constexpr int LD = N + 4, SP = N * LD + 8;         // LDS strides, in values
     static constexpr int LDS = 2 * SP;
-    // divisors in registers: 4 NS values a lane, where that is at most 16 VGPRs
-    static constexpr bool DREG = TPW * NS * sizeof(T) <= 16;
+    // divisors in registers: 4 NS values a lane, where that is at most 16 VGPRs;
+    // else read in each step, ahead of the barrier where there is room for them
+    // beside the transform's two fields, after the forward where there is not
+    static constexpr bool DREG = TPW * NS * sizeof(T) <= 16, DLATE = Line::kRagged && NS * sizeof(T) >= 24;
 };
 
 // One solve.  SCHEME 0: IMEX Euler (divisors dtab); 1: the second-order scheme
@@ -354,7 +356,7 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
 #pragma unroll
                 for (int hb = 0; hb < NS; ++hb) *reinterpret_cast<V *>(row + STEP * LD * k + hb * 16) = X[hb];
             }
-            if constexpr (!SH::DREG) load_div(second ? dp2 : dp, 0);     // ahead of the barrier and the forward
+            if constexpr (!SH::DREG && !SH::DLATE) load_div(second ? dp2 : dp, 0);     // ahead of the barrier and the forward
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < TPW; ++k) {
@@ -363,10 +365,11 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
                 for (int hb = 0; hb < NS; ++hb)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) x[k][hb][i] = col[STEP * k + (hb * 16 + i) * LD];
-                if constexpr (!SH::DREG) {
+                if constexpr (!SH::DREG && !SH::DLATE) {
                     if (k > 0) load_div(second ? dp2 : dp, k);
                 }
                 L.fwd(x[k], X);
+                if constexpr (SH::DLATE) load_div(second ? dp2 : dp, k);
 #pragma unroll
                 for (int hb = 0; hb < NS; ++hb) X[hb] *= dv[k][hb];
                 L.inv(X, x[k]);
