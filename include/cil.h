@@ -171,12 +171,11 @@ int cil_simulate_patterns(cil_model model, cil_precision prec, const cil_problem
  * cil_simulate_patterns.  The history (u^{s-2}, F(u^{s-2})) lives for one
  * call only: a call that continues from a state the previous one left starts
  * again with an Euler step, so it is not the same as one uninterrupted run.
- * Back-ends: a fused persistent kernel (one workgroup per solve, one lane
- * per grid line, state and history resident in LDS) for n = 32 and, in FP32,
- * n = 64; the plain back-end (history in two state-sized device buffers from
- * the library's buffer pool) otherwise.  Path AUTO picks the fused kernel
- * where it exists, PLAIN forces the plain back-end, FUSED and FUSED_LINE
- * require the fused kernel (CIL_EUNSUPPORTED for other sides), FUSED_QUAD is
+ * Back-ends: a persistent kernel on the matrix cores (path AUTO: n <= 128 in
+ * FP32, n <= 96 in FP64; path FUSED: n = 32 and, in FP32, n = 64, else
+ * CIL_EUNSUPPORTED); one with a lane per grid line (path FUSED_LINE, the sides
+ * of FUSED); the plain back-end (history in two state-sized device buffers from
+ * the library's buffer pool; path PLAIN, and AUTO for larger sides).  FUSED_QUAD is
  * CIL_EUNSUPPORTED.  FP32: polish must be 0 (no FP64 continuation; a solve
  * that reaches the FP32 floor ends with status FP32_FLOOR); polish != 0 with
  * tol > 0 is CIL_EUNSUPPORTED. */

@@ -1032,7 +1032,7 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
         MmTables mt;
         const bool mix = mx && mixed_supported(kv.first, kind);
         if (kind == KIND_MM)
-            CIL_TRY(make_mm_tables<T>(c, kv.first, kv.second, hs, &mt));
+            CIL_TRY(make_mm_tables<T>(c, kv.first, kv.second, hs, &mt, c.scheme ? 2.0 * c.dt / 3.0 : 0.0));
         else
             CIL_TRY(make_tables<T>(c, kv.first, kv.second, hs, &t,
                                    quad && kQuadShape[quad_shape(std::is_same<T, float>::value, kv.first)].vform));
@@ -1104,8 +1104,9 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
             }
         }
         if (kind == KIND_MM)
-            CIL_TRY(launch_mm_named<T>(kv.first, 0, (int)kv.second.size(), dS, dls[gi], state, (const T *)mms[gi].tab,
-                                       nullptr, (const T *)mms[gi].cst, c.model, c.dt, pa, gst));
+            CIL_TRY(launch_mm_named<T>(kv.first, c.scheme, (int)kv.second.size(), dS, dls[gi], state,
+                                       (const T *)mms[gi].tab, (const T *)mms[gi].tab2, (const T *)mms[gi].cst,
+                                       c.model, c.dt, pa, gst));
         else
             CIL_TRY(launch_persistent<T>(kv.first, quad, shape, (int)kv.second.size(), dS, dls[gi], state,
                                          (const T *)tabs[gi], c.model, c.dt, pa, gst));
@@ -1175,9 +1176,9 @@ int run_phase2(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vecto
     return CIL_OK;
 }
 
-// Second-order fused solves (line variant; n = 32, and n = 64 in FP32, where
-// state and history fit the LDS of one workgroup), one launch per grid side,
-// in order on the caller's stream.
+// Second-order fused solves, line variant (path FUSED_LINE; n = 32, and n = 64
+// in FP32, where state and history fit the LDS of one workgroup), one launch
+// per grid side, in order on the caller's stream.
 bool sbdf2_fused_supported(int n, bool f32) { return n == 32 || (n == 64 && f32); }
 
 template <typename T>
@@ -1332,8 +1333,9 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     c.status.assign(B, CIL_SOLVE_OK);
     const bool polish = f32 && stp->polish && stp->tol > 0.0;
     c.polish = polish ? stp->polish : 0;
-    const FusedKind kind = fused_kind(stp->path);
+    FusedKind kind = fused_kind(stp->path);
     if (scheme) {
+        if (kind == KIND_QUAD) kind = KIND_MM;                // a quad code shape chosen by option: not this scheme's
         if (stp->path == CIL_PATH_FUSED_QUAD)
             return set_error(CIL_EUNSUPPORTED, "the second-order stepper has no quad-lane kernel");
         if (polish)
@@ -1363,8 +1365,8 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     std::map<int, std::vector<int>> fused_byn, plain_byn;
     for (int b = 0; b < B; ++b) {
         const int n = hs[b].n;
-        const bool fs = scheme ? sbdf2_fused_supported(n, f32) && stp->path != CIL_PATH_PLAIN
-                               : persistent_supported(n, f32, stp->path);
+        const bool fs = persistent_supported(n, f32, stp->path) &&
+                        (!scheme || stp->path < CIL_PATH_FUSED || sbdf2_fused_supported(n, f32));
         if (stp->path >= CIL_PATH_FUSED && !fs)
             return set_error(CIL_EUNSUPPORTED, "no fused %sstepper for n = %d in %s", scheme ? "second-order " : "", n,
                              f32 ? "FP32" : "FP64");
@@ -1403,7 +1405,7 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         CIL_TRY(cb.alloc((void **)&mx.state64, sizeof(double) * (size_t)end));
         CIL_TRY(cb.alloc((void **)&mx.sw, sizeof(long long) * B));
     }
-    if (scheme) {
+    if (scheme && kind == KIND_LINE) {
         if (f32) CIL_TRY(run_fused_sbdf2<float>(c, fused_byn, hs, dS, (float *)state, c.floor_coef32, dsteps, dres, dstat));
         else CIL_TRY(run_fused_sbdf2<double>(c, fused_byn, hs, dS, (double *)state, 0.0, dsteps, dres, dstat));
     } else if (f32) {

@@ -307,9 +307,11 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
             __syncthreads();                                  // the FP64 field's last readers are done
         }
     };
-    V uh[SCHEME ? TPW : 1][SCHEME ? NS : 1], fh[SCHEME ? TPW : 1][SCHEME ? NS : 1];
-    bool second = false;                                      // a step with history
-    const T c23 = T(2.0 * dt / 3.0), third = T(1.0 / 3.0);
+    // second order: r = kt (k4 u^{s-1} - u^{s-2}) + kc (k2 F(u^{s-1}) - F(u^{s-2})) with (k4, kt, k2, kc) = (4, 1/3,
+    // 2, 2 dt / 3); the first step is the IMEX-Euler one, (1, 1, 1, dt) and an empty history
+    V uh[SCHEME ? TPW : 1][SCHEME ? NS : 1] = {}, fh[SCHEME ? TPW : 1][SCHEME ? NS : 1] = {};
+    T k4 = T(1), kt = T(1), k2 = T(1), kc = tdt;
+    const T *dsel = dp;                                       // the divisors of the step
     long long last_rebase = step;
     if constexpr (RF) rebase(true);
     int fin = -1;
@@ -341,8 +343,7 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
                             q = own + tdt * (r[i] + (sp ? gg : f));
                         } else if constexpr (SCHEME == 1) {
                             const T F = react(own, oth), ud = own - c0;
-                            q = second ? fma(c23, fma(T(2), F, -fh[k][hb][i]), fma(T(4), ud, -uh[k][hb][i]) * third)
-                                       : fma(tdt, F, ud);
+                            q = fma(kc, fma(k2, F, -fh[k][hb][i]), fma(k4, ud, -uh[k][hb][i]) * kt);
                             uh[k][hb][i] = ud;
                             fh[k][hb][i] = F;
                         } else {
@@ -356,7 +357,7 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
 #pragma unroll
                 for (int hb = 0; hb < NS; ++hb) *reinterpret_cast<V *>(row + STEP * LD * k + hb * 16) = X[hb];
             }
-            if constexpr (!SH::DREG && !SH::DLATE) load_div(second ? dp2 : dp, 0);     // ahead of the barrier and the forward
+            if constexpr (!SH::DREG && !SH::DLATE) load_div(dsel, 0);
             __syncthreads();
 #pragma unroll
             for (int k = 0; k < TPW; ++k) {
@@ -366,10 +367,10 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
 #pragma unroll
                     for (int i = 0; i < 4; ++i) x[k][hb][i] = col[STEP * k + (hb * 16 + i) * LD];
                 if constexpr (!SH::DREG && !SH::DLATE) {
-                    if (k > 0) load_div(second ? dp2 : dp, k);
+                    if (k > 0) load_div(dsel, k);
                 }
                 L.fwd(x[k], X);
-                if constexpr (SH::DLATE) load_div(second ? dp2 : dp, k);
+                if constexpr (SH::DLATE) load_div(dsel, k);
 #pragma unroll
                 for (int hb = 0; hb < NS; ++hb) X[hb] *= dv[k][hb];
                 L.inv(X, x[k]);
@@ -391,8 +392,12 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
                 }
             }
             if constexpr (SCHEME == 1) {
-                if (!second) {
-                    second = true;
+                if (dsel != dp2) {
+                    dsel = dp2;
+                    k4 = T(4);
+                    kt = T(1.0 / 3.0);                        // a multiply, not a divide
+                    k2 = T(2);
+                    kc = T(2.0 * dt / 3.0);
                     if constexpr (SH::DREG) {
 #pragma unroll
                         for (int k = 0; k < TPW; ++k) load_div(dp2, k);

@@ -56,20 +56,23 @@ int mm_call(F &&f)
 {
     return f(Line{}, std::integral_constant<int, TPW>{}, std::integral_constant<int, WPE>{});
 }
-template <typename T, typename F>
+// The second-order scheme keeps the history in registers too, which costs its
+// FP32 64^2 and FP64 32^2 kernels one step of occupancy.
+template <typename T, int SCHEME = 0, typename F>
 int mm_dispatch(int n, F &&f)
 {
     constexpr bool f32 = sizeof(T) == 4;
-    if (n == 32) return mm_call<Line32<T>, 1, 4>(f);
-    if (n == 64) return mm_call<Line64<T>, 1, f32 ? 4 : 2>(f);
+    constexpr int w32 = SCHEME && !f32 ? 3 : 4, w64 = SCHEME || !f32 ? 2 : 4;
+    if (n == 32) return mm_call<Line32<T>, 1, w32>(f);
+    if (n == 64) return mm_call<Line64<T>, 1, w64>(f);
     if (n < 2 || n > mm_max_side(f32)) return CIL_EUNSUPPORTED;
     if constexpr (f32) {
         if (n == 128) return mm_call<Line128<T>, 2, 2>(f);
         if (mm_padded(n) == 128) return mm_call<LineDense<T, 4>, 2, 2>(f);
     }
     switch (mm_padded(n)) {
-    case 32: return mm_call<LineDense<T, 1>, 1, 4>(f);
-    case 64: return mm_call<LineDense<T, 2>, 1, f32 ? 4 : 2>(f);
+    case 32: return mm_call<LineDense<T, 1>, 1, w32>(f);
+    case 64: return mm_call<LineDense<T, 2>, 1, w64>(f);
     case 96: return mm_call<LineDense<T, 3>, 1, 3>(f);
     default: return CIL_EUNSUPPORTED;
     }
@@ -105,13 +108,16 @@ template <typename T>
 int launch_mm(int n, int scheme, int nl, const DevSolve *S, const int *list, T *state, const T *tab, const T *tab2,
               const T *cst, int model, double dt, const PersistArgs &pa, hipStream_t st)
 {
-    return mm_dispatch<T>(n, [&](auto line, auto tpw, auto wpe) -> int {
+    auto go = [&](auto line, auto tpw, auto wpe, auto sch) -> int {
         using Line = decltype(line);
-        constexpr int TPW = decltype(tpw)::value, WPE = decltype(wpe)::value;
-        if (scheme) launch_mm_line<T, Line, 1, TPW, WPE>(nl, S, list, state, tab, tab2, cst, model, dt, pa, st);
-        else launch_mm_line<T, Line, 0, TPW, WPE>(nl, S, list, state, tab, tab2, cst, model, dt, pa, st);
+        launch_mm_line<T, Line, decltype(sch)::value, decltype(tpw)::value, decltype(wpe)::value>(
+            nl, S, list, state, tab, tab2, cst, model, dt, pa, st);
         return CIL_OK;
-    });
+    };
+    using std::integral_constant;
+    if (scheme)
+        return mm_dispatch<T, 1>(n, [&](auto l, auto t, auto w) { return go(l, t, w, integral_constant<int, 1>{}); });
+    return mm_dispatch<T, 0>(n, [&](auto l, auto t, auto w) { return go(l, t, w, integral_constant<int, 0>{}); });
 }
 
 }  // namespace cil

@@ -119,3 +119,18 @@ def test_steady_state_far_from_the_state(cil):
     cil.cil_simulate_patterns(2, b, probs, 0.01, 20, check_every=20, path=cil.CIL_PATH_PLAIN)
     # 20 steps of at most 16 roundings each
     assert float((a.double() - b).abs().max()) <= 20 * 16 * 2.0 ** -24 * float(b.abs().max())
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("model", [0, 2])
+def test_second_order_every_side_against_the_plain_path(cil, model, dtype):
+    sides = list(range(2, 129))
+    ref, offs, probs = batch(cil, model, sides, 150, dtype)
+    got = ref.clone()
+    for st, path in ((ref, cil.CIL_PATH_PLAIN), (got, cil.CIL_PATH_AUTO)):
+        rep = cil.cil_simulate_patterns(model, st, probs, MODELS[model][3], 12, check_every=5, path=path, polish=0,
+                                        offsets=offs, scheme="sbdf2")
+        assert np.all(rep["steps_taken"] == 12) and np.all(rep["status"] == 0)
+    for n, o in zip(sides, offs):
+        a, b = got[o:o + 2 * n * n + 3].double(), ref[o:o + 2 * n * n + 3].double()
+        assert float((a - b).abs().max()) <= BARS[dtype] * float(b[:-3].abs().max()), n
