@@ -263,15 +263,16 @@ __global__ __launch_bounds__(256) void k_classify(ClassifyArgs c, long long nA, 
 
 // ---------------------------------------------------------------- canonical
 // Double-double accumulation of the exact squares, one wavefront per pair (or
-// sixteen, when few pairs are re-checked), then a certified rounding.  The accumulation records whether any of its
-// roundings lost bits: if none did, hi + lo is the exact sum and the
-// hardware's RN(hi + lo) is the correctly rounded value, ties included (the
-// common case for FP32 sets, whose squares are exact).  Otherwise, with the
+// sixteen, when few pairs are re-checked), then a certified rounding: with the
 // relative error bound delta, RN(sum) = RN(hi + lo) whenever the interval
-// [S - delta S, S + delta S] holds no rounding boundary.  If neither holds
-// (or when forced) the wavefront recomputes the sum exactly: each lane builds
-// a non-overlapping expansion of its terms (Shewchuk's exact summation),
-// lane 0 merges the 64 expansions and rounds once, half to even.
+// [S - delta S, S + delta S] holds no rounding boundary.  Where it holds one
+// (an exact tie, above all) the pair is summed again with a record of whether
+// any rounding lost bits: if none did, hi + lo is the exact sum and the
+// hardware's RN(hi + lo) is the correctly rounded value, ties included.  If
+// that does not decide it either (or when forced) the wavefront recomputes
+// the sum exactly: each lane builds a non-overlapping expansion of its terms
+// (Shewchuk's exact summation), lane 0 merges the 64 expansions and rounds
+// once, half to even.
 
 __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e)
 {
@@ -290,6 +291,40 @@ __device__ __forceinline__ void dd_add_t(double &hi, double &lo, double bh, doub
     inexact |= (et != 0.0) | (eu != 0.0);
     hi = s + u;
     lo = u - (hi - s);
+}
+
+// (hi, lo) += d^2 without tracking: hi by an exact two-sum, everything it
+// loses into lo, which is rounded.  Eleven FP64 operations a term against
+// twenty-five of dd_add_t.  After k terms of a non-negative sum S the error is
+// at most (2 k^2 + 2 k) 2^-106 S: |lo| stays below 2 k 2^-53 S, and each of the
+// k updates rounds lo and the term added to it once.
+__device__ __forceinline__ void dd_square(double &hi, double &lo, double d)
+{
+    const double p = d * d;
+    double s, e;
+    two_sum(hi, p, s, e);
+    hi = s;
+    lo += e + fma(d, d, -p);
+}
+
+// Relative error bound of a sum of per-lane dd_square accumulations of k terms
+// each, joined by `joins` levels of double-double additions.
+__device__ __forceinline__ double dd_delta(double k, double joins)
+{
+    return (4.0 * k * k + 4.0 * k + 64.0 * (joins + 1.0)) * 0x1p-106;
+}
+
+// Whether fl(hi + lo) = R, with the rest e, is the correctly rounded value of
+// any sum within delta R of hi + lo: no rounding boundary of R (half an ulp
+// away, except below a power of two, where the spacing halves) lies between.
+__device__ __forceinline__ bool dd_certain(double hi, double lo, double delta, double &R)
+{
+    double e;
+    two_sum(hi, lo, R, e);
+    int ex;
+    const double frac = frexp(R, &ex);                   // R = frac 2^ex, frac in [0.5, 1)
+    const double half = (e < 0.0 && frac == 0.5) ? ldexp(1.0, ex - 55) : ldexp(1.0, ex - 54);
+    return isfinite(R) && (fabs(e) + delta * R < half || R == 0.0);
 }
 
 constexpr int EXP_CAP = 64;     // a non-overlapping expansion of doubles has < 40 parts
@@ -357,6 +392,37 @@ __device__ double exact_d2_wave(const T *a, const T *b, long long dim, int lane)
     return lane == 0 ? exp_round(part, np) : 0.0;
 }
 
+// The pairs the untracked sum cannot certify (ties, and one in 2^30 or so): the
+// tracked sum by one wavefront, then where that cannot either the exact one.
+template <typename T>
+__device__ __attribute__((noinline)) double canonical_tracked(const T *a, const T *b, long long dim, int lane,
+                                                              int force_exact, unsigned long long *nexact)
+{
+    double hi = 0.0, lo = 0.0;
+    int inexact = 0;
+    for (long long k = lane; k < dim; k += 64) {
+        const double d = ld(a + k) - ld(b + k);
+        const double p = d * d;
+        dd_add_t(hi, lo, p, fma(d, d, -p), inexact);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const double oh = __shfl_xor(hi, off, 64), ol = __shfl_xor(lo, off, 64);
+        dd_add_t(hi, lo, oh, ol, inexact);
+        inexact |= __shfl_xor(inexact, off, 64);
+    }
+    double D;
+    int certain = dd_certain(hi, lo, (double)(dim + 129) * 0x1p-100, D);   // relative error bound
+    certain = isfinite(D) && (certain || !inexact);
+    certain = __shfl(certain, 0, 64);
+    D = __shfl(D, 0, 64);
+    if (!certain || force_exact) {
+        D = exact_d2_wave(a, b, dim, lane);
+        if (lane == 0) atomicAdd(nexact, 1ull);
+    }
+    return D;
+}
+
 struct CanonOut {
     // pair source: either an int2 list (recheck) or two index arrays
     const int2 *pairs;
@@ -380,10 +446,11 @@ struct CanonOut {
     long long nB;
     unsigned long long *nexact;
     int force_exact;
+    const int *only_if;         // or null: the launch leaves at once where this is 0
 };
 
 // WPP wavefronts per pair: 1 (four pairs per 256-thread block; many pairs, the
-// pass is bandwidth-bound) or 16 (one pair per 1024-thread block; few pairs,
+// pass is bandwidth-bound), 4 or 16 (one pair per block; fewer pairs,
 // latency-bound).  The certified rounding makes the result independent of
 // the summation order, so both give the same doubles.
 template <typename T, int WPP>
@@ -394,6 +461,7 @@ template <typename T, int WPP>
 __global__ __launch_bounds__(WPP == 1 ? 256 : 64 * WPP) void k_canonical(const T *A, const T *B, long long dim,
                                                                          CanonOut o)
 {
+    if (o.only_if && !*o.only_if) return;
     const int lane = threadIdx.x & 63;
     const int sub = WPP == 1 ? 0 : threadIdx.x / 64;
     // list mode: the grid may be sized before the list count is known (an
@@ -437,61 +505,37 @@ __device__ __forceinline__ void canonical_pair(const T *A, const T *B, long long
     const T *a = A + i * dim;
     const T *b = B + j * dim;
     double hi = 0.0, lo = 0.0;
-    int inexact = 0;
-    // four strides' loads in flight; terms accumulated in the same order
     constexpr long long STR = 64LL * WPP;
     long long k = lane + 64LL * sub;
-    for (; k + 3 * STR < dim; k += 4 * STR) {
+    for (; k + 3 * STR < dim; k += 4 * STR) {            // four strides' loads in flight
         double da[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) da[u] = ld(a + k + u * STR) - ld(b + k + u * STR);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const double p = da[u] * da[u];
-            dd_add_t(hi, lo, p, fma(da[u], da[u], -p), inexact);
-        }
+        for (int u = 0; u < 4; ++u) dd_square(hi, lo, da[u]);
     }
-    for (; k < dim; k += STR) {
-        const double d = ld(a + k) - ld(b + k);
-        const double p = d * d;
-        dd_add_t(hi, lo, p, fma(d, d, -p), inexact);
-    }
+    for (; k < dim; k += STR) dd_square(hi, lo, ld(a + k) - ld(b + k));
+    int unused = 0;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
         const double oh = __shfl_xor(hi, off, 64), ol = __shfl_xor(lo, off, 64);
-        dd_add_t(hi, lo, oh, ol, inexact);
-        inexact |= __shfl_xor(inexact, off, 64);
+        dd_add_t(hi, lo, oh, ol, unused);
     }
     if constexpr (WPP > 1) {      // combine the pair's wavefronts; wavefront 0 finishes
         __shared__ double phi[WPP], plo[WPP];
-        __shared__ int pin[WPP];
         if (lane == 0) {
             phi[sub] = hi;
             plo[sub] = lo;
-            pin[sub] = inexact;
         }
         __syncthreads();
         if (sub != 0) return;
-        for (int v = 1; v < WPP; ++v) {
-            dd_add_t(hi, lo, phi[v], plo[v], inexact);
-            inexact |= pin[v];
-        }
+        for (int v = 1; v < WPP; ++v) dd_add_t(hi, lo, phi[v], plo[v], unused);
     }
-    double R, e;
-    two_sum(hi, lo, R, e);
-    const double delta = (double)(dim + 65 * WPP + 64) * 0x1p-100;   // relative error bound
-    int ex;
-    const double frac = frexp(R, &ex);                   // R = frac 2^ex, frac in [0.5, 1)
-    // rounding boundaries of R: R +- half an ulp (ulp = 2^(ex-53)), except
-    // below a power of two, where the spacing halves
-    const double half = (e < 0.0 && frac == 0.5) ? ldexp(1.0, ex - 55) : ldexp(1.0, ex - 54);
-    int certain = isfinite(R) && (!inexact || fabs(e) + delta * R < half || R == 0.0);
+    double D;
+    int certain = dd_certain(hi, lo, dd_delta((double)((dim + STR - 1) / STR), 6 + WPP), D);
     certain = __shfl(certain, 0, 64);                    // lane 0 decides for the wavefront
-    double D = R;
-    if (!certain || o.force_exact) {
-        D = exact_d2_wave(a, b, dim, lane);
-        if (lane == 0) atomicAdd(o.nexact, 1ull);
-    }
+    D = __shfl(D, 0, 64);
+    if (!certain || o.force_exact) D = canonical_tracked(a, b, dim, lane, o.force_exact, o.nexact);
     if (lane == 0) {
         if (o.d2) o.d2[w] = D;
         if (o.range_mm) {       // non-negative doubles order as their bit patterns
@@ -510,6 +554,129 @@ __device__ __forceinline__ void canonical_pair(const T *A, const T *B, long long
             if (o.bins) o.bins[i * o.nB + j] = (uint8_t)bin;
         }
     }
+}
+
+// All pairs of two sets at once.  Nothing is listed, so rows can be shared: a
+// wavefront takes RW x CW pairs, its lanes along k, and reads RW + CW values for
+// RW CW terms where a wavefront per pair reads two for one; a block of four takes
+// 4 RW x CW pairs, KW such groups split k between them.  2 x 8 pairs and KW = 1 for
+// many pairs, 1 x 4 and KW = 4 for few.  Bound by FP64 issue (eleven operations a
+// term; the vector units issue in 80 % of the cycles): 62 500 pairs of d = 8192 in
+// FP32 take 247 us, 385 by a wavefront per pair (530 with the tracked sum).  The sums of a wavefront are reduced by halving: at each of log2(RW CW)
+// levels a lane hands over half of its pairs and keeps the rest, then plainly.
+// Set blockIdx.z starts strideA (strideB) elements further; with `tri` only pairs
+// j >= i are formed (self-pairs of one set) and written twice.
+template <typename T, int RW, int CW, int KW>
+__global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) void k_canonical_grid(
+    const T *A, long long nA, long long strideA, const T *B, long long nB, long long strideB, long long dim, double *d2,
+    long long ldd, long long strideD, int tri, const int *only_if, unsigned long long *nexact)
+{
+    constexpr int NP = RW * CW, TI = 4 * RW;
+    __shared__ double part[KW > 1 ? KW - 1 : 1][4][NP][2];
+    if (only_if && *only_if) return;                     // the list is not the grid of all pairs
+    // the wavefront's numbers in scalars: the rows' addresses then take no lane registers
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3),
+              kw = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    const long long i0 = (long long)blockIdx.y * TI + RW * wv, j0 = (long long)blockIdx.x * CW;
+    if (tri && j0 + CW <= (long long)blockIdx.y * TI) return;      // the whole block lies below the diagonal
+    A += blockIdx.z * strideA;
+    B += blockIdx.z * strideB;
+    d2 += blockIdx.z * strideD;
+    const T *ra[RW], *rb[CW];
+#pragma unroll
+    for (int r = 0; r < RW; ++r) ra[r] = A + min(i0 + r, nA - 1) * dim;
+#pragma unroll
+    for (int q = 0; q < CW; ++q) rb[q] = B + min(j0 + q, nB - 1) * dim;
+    double hi[NP], lo[NP];
+#pragma unroll
+    for (int e = 0; e < NP; ++e) hi[e] = lo[e] = 0.0;
+    // Blocks start at different k and wrap round: rows are often a power of two
+    // apart, and at one k they would all be on one L2 channel (62 500 pairs of d =
+    // 8192 in FP32: 325 against 582 us).
+    constexpr long long STR = 64LL * KW;
+    const unsigned chunks = (unsigned)((dim + STR - 1) / STR);
+    const unsigned turn = (blockIdx.x * 5u + blockIdx.y * 3u + blockIdx.z) * 7u % chunks * (unsigned)STR;
+    auto sum_range = [&](unsigned from, unsigned to) __attribute__((always_inline)) {
+        unsigned k = from + lane + 64u * kw;
+        if (k >= to) return;
+        T a[RW], b[CW];                                  // read one round ahead
+        auto read = [&](unsigned at) __attribute__((always_inline)) {
+#pragma unroll
+            for (int r = 0; r < RW; ++r) a[r] = ra[r][at];
+#pragma unroll
+            for (int q = 0; q < CW; ++q) b[q] = rb[q][at];
+        };
+        read(k);
+        while (true) {
+            double av[RW], bv[CW];
+#pragma unroll
+            for (int r = 0; r < RW; ++r) av[r] = (double)a[r];
+#pragma unroll
+            for (int q = 0; q < CW; ++q) bv[q] = (double)b[q];
+            k += (unsigned)STR;
+            const bool more = k < to;
+            read(more ? k : k - (unsigned)STR);
+#pragma unroll
+            for (int r = 0; r < RW; ++r)
+#pragma unroll
+                for (int q = 0; q < CW; ++q) dd_square(hi[r * CW + q], lo[r * CW + q], av[r] - bv[q]);
+            if (!more) break;
+        }
+    };
+    for (int lap = 0; lap < 2; ++lap) sum_range(lap ? 0u : turn, lap ? turn : (unsigned)dim);
+    int unused = 0;
+    int mine = 0;                                        // first of the pairs the lane keeps
+#pragma unroll
+    for (int half = NP / 2; half >= 1; half >>= 1) {
+        const int off = 64 / NP * half;
+        const bool up = (lane & off) != 0;
+        mine += up ? half : 0;
+#pragma unroll
+        for (int e = 0; e < half; ++e) {
+            const double sh = up ? hi[e] : hi[e + half], sl = up ? lo[e] : lo[e + half];
+            double kh = up ? hi[e + half] : hi[e], kl = up ? lo[e + half] : lo[e];
+            dd_add_t(kh, kl, __shfl_xor(sh, off, 64), __shfl_xor(sl, off, 64), unused);
+            hi[e] = kh;
+            lo[e] = kl;
+        }
+    }
+#pragma unroll
+    for (int off = 32 / NP; off >= 1; off >>= 1)
+        dd_add_t(hi[0], lo[0], __shfl_xor(hi[0], off, 64), __shfl_xor(lo[0], off, 64), unused);
+    if constexpr (KW > 1) {
+        if (kw > 0 && (lane & (64 / NP - 1)) == 0) {
+            part[kw - 1][wv][mine][0] = hi[0];
+            part[kw - 1][wv][mine][1] = lo[0];
+        }
+        __syncthreads();
+        if (kw > 0) return;
+        for (int v = 0; v < KW - 1; ++v) dd_add_t(hi[0], lo[0], part[v][wv][mine][0], part[v][wv][mine][1], unused);
+    }
+    double D;
+    bool certain = dd_certain(hi[0], lo[0], dd_delta((double)((dim + STR - 1) / STR), 6 + KW), D);
+    const long long i = i0 + mine / CW, j = j0 + mine % CW;
+    const bool wanted = (lane & (64 / NP - 1)) == 0 && i < nA && j < nB && (!tri || j >= i);
+    unsigned long long redo = __ballot(wanted && !certain);
+    while (redo) {                                       // rare: the whole wavefront sums that pair again
+        const int src = __ffsll((long long)redo) - 1;
+        redo &= redo - 1;
+        const long long ii = __shfl(i, src, 64), jj = __shfl(j, src, 64);
+        const double v = canonical_tracked(A + ii * dim, B + jj * dim, dim, lane, 0, nexact);
+        const double w = __shfl(v, 0, 64);
+        if (lane == src) D = w;
+    }
+    if (wanted) {
+        d2[i * ldd + j] = D;
+        if (tri && j < nA && i < nB) d2[j * ldd + i] = D;
+    }
+}
+
+// *not_grid |= the list is not (0, 0), (0, 1), ..., row by row over nB columns.
+__global__ __launch_bounds__(256) void k_list_is_grid(const long long *ia, const long long *jb, long long np,
+                                                      long long nB, int *not_grid)
+{
+    const long long w = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (w < np && (ia[w] != w / nB || jb[w] != w % nB)) *not_grid = 1;
 }
 
 // ======================================================================
@@ -552,6 +719,8 @@ int scratch(long long cap, DistScratch *s)
     return CIL_OK;
 }
 
+constexpr long long kGridPairs = 32768;     // pairs from which sixteen a wavefront leave two wavefronts a SIMD
+
 // Launches waves for pairs co.first .. co.first + nwaves - 1 (in list mode
 // nwaves may exceed the list: the surplus waves leave at once).
 template <typename T>
@@ -561,10 +730,39 @@ int run_canonical(const T *A, const T *B, long long dim, CanonOut &co, long long
     const ProfMark pm = prof_begin("k_canonical", st);
     if (nwaves < 2048 && dim >= 4096)
         hipLaunchKernelGGL((k_canonical<T, 16>), dim3((unsigned)nwaves), dim3(1024), 0, st, A, B, dim, co);
+    else if (nwaves < kGridPairs && dim >= 4096)
+        hipLaunchKernelGGL((k_canonical<T, 4>), dim3((unsigned)nwaves), dim3(256), 0, st, A, B, dim, co);
     else
         hipLaunchKernelGGL((k_canonical<T, 1>), dim3((unsigned)((nwaves + 3) / 4)), dim3(256), 0, st, A, B, dim, co);
     prof_end(pm, st);
     return check_launch("k_canonical");
+}
+
+// All pairs (k_canonical_grid) of `sets` pairs of sets.
+template <typename T, int RW, int CW, int KW>
+int launch_canonical_grid(const T *A, long long nA, long long strideA, const T *B, long long nB, long long strideB,
+                          long long dim, double *d2, long long ldd, long long strideD, int sets, int tri,
+                          const int *only_if, unsigned long long *nexact, hipStream_t st)
+{
+    const dim3 grid((unsigned)((nB + CW - 1) / CW), (unsigned)((nA + 4 * RW - 1) / (4 * RW)), (unsigned)sets);
+    const ProfMark pm = prof_begin("k_canonical_grid", st);
+    hipLaunchKernelGGL((k_canonical_grid<T, RW, CW, KW>), grid, dim3(256 * KW), 0, st, A, nA, strideA, B, nB, strideB,
+                       dim, d2, ldd, strideD, tri, only_if, nexact);
+    prof_end(pm, st);
+    return check_launch("k_canonical_grid");
+}
+template <typename T>
+int run_canonical_grid(const T *A, long long nA, long long strideA, const T *B, long long nB, long long strideB,
+                       long long dim, double *d2, long long ldd, long long strideD, int sets, int tri,
+                       const int *only_if, unsigned long long *nexact, hipStream_t st)
+{
+    if (nA <= 0 || nB <= 0 || sets <= 0) return CIL_OK;
+    const long long pairs = nA * nB * sets / (tri ? 2 : 1);
+    if (pairs >= kGridPairs)
+        return launch_canonical_grid<T, 2, 8, 1>(A, nA, strideA, B, nB, strideB, dim, d2, ldd, strideD, sets, tri,
+                                                 only_if, nexact, st);
+    return launch_canonical_grid<T, 1, 4, 4>(A, nA, strideA, B, nB, strideB, dim, d2, ldd, strideD, sets, tri, only_if,
+                                             nexact, st);
 }
 
 struct Approx {
@@ -908,8 +1106,10 @@ __global__ void k_range_radii(const unsigned long long *cnt, long long cap, int 
 // Re-check launches over a list whose length stays on the device: for
 // d < 4096 one launch of 2048 waves striding over it; for longer vectors a
 // first launch of 256 pairs at sixteen waves each (the usual short list at
-// the latency of one pair), then a strided launch of 8192 single-wave slots
-// for the rest, which leaves at once when there is none.
+// the latency of one pair), then a strided launch of 2048 slots of four waves
+// for the rest, which leaves at once when there is none (2769 pairs of d = 32768
+// in all 145 us, with single-wave slots 295: wavefronts that walk whole rows at one
+// pace from k = 0 on crowd the memory channels).
 template <typename T>
 int canonical_any_length(const T *A, const T *B, long long dim, CanonOut co, long long cap, hipStream_t st)
 {
@@ -920,11 +1120,11 @@ int canonical_any_length(const T *A, const T *B, long long dim, CanonOut co, lon
     const long long first = std::min(recheck_guess(dim), std::max(cap, 1LL));
     CIL_TRY(run_canonical(A, B, dim, co, first, st));
     if (cap > first) {
-        constexpr long long TAIL = 8192;
+        constexpr long long TAIL = 2048;
         co.first = first;
         co.stride = TAIL;
         const ProfMark pm = prof_begin("k_canonical", st);
-        hipLaunchKernelGGL((k_canonical<T, 1>), dim3((unsigned)(TAIL / 4)), dim3(256), 0, st, A, B, dim, co);
+        hipLaunchKernelGGL((k_canonical<T, 4>), dim3((unsigned)TAIL), dim3(256), 0, st, A, B, dim, co);
         prof_end(pm, st);
         CIL_TRY(check_launch("k_canonical"));
     }
@@ -1098,7 +1298,7 @@ int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, lon
     DistScratch s;
     CIL_TRY(scratch(1, &s));
     // the list counter slot doubles as the bad-index flag here; nexact counts fallbacks
-    CIL_TRY(fill_zero(s.nlist, sizeof(unsigned long long) * 2, st));
+    CIL_TRY(fill_zero(s.nlist, sizeof(unsigned long long) * 3, st));
     CanonOut co{};
     co.ia = ia;
     co.jb = jb;
@@ -1109,9 +1309,20 @@ int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, lon
     co.d2 = d2;
     co.nexact = s.nexact;
     co.force_exact = g_force_exact;
+    // A list as long as the grid of all pairs mostly is that grid, row by row:
+    // the device looks, and one of the two launches leaves at once (with fewer
+    // pairs the shared rows gain nothing: 4608 of d = 32768 173 against 153 us).
+    if (np == nA * nB && np >= kGridPairs && dim < (1ll << 31) && !g_force_exact) {
+        int *not_grid = (int *)(s.nlist + 2);
+        hipLaunchKernelGGL(k_list_is_grid, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, ia, jb, np, nB, not_grid);
+        CIL_TRY(check_launch("k_list_is_grid"));
+        CIL_TRY(run_canonical_grid(A, nA, 0, B, nB, 0, dim, d2, nB, 0, 1, 0, not_grid, s.nexact, st));
+        co.only_if = not_grid;
+    }
     CIL_TRY(run_canonical(A, B, dim, co, np, st));
-    unsigned long long flags[2];
-    CIL_HIP(hipMemcpyAsync(flags, s.nlist, sizeof(flags), hipMemcpyDeviceToHost, st));
+    unsigned long long *flags;
+    CIL_TRY(host_stage(HS_DIST, 4096, (void **)&flags));
+    CIL_HIP(hipMemcpyAsync(flags, s.nlist, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     CIL_TRY(stream_wait(st));
     t_pairs = np;
     t_rechecked = np;
