@@ -416,6 +416,29 @@ int cil_statistic_adaptive(const void *setA, int64_t nA, const void *setB, int64
                            double *radii, int64_t *counts, uint8_t *bins, double *Y, double *y_obs, double *f,
                            double *loglik, int32_t *m_eff, int32_t *status, void *hip_stream);
 
+/* The costs of P parameter proposals from their synthetic patterns (Alg. 3bst,
+ * eq. cil:CF_synth), all proposals together.  Per proposal p, with S_p the
+ * n_syn patterns at S + p n_syn dim:
+ *   radii of the distances between distinct patterns of S_p (cil_distance_range
+ *     with exclude_diagonal, cil_radii);
+ *   Y: cil_bootstrap_features of the bins of the pairs of S_p with (idx1, idx2);
+ *   y: the observed vector, cil_bootstrap_features of the bins of data against
+ *     S_p for every data pattern and the columns `subset`;
+ *   f, loglik, status: cil_gaussian_loglik of (Y, y).
+ * Same results as those calls, bit for bit.  Every distance is formed
+ * canonically, which is meant for few pairs per proposal (n_syn of the order
+ * of a hundred).
+ *   S device[P][n_syn][dim], data device[n_set][dim]; idx1 device[n_boot][k1],
+ *   idx2 device[n_boot][k2], subset device[ks]: indices into the n_syn patterns,
+ *   checked on the device (CIL_EINVAL).  f, loglik, status host[P]: status
+ *   CIL_OK, CIL_ENOTSPD or, for distances without a range, CIL_EINVAL (f =
+ *   loglik = NaN for either).  CIL_ENONFINITE for a non-finite distance within
+ *   a set.  2 <= n_syn <= 4096, M <= 64, n_boot >= 2.  Synchronises. */
+int cil_synthetic_costs(const void *S, int32_t P, int64_t n_syn, const void *data, int64_t n_set, int64_t dim,
+                        cil_precision prec, int32_t M, int32_t law, const int32_t *idx1, int32_t k1,
+                        const int32_t *idx2, int32_t k2, const int32_t *subset, int32_t ks, int32_t n_boot, double *f,
+                        double *loglik, int32_t *status, void *hip_stream);
+
 /* Library options (host only; they apply to later calls).
  * CIL_OPT_FORCE_EXACT_SUM (value 0/1): every canonical distance is taken by
  *   the exact (slow) summation instead of the certified double-double one;

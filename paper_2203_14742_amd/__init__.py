@@ -115,6 +115,9 @@ def lib() -> ctypes.CDLL:
         L.cil_statistic_adaptive.argtypes = [vp, i64, vp, i64, i64, ctypes.c_int, i32, i32, vp, i32, vp, i32, i32,
                                              vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.cil_statistic_adaptive.restype = ctypes.c_int
+        L.cil_synthetic_costs.argtypes = [vp, i32, i64, vp, i64, i64, ctypes.c_int, i32, i32, vp, i32, vp, i32, vp, i32,
+                                          i32, vp, vp, vp, vp]
+        L.cil_synthetic_costs.restype = ctypes.c_int
         L.cil_set_option.argtypes = [i32, i64]
         L.cil_profile.argtypes = [i32]
         L.cil_profile_read.argtypes = [ctypes.c_char_p, vp, vp]
@@ -494,6 +497,27 @@ def cil_statistic_adaptive(A, B, M: int, idxA, idxB, law: int = 0, bins=None, Y=
                                         _dev(Y, "Y"), _dev(y_obs, "y_obs"), _dev(f, "f"), _dev(ll, "loglik"),
                                         _dev(me, "m_eff"), _dev(stt, "status"), _stream(A2)))
     return lo.value, hi.value, radii, counts, bins, Y, y_obs, (f, ll, me, stt)
+
+
+def cil_synthetic_costs(S, data, n_syn: int, M: int, idx1, idx2, subset, law: int = 0):
+    """Costs of P = len(S) / n_syn proposals from their synthetic patterns S
+    [P n_syn, dim] (proposal-major) and the data [n_set, dim], with the resample
+    lists idx1 [n_boot, k1], idx2 [n_boot, k2] and the observed vector's columns
+    subset [ks].  Returns numpy (f [P], loglik [P], status [P])."""
+    import torch
+    S2, d2 = _sets(S, data)
+    dev = S2.device
+    P = S2.shape[0] // n_syn
+    idx1, idx2, subset = (x.to(device=dev, dtype=torch.int32).contiguous() for x in (idx1, idx2, subset))
+    n_boot, k1 = idx1.shape
+    if idx2.shape[0] != n_boot:
+        raise ValueError("index lists must have the same number of resamples")
+    f, ll, status = np.empty(P), np.empty(P), np.empty(P, dtype=np.int32)
+    _check(lib().cil_synthetic_costs(_dev(S2, "S"), P, n_syn, _dev(d2, "data"), d2.shape[0], S2.shape[1], _prec(S2), M,
+                                     law, _dev(idx1, "idx1"), k1, _dev(idx2, "idx2"), idx2.shape[1],
+                                     _dev(subset, "subset"), subset.numel(), n_boot, f.ctypes.data, ll.ctypes.data,
+                                     status.ctypes.data, _stream(S2)))
+    return f, ll, status
 
 
 # ------------------------------------------------ further features (Sec. 3.1)

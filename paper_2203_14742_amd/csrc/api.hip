@@ -865,6 +865,28 @@ int cil_gaussian_loglik(const double *Y, int32_t P, int32_t n_boot, int32_t M, c
     return loglik_impl(Y, P, n_boot, M, y_obs, f, loglik, m_eff, status, (hipStream_t)hip_stream);
 }
 
+int cil_synthetic_costs(const void *S, int32_t P, int64_t n_syn, const void *data, int64_t n_set, int64_t dim,
+                        cil_precision prec, int32_t M, int32_t law, const int32_t *idx1, int32_t k1,
+                        const int32_t *idx2, int32_t k2, const int32_t *subset, int32_t ks, int32_t n_boot, double *f,
+                        double *loglik, int32_t *status, void *hip_stream)
+{
+    API_BEGIN();
+    if (P < 0 || P > 65535) return set_error(CIL_EINVAL, "P must be in [0, 65535]");
+    CIL_TRY(check_sets(S, n_syn, data, n_set, dim, prec));
+    if (n_syn < 2 || n_set < 1 || k1 < 1 || k2 < 1 || ks < 1 || n_boot < 2)
+        return set_error(CIL_EINVAL, "need n_syn >= 2, n_set, k1, k2, ks >= 1 and n_boot >= 2");
+    if (n_syn > 4096 || n_set > 4096 || (int64_t)k1 * k2 > INT32_MAX || (int64_t)n_set * ks > INT32_MAX ||
+        dim >= ((int64_t)1 << 31))
+        return set_error(CIL_EINVAL, "sizes out of range");
+    if (M < 1 || M > 64) return set_error(CIL_EINVAL, "M must be in [1, 64]");
+    if (law != 0 && law != 1) return set_error(CIL_EINVAL, "unknown radius law %d", law);
+    if (P == 0) return CIL_OK;
+    if (!idx1 || !idx2 || !subset || !f || !loglik || !status) return set_error(CIL_EINVAL, "null pointer");
+    CIL_TRY(check_device());
+    return synthetic_costs_impl(S, P, n_syn, data, n_set, dim, prec, M, law, idx1, k1, idx2, k2, subset, ks, n_boot, f,
+                                loglik, status, (hipStream_t)hip_stream);
+}
+
 int cil_minmax_scale(const void *patterns, int64_t count, int32_t n, cil_precision prec, void *out, void *hip_stream)
 {
     API_BEGIN();

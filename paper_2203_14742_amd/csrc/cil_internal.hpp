@@ -39,14 +39,14 @@ enum WsSlot {
     WS_STEP_WORK_B, WS_STEP_STATE64, WS_STEP_LIST64, WS_STEP_DCT,
     WS_DIST_NORMS, WS_DIST_SPLIT_A, WS_DIST_SPLIT_B, WS_DIST_RECHECK, WS_DIST_COUNTS,
     WS_DIST_MISC, WS_DIST_SAMPLE, WS_BOOT_MISC, WS_BOOT_MULT, WS_STATS_MISC, WS_FEAT_MISC, WS_FEAT_SEG,
-    WS_DIST_REDUCED,
+    WS_DIST_REDUCED, WS_COSTS,
     WS_NUM_SLOTS
 };
 int ws_get(int slot, size_t bytes, void **ptr);
 // Pinned host buffers for the small copies between the host and the device
 // inside a call (so they run asynchronously), grow-only, one per (device,
 // slot); freed by cil_shutdown().
-enum HostSlot { HS_DIST = 0, HS_BOOT, HS_STEP, HS_NUM_SLOTS };
+enum HostSlot { HS_DIST = 0, HS_BOOT, HS_STEP, HS_COSTS, HS_NUM_SLOTS };
 int host_stage(int slot, size_t bytes, void **ptr);
 int current_device(int *dev);
 // Wait for everything issued to `st` (polls, then blocks; CIL_OPT_SYNC_SPIN_US).
@@ -128,6 +128,11 @@ int combine_segments_impl(const double *D, long long n, int nseg, int mode, doub
 int value_range_impl(const double *V, long long n, double *vmin, double *vmax, hipStream_t st);
 int bin_values_impl(const double *V, long long n, const double *radii, int M, uint8_t *bins, int64_t *counts,
                     hipStream_t st);
+
+// Costs of a batch of proposals (costs.hip).
+int synthetic_costs_impl(const void *S, int P, long long n_syn, const void *data, long long n_set, long long dim,
+                         cil_precision prec, int M, int law, const int *idx1, int k1, const int *idx2, int k2,
+                         const int *subset, int ks, int n_boot, double *f, double *loglik, int *status, hipStream_t st);
 
 // Gram FP32 -> FP64 promotion interval (gram.hip), shared with the error bound.
 int gram_flush_interval();

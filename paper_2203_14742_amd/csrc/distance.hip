@@ -564,24 +564,48 @@ __device__ __forceinline__ void canonical_pair(const T *A, const T *B, long long
 // term; the vector units issue in 80 % of the cycles): 62 500 pairs of d = 8192 in
 // FP32 take 247 us, 385 by a wavefront per pair (530 with the tracked sum).  The sums of a wavefront are reduced by halving: at each of log2(RW CW)
 // levels a lane hands over half of its pairs and keeps the rest, then plainly.
-// Set blockIdx.z starts strideA (strideB) elements further; with `tri` only pairs
-// j >= i are formed (self-pairs of one set) and written twice.
+// With `square` the columns are one of several sets (blockIdx.z, strideB elements
+// apart) and the pairs those within the set, of which only j >= i are formed and
+// written twice, followed by those of A's rows with it (rows nB, nB + 1, ... of
+// d2).  blockIdx.x then counts the tiles that are formed, one after the other, so
+// that every XCD gets its share of them (by rows and columns the eight XCDs, which
+// take workgroups in turn, had 1 to 8 of 36 tiles each: 1430 us for 20 sets of 64
+// patterns of d = 32768 and 8 rows, 1016 so).
 template <typename T, int RW, int CW, int KW>
 __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) void k_canonical_grid(
-    const T *A, long long nA, long long strideA, const T *B, long long nB, long long strideB, long long dim, double *d2,
-    long long ldd, long long strideD, int tri, const int *only_if, unsigned long long *nexact)
+    const T *A, long long nA, const T *B, long long nB, long long dim, double *d2, int square, long long strideB,
+    const int *only_if, int force_exact, unsigned long long *nexact)
 {
     constexpr int NP = RW * CW, TI = 4 * RW;
+    static_assert(CW % TI == 0, "a block's rows lie within one column tile");
     __shared__ double part[KW > 1 ? KW - 1 : 1][4][NP][2];
     if (only_if && *only_if) return;                     // the list is not the grid of all pairs
     // the wavefront's numbers in scalars: the rows' addresses then take no lane registers
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3),
               kw = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
-    const long long i0 = (long long)blockIdx.y * TI + RW * wv, j0 = (long long)blockIdx.x * CW;
-    if (tri && j0 + CW <= (long long)blockIdx.y * TI) return;      // the whole block lies below the diagonal
-    A += blockIdx.z * strideA;
-    B += blockIdx.z * strideB;
-    d2 += blockIdx.z * strideD;
+    int bi = blockIdx.y, bj = blockIdx.x;
+    bool within = false;
+    if (square) {
+        constexpr int RT = CW / TI;                      // row tiles to a column tile
+        const int nct = (int)((nB + CW - 1) / CW), ntri = RT * nct * (nct + 1) / 2, t = blockIdx.x;
+        within = t < ntri;
+        if (within) {                                    // column tile bj holds the row tiles 0 .. RT (bj + 1) - 1
+            bj = (int)((sqrtf(8.0f * (t / RT) + 1.0f) - 1.0f) * 0.5f);
+            while (RT * (bj + 1) * (bj + 2) / 2 <= t) ++bj;
+            while (RT * bj * (bj + 1) / 2 > t) --bj;
+            bi = t - RT * bj * (bj + 1) / 2;
+        } else {
+            bi = (t - ntri) / nct;
+            bj = (t - ntri) % nct;
+        }
+        B += blockIdx.z * strideB;
+        d2 += blockIdx.z * (nA + nB) * nB + (within ? 0 : nB * nB);
+        if (within) {
+            A = B;
+            nA = nB;
+        }
+    }
+    const long long i0 = (long long)bi * TI + RW * wv, j0 = (long long)bj * CW;
     const T *ra[RW], *rb[CW];
 #pragma unroll
     for (int r = 0; r < RW; ++r) ra[r] = A + min(i0 + r, nA - 1) * dim;
@@ -655,19 +679,19 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
     double D;
     bool certain = dd_certain(hi[0], lo[0], dd_delta((double)((dim + STR - 1) / STR), 6 + KW), D);
     const long long i = i0 + mine / CW, j = j0 + mine % CW;
-    const bool wanted = (lane & (64 / NP - 1)) == 0 && i < nA && j < nB && (!tri || j >= i);
-    unsigned long long redo = __ballot(wanted && !certain);
+    const bool wanted = (lane & (64 / NP - 1)) == 0 && i < nA && j < nB && (!within || j >= i);
+    unsigned long long redo = __ballot(wanted && (!certain || force_exact));
     while (redo) {                                       // rare: the whole wavefront sums that pair again
         const int src = __ffsll((long long)redo) - 1;
         redo &= redo - 1;
         const long long ii = __shfl(i, src, 64), jj = __shfl(j, src, 64);
-        const double v = canonical_tracked(A + ii * dim, B + jj * dim, dim, lane, 0, nexact);
+        const double v = canonical_tracked(A + ii * dim, B + jj * dim, dim, lane, force_exact, nexact);
         const double w = __shfl(v, 0, 64);
         if (lane == src) D = w;
     }
     if (wanted) {
-        d2[i * ldd + j] = D;
-        if (tri && j < nA && i < nB) d2[j * ldd + i] = D;
+        d2[i * nB + j] = D;
+        if (within) d2[j * nB + i] = D;
     }
 }
 
@@ -738,31 +762,28 @@ int run_canonical(const T *A, const T *B, long long dim, CanonOut &co, long long
     return check_launch("k_canonical");
 }
 
-// All pairs (k_canonical_grid) of `sets` pairs of sets.
+// All pairs of A and B (sets = 0), or the square form for `sets` sets.
 template <typename T, int RW, int CW, int KW>
-int launch_canonical_grid(const T *A, long long nA, long long strideA, const T *B, long long nB, long long strideB,
-                          long long dim, double *d2, long long ldd, long long strideD, int sets, int tri,
-                          const int *only_if, unsigned long long *nexact, hipStream_t st)
+int launch_canonical_grid(const T *A, long long nA, const T *B, long long nB, long long strideB, long long dim,
+                          double *d2, int sets, const int *only_if, unsigned long long *nexact, hipStream_t st)
 {
-    const dim3 grid((unsigned)((nB + CW - 1) / CW), (unsigned)((nA + 4 * RW - 1) / (4 * RW)), (unsigned)sets);
+    const long long nct = (nB + CW - 1) / CW, nrt = (nA + 4 * RW - 1) / (4 * RW);
+    const dim3 grid = sets ? dim3((unsigned)(CW / (4 * RW) * nct * (nct + 1) / 2 + nrt * nct), 1, (unsigned)sets)
+                           : dim3((unsigned)nct, (unsigned)nrt);
     const ProfMark pm = prof_begin("k_canonical_grid", st);
-    hipLaunchKernelGGL((k_canonical_grid<T, RW, CW, KW>), grid, dim3(256 * KW), 0, st, A, nA, strideA, B, nB, strideB,
-                       dim, d2, ldd, strideD, tri, only_if, nexact);
+    hipLaunchKernelGGL((k_canonical_grid<T, RW, CW, KW>), grid, dim3(256 * KW), 0, st, A, nA, B, nB, dim, d2, sets > 0,
+                       strideB, only_if, g_force_exact, nexact);
     prof_end(pm, st);
     return check_launch("k_canonical_grid");
 }
 template <typename T>
-int run_canonical_grid(const T *A, long long nA, long long strideA, const T *B, long long nB, long long strideB,
-                       long long dim, double *d2, long long ldd, long long strideD, int sets, int tri,
-                       const int *only_if, unsigned long long *nexact, hipStream_t st)
+int run_canonical_grid(const T *A, long long nA, const T *B, long long nB, long long strideB, long long dim, double *d2,
+                       int sets, const int *only_if, unsigned long long *nexact, hipStream_t st)
 {
-    if (nA <= 0 || nB <= 0 || sets <= 0) return CIL_OK;
-    const long long pairs = nA * nB * sets / (tri ? 2 : 1);
+    const long long pairs = sets ? sets * (nA + nB / 2) * nB : nA * nB;
     if (pairs >= kGridPairs)
-        return launch_canonical_grid<T, 2, 8, 1>(A, nA, strideA, B, nB, strideB, dim, d2, ldd, strideD, sets, tri,
-                                                 only_if, nexact, st);
-    return launch_canonical_grid<T, 1, 4, 4>(A, nA, strideA, B, nB, strideB, dim, d2, ldd, strideD, sets, tri, only_if,
-                                             nexact, st);
+        return launch_canonical_grid<T, 2, 8, 1>(A, nA, B, nB, strideB, dim, d2, sets, only_if, nexact, st);
+    return launch_canonical_grid<T, 1, 4, 4>(A, nA, B, nB, strideB, dim, d2, sets, only_if, nexact, st);
 }
 
 struct Approx {
@@ -1291,6 +1312,25 @@ template int approx_d2_impl<double>(const double *, long long, const double *, l
 template int approx_d2_impl<float>(const float *, long long, const float *, long long, long long, double *, double *,
                                    hipStream_t);
 
+// Canonical squared distances of every pair within P sets of n_syn patterns
+// (S, back to back) and between n_set patterns and each of those sets:
+// D[p][n_syn + n_set][n_syn], the set's own rows first; *nexact counts the exact
+// sums on the device.  Stream-ordered.
+template <typename T>
+int grid_distances_impl(const T *S, int P, long long n_syn, const T *data, long long n_set, long long dim, double *D,
+                        unsigned long long **nexact, hipStream_t st)
+{
+    DistScratch s;
+    CIL_TRY(scratch(1, &s));
+    CIL_TRY(fill_zero(s.nexact, sizeof(unsigned long long), st));
+    *nexact = s.nexact;
+    return run_canonical_grid(data, n_set, S, n_syn, n_syn * dim, dim, D, P, nullptr, s.nexact, st);
+}
+template int grid_distances_impl<double>(const double *, int, long long, const double *, long long, long long, double *,
+                                         unsigned long long **, hipStream_t);
+template int grid_distances_impl<float>(const float *, int, long long, const float *, long long, long long, double *,
+                                        unsigned long long **, hipStream_t);
+
 template <typename T>
 int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, long long dim, const long long *ia,
                          const long long *jb, long long np, double *d2, hipStream_t st)
@@ -1316,7 +1356,7 @@ int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, lon
         int *not_grid = (int *)(s.nlist + 2);
         hipLaunchKernelGGL(k_list_is_grid, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, ia, jb, np, nB, not_grid);
         CIL_TRY(check_launch("k_list_is_grid"));
-        CIL_TRY(run_canonical_grid(A, nA, 0, B, nB, 0, dim, d2, nB, 0, 1, 0, not_grid, s.nexact, st));
+        CIL_TRY(run_canonical_grid(A, nA, B, nB, 0, dim, d2, 0, not_grid, s.nexact, st));
         co.only_if = not_grid;
     }
     CIL_TRY(run_canonical(A, B, dim, co, np, st));
