@@ -226,8 +226,8 @@ def cil_simulate_patterns(model: int, state, problems, dt: float, max_steps: int
     """Run the solves in place on ``state`` (float32/float64 device tensor).
     scheme "euler": IMEX Euler (cil_simulate_patterns); "sbdf2": the
     second-order IMEX stepper (cil_simulate_patterns_sbdf2; with the AUTO
-    path the matrix-core kernel runs n <= 128 in FP32 and n <= 96 in FP64, the
-    plain back-end larger sides; FP32 with polish=0 only).
+    path the matrix-core kernels run n <= 128, the plain back-end larger sides;
+    FP32 with polish=0 only).
     Returns a dict of numpy arrays: steps_taken, steps_fp64, final_resid, status."""
     if scheme not in ("euler", "sbdf2"):
         raise ValueError("unknown scheme %r" % (scheme,))

@@ -9,7 +9,7 @@
 // -(4/h^2)(sin^2(pi k/2n) + sin^2(pi l/2n)), so the solve is: 2D DCT-II,
 // divide by 1 + dt nu_s Lambda_kl, inverse 2D DCT.
 //
-// Two back-ends:
+// Three back-ends:
 //   plain  one kernel per stage (reaction, row DCT, column DCT + divide,
 //          column inverse, row inverse + residual), dense cosine matrices,
 //          state streamed through HBM, host-driven step loop; any n >= 2.
@@ -19,7 +19,10 @@
 //          up to 128 in FP32, 96 in FP64), by one lane (dct_reg.hpp) or by a
 //          quad of lanes (dct_quad.hpp; n in {32, 64, 128} in FP32, {32, 64}
 //          in FP64); the workgroup evaluates its own stop rule and retires.
-// Both evaluate the stationarity residual max |u^s - u^{s-1}| / dt in FP64
+//   tiled  (stepper_split.hip) the matrix-core transforms with a wavefront per
+//          eight lines and a launch per pass over all solves, the field in
+//          memory, the plain back-end's step loop; FP64, n in 65 .. 128.
+// All evaluate the stationarity residual max |u^s - u^{s-1}| / dt in FP64
 // every check_every steps (and at max_steps), per solve.  FP32 solves whose
 // residual falls below the FP32 floor continue in FP64 (phase 2).
 #include <hip/hip_runtime.h>
@@ -27,6 +30,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -619,6 +623,21 @@ bool persistent_supported(int n, bool f32, int path)
     return path == CIL_PATH_AUTO && n >= 2 && n <= mm_max_side(f32);
 }
 
+// Whether the solves whose side has both a persistent and a tile-by-tile kernel
+// take the latter (FP64, 65 to 96): while all solves of the call together have
+// at most 1200 wavefronts, a little more than one to a SIMD, and evaluation
+// steps, at which the host looks, are at least three apart.  Measured (us per
+// step, tile by tile / persistent; FHN 96^2): 1 solve 16.0 / 28.9, 32 20.9 / 31.2,
+// 64 24.0 / 31.6, 128 37.9 / 32.8; 16 solves evaluated every step 42.6 / 44.4,
+// every second 30.3 / 37.0, 64 solves every second 38.9 / 37.2, every third
+// 32.8 / 34.7; 128 solves of sides 64, 51, 70 in turn 25.5 / 31.8, 256 37.7 / 33.0.
+bool tile_by_tile(const std::vector<DevSolve> &hs, bool f32, int check)
+{
+    int64_t waves = 0;
+    for (const DevSolve &s : hs) waves += mm_padded(s.n) / 8;
+    return !f32 && waves <= 1200 && check >= 3;
+}
+
 int quad_shape(bool f32, int n)
 {
     if (g_quad_shape_option >= 0) return g_quad_shape_option;
@@ -756,13 +775,18 @@ int launch_persistent(int n, bool quad, int shape, int nl, const DevSolve *S, co
     return check_launch(name);
 }
 
-// One plain group: solves with one grid side n, advanced in lockstep.
+// One plain group: solves with one grid side n, advanced in lockstep; or the
+// solves of any sides that step tile by tile on the matrix cores (split).
 struct PlainGroup {
     int n = 0;
     std::vector<int> active;
     int *dlist = nullptr;
     void *work = nullptr;         // 2 buffers [cap][2][n][n]
     size_t work_cap = 0;
+    bool split = false;
+    std::vector<std::vector<SplitItem>> tiles;    // per active solve
+    std::vector<SplitItem> items;                 // in launch order
+    SplitItem *ditems = nullptr;
 };
 
 // History of the second-order stepper for one plain launch: u^{s-2} and
@@ -1016,11 +1040,13 @@ int launch_mixed_named(FusedKind kind, int n, int nl, const DevSolve *S, const i
 
 // Fused solves, all sides in one go: every workgroup runs its solve from
 // steps[b] until its stop rule fires.  `dsteps/dres/dstat` are per-solve
-// device arrays; the host copies are refreshed after the launches.
+// device arrays; the host copies are refreshed after the launches.  `aside`, if
+// given, is called once the kernels run, all on streams of their own, to run
+// other solves on the caller's stream beside them.
 template <typename T>
 int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, DevSolve *dS, T *state,
               FusedKind kind, double floor_coef, long long *dsteps, double *dres, int *dstat,
-              const MixedArgs *mx = nullptr)
+              const MixedArgs *mx = nullptr, const std::function<int()> *aside = nullptr)
 {
     if (byn.empty()) return CIL_OK;
     const bool quad = kind != KIND_LINE;
@@ -1070,7 +1096,7 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
     const int ng = (int)byn.size();
     // a side per stream, at most eight streams (a batch may hold a hundred sides; four hardware queues serve them)
     const int nst = std::min(ng, 8);
-    if (ng > 1) {
+    if (ng > 1 || aside) {
         CIL_TRY(aux_streams(nst, ng, &aux));
         CIL_HIP(hipEventRecord(aux->ev[0], c.st));
     }
@@ -1096,10 +1122,7 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
                                            (const float *)(kind == KIND_MM ? mms[gi].tab : tabs[gi]),
                                            (const double *)tabs64[gi], c.model, c.dt, pa, pa64, mx->sw, mx->refine,
                                            mode, gst));
-                if (aux) {
-                    CIL_HIP(hipEventRecord(aux->ev[1 + gi], gst));
-                    CIL_HIP(hipStreamWaitEvent(c.st, aux->ev[1 + gi], 0));
-                }
+                if (aux) CIL_HIP(hipEventRecord(aux->ev[1 + gi], gst));
                 continue;
             }
         }
@@ -1110,11 +1133,11 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
         else
             CIL_TRY(launch_persistent<T>(kv.first, quad, shape, (int)kv.second.size(), dS, dls[gi], state,
                                          (const T *)tabs[gi], c.model, c.dt, pa, gst));
-        if (aux) {
-            CIL_HIP(hipEventRecord(aux->ev[1 + gi], gst));
-            CIL_HIP(hipStreamWaitEvent(c.st, aux->ev[1 + gi], 0));
-        }
+        if (aux) CIL_HIP(hipEventRecord(aux->ev[1 + gi], gst));
     }
+    if (aside) CIL_TRY((*aside)());
+    if (aux)
+        for (int gi = 0; gi < ng; ++gi) CIL_HIP(hipStreamWaitEvent(c.st, aux->ev[1 + gi], 0));
     HostResults h;
     CIL_TRY(fetch_results(c, B, dsteps, dres, dstat, mx ? mx->sw : nullptr, &h));
     for (size_t gi = 0; gi < groups.size(); ++gi)
@@ -1232,14 +1255,41 @@ int run_fused_sbdf2(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::
     return CIL_OK;
 }
 
+// Launch order of a split group's tiles: workgroups go round the eight XCDs, and a
+// solve's tiles all go to one of them, whose L2 then holds its field between the
+// passes (64 solves of 128^2: 25.8 us a step, 34.6 in the solves' order).  Solves in order of falling cost, each to the XCD with the least.
+int upload_items(PlainGroup &g, hipStream_t st)
+{
+    constexpr int X = 8;
+    std::vector<SplitItem> per[X];
+    std::vector<const std::vector<SplitItem> *> order;
+    for (auto &t : g.tiles) order.push_back(&t);
+    std::stable_sort(order.begin(), order.end(), [](auto *a, auto *b) { return a->size() > b->size(); });
+    for (auto *t : order) {
+        auto *x = std::min_element(per, per + X, [](auto &a, auto &b) { return a.size() < b.size(); });
+        x->insert(x->end(), t->begin(), t->end());
+    }
+    size_t most = 0;
+    for (auto &x : per) most = std::max(most, x.size());
+    SplitItem none{};
+    none.b = -1;
+    for (size_t k = 0; k < most; ++k)
+        for (auto &x : per) g.items.push_back(k < x.size() ? x[k] : none);
+    CIL_HIP(hipMemcpyAsync(g.ditems, g.items.data(), sizeof(SplitItem) * g.items.size(), hipMemcpyHostToDevice, st));
+    return CIL_OK;
+}
+
 // Plain solves: host-driven lockstep loop from a common step `start`; a
 // launch per stage per step, the residual read back every check_every steps.
 template <typename T>
 int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T *state, int64_t start,
               double floor_coef, StepResults R, int B)
 {
-    std::vector<unsigned long long> h_resid(B), h_maxabs(B);
-    std::vector<int> h_bad(B);
+    char *stage;
+    const size_t b8 = sizeof(unsigned long long) * (size_t)B, rbytes = 2 * b8 + sizeof(int) * (size_t)B;
+    CIL_TRY(host_stage(HS_STEP, rbytes, (void **)&stage));
+    const unsigned long long *h_resid = (const unsigned long long *)stage, *h_maxabs = h_resid + B;
+    const int *h_bad = (const int *)(stage + 2 * b8);
     int64_t step = start;
     auto any_active = [&]() {
         for (auto &g : groups)
@@ -1254,13 +1304,24 @@ int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T 
             const int nl = (int)g.active.size();
             CIL_HIP(hipMemcpyAsync(g.dlist, g.active.data(), sizeof(int) * nl, hipMemcpyHostToDevice, c.st));
             hipLaunchKernelGGL(k_clear_results, dim3((nl + 255) / 256), dim3(256), 0, c.st, g.dlist, nl, R);
+            if constexpr (std::is_same<T, double>::value) {
+                if (g.split) {
+                    if (g.items.empty()) CIL_TRY(upload_items(g, c.st));
+                    SplitArgs a{};
+                    a.items = g.ditems;
+                    a.state = state;
+                    a.res = R;
+                    const ProfMark pm = prof_begin(c.scheme ? "split_step_sbdf2_f64" : "split_step_f64", c.st);
+                    CIL_TRY(launch_split(a, (int)g.items.size(), c.model, c.dt, K, c.scheme != 0, step == 0, c.st));
+                    prof_end(pm, c.st);
+                    continue;
+                }
+            }
             const Sbdf2Args<T> bdf{(T *)c.uh, (T *)c.fh, step};
             CIL_TRY(launch_plain<T>(g, dS, state, nl, c.model, c.dt, K, R, c.st, c.scheme ? &bdf : nullptr));
         }
-        CIL_HIP(hipMemcpyAsync(h_resid.data(), R.resid, sizeof(unsigned long long) * B, hipMemcpyDeviceToHost, c.st));
-        CIL_HIP(hipMemcpyAsync(h_maxabs.data(), R.maxabs, sizeof(unsigned long long) * B, hipMemcpyDeviceToHost, c.st));
-        CIL_HIP(hipMemcpyAsync(h_bad.data(), R.bad, sizeof(int) * B, hipMemcpyDeviceToHost, c.st));
-        CIL_HIP(hipStreamSynchronize(c.st));
+        CIL_HIP(hipMemcpyAsync(stage, R.resid, rbytes, hipMemcpyDeviceToHost, c.st));
+        CIL_TRY(stream_wait(c.st));
         step = next;
         for (auto &g : groups) {
             std::vector<int> keep;
@@ -1290,16 +1351,72 @@ int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T 
                 }
                 keep.push_back(b);
             }
+            if (g.split && keep.size() < g.active.size()) {
+                g.items.clear();
+                g.tiles.erase(std::remove_if(g.tiles.begin(), g.tiles.end(),
+                                             [&](const std::vector<SplitItem> &t) {
+                                                 return std::find(keep.begin(), keep.end(), t[0].b) == keep.end();
+                                             }),
+                              g.tiles.end());
+            }
             g.active.swap(keep);
         }
     }
     return CIL_OK;
 }
 
-template <typename T>
-int make_plain_groups(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<PlainGroup> &out)
+// The solves of `byn` as one split group: tables per side, items per tile.
+int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, PlainGroup *g)
 {
+    size_t work = 0;
+    for (auto &kv : byn) work += (size_t)2 * mm_padded(kv.first) * mm_padded(kv.first) * kv.second.size();
+    double *w, *h = nullptr;
+    CIL_TRY(c.cb->alloc((void **)&w, sizeof(double) * work));
+    if (c.scheme) CIL_TRY(c.cb->alloc((void **)&h, sizeof(double) * 2 * work));
+    size_t most = 0;
     for (auto &kv : byn) {
+        MmTables mt;
+        CIL_TRY(make_mm_tables<double>(c, kv.first, kv.second, hs, &mt, c.scheme ? 2.0 * c.dt / 3.0 : 0.0));
+        const int N = mm_padded(kv.first), per = 2 * N * 8;           // values to a tile
+        for (int b : kv.second) {
+            std::vector<SplitItem> tiles(N / 8);
+            for (int t = 0; t < N / 8; ++t) {
+                const size_t div = (size_t)hs[b].tab * 2 * N * N + (size_t)t * per;
+                tiles[t] = SplitItem{hs[b], b, t, (const double *)mt.cst, (const double *)mt.tab + div,
+                                     c.scheme ? (const double *)mt.tab2 + div : nullptr, w,
+                                     h ? h + (size_t)2 * t * per : nullptr};
+            }
+            g->tiles.push_back(std::move(tiles));
+            g->active.push_back(b);
+            w += (size_t)2 * N * N;
+            if (h) h += (size_t)4 * N * N;
+            most = std::max<size_t>(most, N / 8);
+        }
+    }
+    g->split = true;
+    // the fullest XCD exceeds the average by at most one solve
+    size_t all = 0;
+    for (auto &t : g->tiles) all += t.size();
+    CIL_TRY(c.cb->alloc((void **)&g->ditems, sizeof(SplitItem) * (all + 8 * most)));
+    CIL_TRY(c.cb->alloc((void **)&g->dlist, sizeof(int) * g->active.size()));
+    return CIL_OK;
+}
+
+template <typename T>
+int make_plain_groups(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, bool split,
+                      std::vector<PlainGroup> &out)
+{
+    std::map<int, std::vector<int>> tiled;
+    if (split)
+        for (auto &kv : byn)
+            if (split_supported(kv.first, std::is_same<T, float>::value)) tiled.insert(kv);
+    if (!tiled.empty()) {
+        PlainGroup g;
+        CIL_TRY(make_split_group(c, tiled, hs, &g));
+        out.push_back(std::move(g));
+    }
+    for (auto &kv : byn) {
+        if (tiled.count(kv.first)) continue;
         PlainGroup g;
         g.n = kv.first;
         g.active = kv.second;
@@ -1361,8 +1478,11 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         total += elems[b];
     }
 
-    // phase 1: fused sides run persistently, the rest in the plain lockstep loop
+    // phase 1: fused sides run persistently, the rest in the lockstep loop (FP64
+    // sides up to 128 tile by tile on the matrix cores, others in plain kernels)
+    const bool autop = stp->path == CIL_PATH_AUTO;
     std::map<int, std::vector<int>> fused_byn, plain_byn;
+    const bool tiled = autop && tile_by_tile(hs, f32, (int)stp->check_every);
     for (int b = 0; b < B; ++b) {
         const int n = hs[b].n;
         const bool fs = persistent_supported(n, f32, stp->path) &&
@@ -1370,10 +1490,12 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         if (stp->path >= CIL_PATH_FUSED && !fs)
             return set_error(CIL_EUNSUPPORTED, "no fused %sstepper for n = %d in %s", scheme ? "second-order " : "", n,
                              f32 ? "FP32" : "FP64");
-        if (fs) fused_byn[n].push_back(b);
+        if (fs && !(tiled && split_supported(n, f32))) fused_byn[n].push_back(b);
         else plain_byn[n].push_back(b);
     }
-    if (scheme && !plain_byn.empty()) {              // the plain back-end keeps the history in HBM
+    bool plain_hist = false;                         // the plain kernels keep the history in HBM
+    for (auto &kv : plain_byn) plain_hist |= !(autop && split_supported(kv.first, f32));
+    if (scheme && plain_hist) {
         int64_t end = 0;
         for (int b = 0; b < B; ++b) end = std::max<int64_t>(end, hs[b].off + elems[b]);
         const size_t es = f32 ? sizeof(float) : sizeof(double);
@@ -1390,9 +1512,9 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
     CIL_TRY(cb.alloc((void **)&dstat, sizeof(int) * B));
     CIL_TRY(fill_zero(dstat, sizeof(int) * B, st));
     StepResults R;
-    CIL_TRY(cb.alloc((void **)&R.resid, sizeof(unsigned long long) * B));
-    CIL_TRY(cb.alloc((void **)&R.maxabs, sizeof(unsigned long long) * B));
-    CIL_TRY(cb.alloc((void **)&R.bad, sizeof(int) * B));
+    CIL_TRY(cb.alloc((void **)&R.resid, (2 * sizeof(unsigned long long) + sizeof(int)) * B));   // read back as one block
+    R.maxabs = R.resid + B;
+    R.bad = (int *)(R.maxabs + B);
 
     c.sw.assign(B, -1);
     MixedArgs mx{nullptr, nullptr, c.polish == 2};
@@ -1405,25 +1527,26 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         CIL_TRY(cb.alloc((void **)&mx.state64, sizeof(double) * (size_t)end));
         CIL_TRY(cb.alloc((void **)&mx.sw, sizeof(long long) * B));
     }
+    std::vector<PlainGroup> pg;
+    if (f32) CIL_TRY(make_plain_groups<float>(c, plain_byn, hs, autop, pg));
+    else CIL_TRY(make_plain_groups<double>(c, plain_byn, hs, autop, pg));
+    const std::function<int()> lockstep = [&]() -> int {
+        return f32 ? run_plain<float>(c, pg, dS, (float *)state, 0, c.floor_coef32, R, B)
+                   : run_plain<double>(c, pg, dS, (double *)state, 0, 0.0, R, B);
+    };
+    const std::function<int()> *aside = pg.empty() ? nullptr : &lockstep;
     if (scheme && kind == KIND_LINE) {
         if (f32) CIL_TRY(run_fused_sbdf2<float>(c, fused_byn, hs, dS, (float *)state, c.floor_coef32, dsteps, dres, dstat));
         else CIL_TRY(run_fused_sbdf2<double>(c, fused_byn, hs, dS, (double *)state, 0.0, dsteps, dres, dstat));
     } else if (f32) {
         CIL_TRY(run_fused<float>(c, fused_byn, hs, dS, (float *)state, kind, c.floor_coef32, dsteps, dres, dstat,
-                                 use_mixed ? &mx : nullptr));
+                                 use_mixed ? &mx : nullptr, aside));
     } else {
-        CIL_TRY(run_fused<double>(c, fused_byn, hs, dS, (double *)state, kind, 0.0, dsteps, dres, dstat));
+        CIL_TRY(run_fused<double>(c, fused_byn, hs, dS, (double *)state, kind, 0.0, dsteps, dres, dstat, nullptr, aside));
     }
-    if (!plain_byn.empty()) {
+    if (fused_byn.empty() && aside) {
         CIL_HIP(hipMemcpyAsync(dS, hs.data(), sizeof(DevSolve) * B, hipMemcpyHostToDevice, st));
-        std::vector<PlainGroup> pg;
-        if (f32) {
-            CIL_TRY(make_plain_groups<float>(c, plain_byn, pg));
-            CIL_TRY(run_plain<float>(c, pg, dS, (float *)state, 0, c.floor_coef32, R, B));
-        } else {
-            CIL_TRY(make_plain_groups<double>(c, plain_byn, pg));
-            CIL_TRY(run_plain<double>(c, pg, dS, (double *)state, 0, 0.0, R, B));
-        }
+        CIL_TRY(lockstep());
     }
 
     // phase 2: FP32 solves stopped at the FP32 floor continue: those whose
@@ -1475,12 +1598,12 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
             else pz[std::make_pair(hs[b].n, c.steps[b])].push_back(b);
         }
         CIL_TRY(run_fused<double>(c, fz, hs64, dS64, state64, kind, 0.0, dsteps, dres, dstat));
-        if (!pz.empty()) CIL_HIP(hipMemcpyAsync(dS64, hs64.data(), sizeof(DevSolve) * B, hipMemcpyHostToDevice, st));
         for (auto &kv : pz) {
             std::map<int, std::vector<int>> one;
             one[kv.first.first] = kv.second;
             std::vector<PlainGroup> pg;
-            CIL_TRY(make_plain_groups<double>(c, one, pg));
+            CIL_TRY(make_plain_groups<double>(c, one, hs64, autop, pg));
+            CIL_HIP(hipMemcpyAsync(dS64, hs64.data(), sizeof(DevSolve) * B, hipMemcpyHostToDevice, st));
             CIL_TRY(run_plain<double>(c, pg, dS64, state64, kv.first.second, 0.0, R, B));
         }
         for (int b : promoted) steps64[b] = c.steps[b] - before[b];

@@ -49,6 +49,23 @@ __global__ void k_mm_dense_const(int n, T *out)
     out[e] = T(v);
 }
 
+// The line of side n <= 128: f(LineType).
+template <typename T, typename F>
+int mm_line(int n, F &&f)
+{
+    if (n == 32) return f(Line32<T>{});
+    if (n == 64) return f(Line64<T>{});
+    if (n == 128) return f(Line128<T>{});
+    if (n < 2) return CIL_EUNSUPPORTED;
+    switch (mm_padded(n)) {
+    case 32: return f(LineDense<T, 1>{});
+    case 64: return f(LineDense<T, 2>{});
+    case 96: return f(LineDense<T, 3>{});
+    case 128: return f(LineDense<T, 4>{});
+    default: return CIL_EUNSUPPORTED;
+    }
+}
+
 // The line of side n and its launch shape: f(LineType, TPW, WPE), TPW the tiles
 // per wavefront, WPE the wavefronts per SIMD to allocate registers for.
 template <typename Line, int TPW, int WPE, typename F>
@@ -81,7 +98,7 @@ int mm_dispatch(int n, F &&f)
 template <typename T>
 int mm_make_tables(int n, const TabSpec *specs, int ntab, double dt, T *out, hipStream_t st)
 {
-    return mm_dispatch<T>(n, [&](auto line, auto, auto) -> int {
+    return mm_line<T>(n, [&](auto line) -> int {
         using Line = decltype(line);
         hipLaunchKernelGGL((k_mm_tables<T, Line>), dim3((2 * Line::N * Line::N + 255) / 256, ntab), dim3(256), 0, st,
                            specs, ntab, n, dt, out);
@@ -92,7 +109,7 @@ int mm_make_tables(int n, const TabSpec *specs, int ntab, double dt, T *out, hip
 template <typename T>
 int mm_make_consts(int n, T *out, hipStream_t st)
 {
-    return mm_dispatch<T>(n, [&](auto line, auto, auto) -> int {
+    return mm_line<T>(n, [&](auto line) -> int {
         using Line = decltype(line);
         if constexpr (Line::kRagged) {
             constexpr int NB = Line::N / 32;
