@@ -174,7 +174,8 @@ int cil_simulate_patterns(cil_model model, cil_precision prec, const cil_problem
  * Back-ends: a persistent kernel on the matrix cores (path AUTO: n <= 128 in
  * FP32, n <= 96 in FP64; path FUSED: n = 32 and, in FP32, n = 64, else
  * CIL_EUNSUPPORTED); the same transforms tile by tile over many compute units
- * (path AUTO, n <= 128 in FP64); one with a lane per grid line (path FUSED_LINE, the sides
+ * (path AUTO, 64 < n <= 128, where a call's solves do not fill the chip and in
+ * FP64 above 96); one with a lane per grid line (path FUSED_LINE, the sides
  * of FUSED); the plain back-end (history in two state-sized device buffers from
  * the library's buffer pool; path PLAIN, and AUTO for larger sides).  FUSED_QUAD is
  * CIL_EUNSUPPORTED.  FP32: polish must be 0 (no FP64 continuation; a solve

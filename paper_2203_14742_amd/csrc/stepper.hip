@@ -21,7 +21,7 @@
 //          in FP64); the workgroup evaluates its own stop rule and retires.
 //   tiled  (stepper_split.hip) the matrix-core transforms with a wavefront per
 //          eight lines and a launch per pass over all solves, the field in
-//          memory, the plain back-end's step loop; FP64, n in 65 .. 128.
+//          memory, the plain back-end's step loop; n in 65 .. 128.
 // All evaluate the stationarity residual max |u^s - u^{s-1}| / dt in FP64
 // every check_every steps (and at max_steps), per solve.  FP32 solves whose
 // residual falls below the FP32 floor continue in FP64 (phase 2).
@@ -623,19 +623,22 @@ bool persistent_supported(int n, bool f32, int path)
     return path == CIL_PATH_AUTO && n >= 2 && n <= mm_max_side(f32);
 }
 
-// Whether the solves whose side has both a persistent and a tile-by-tile kernel
-// take the latter (FP64, 65 to 96): while all solves of the call together have
-// at most 1200 wavefronts, a little more than one to a SIMD, and evaluation
-// steps, at which the host looks, are at least three apart.  Measured (us per
-// step, tile by tile / persistent; FHN 96^2): 1 solve 16.0 / 28.9, 32 20.9 / 31.2,
-// 64 24.0 / 31.6, 128 37.9 / 32.8; 16 solves evaluated every step 42.6 / 44.4,
-// every second 30.3 / 37.0, 64 solves every second 38.9 / 37.2, every third
-// 32.8 / 34.7; 128 solves of sides 64, 51, 70 in turn 25.5 / 31.8, 256 37.7 / 33.0.
-bool tile_by_tile(const std::vector<DevSolve> &hs, bool f32, int check)
+// Whether a side that has both a persistent and a tile-by-tile kernel takes the
+// latter: while all solves of the call together are few wavefronts for the
+// chip's 1024 SIMDs, and the evaluation steps, at which the host looks, are
+// some steps apart.  us per step, tile by tile / persistent (FHN):
+//   FP64 96^2        1 solve 16.0 / 28.9, 32 20.9 / 31.2, 64 24.0 / 31.6, 128 37.9 /
+//                    32.8; 16 solves evaluated every step 42.6 / 44.4, every
+//                    second 30.3 / 37.0, 64 every second 38.9 / 37.2, every third
+//                    32.8 / 34.7; 128 of sides 64, 51, 70 25.5 / 31.8, 256 37.7 / 33.0
+//   FP32 112^2       1 solve 16.4 / 38.0, 64 25.5 / 40.9, 128 40.0 / 41.0, 192 52 / 42
+//   FP32 96^2        1 solve 12.0 / 15.8, 32 16.7 / 18.2, 48 17.2 / 18.1, 64 18.7 / 18.1
+//   FP32 128^2       1 solve 10.5 / 14.4, 32 15.4 / 16.5, 48 17.4 / 16.4
+bool tile_by_tile(int n, bool f32, int64_t waves, int check)
 {
-    int64_t waves = 0;
-    for (const DevSolve &s : hs) waves += mm_padded(s.n) / 8;
-    return !f32 && waves <= 1200 && check >= 3;
+    if (!split_supported(n)) return false;
+    if (f32 && (n <= 96 || n == 128)) return waves <= 512 && check >= 8;
+    return waves <= (f32 ? 1900 : 1200) && check >= 3;
 }
 
 int quad_shape(bool f32, int n)
@@ -777,6 +780,7 @@ int launch_persistent(int n, bool quad, int shape, int nl, const DevSolve *S, co
 
 // One plain group: solves with one grid side n, advanced in lockstep; or the
 // solves of any sides that step tile by tile on the matrix cores (split).
+template <typename T>
 struct PlainGroup {
     int n = 0;
     std::vector<int> active;
@@ -784,9 +788,11 @@ struct PlainGroup {
     void *work = nullptr;         // 2 buffers [cap][2][n][n]
     size_t work_cap = 0;
     bool split = false;
-    std::vector<std::vector<SplitItem>> tiles;    // per active solve
-    std::vector<SplitItem> items;                 // in launch order
-    SplitItem *ditems = nullptr;
+    std::vector<std::vector<SplitItem<T>>> tiles;    // per active solve
+    std::vector<SplitItem<T>> items;              // in launch order
+    SplitItem<T> *ditems = nullptr;
+    T *c0 = nullptr;
+    bool started = false;
 };
 
 // History of the second-order stepper for one plain launch: u^{s-2} and
@@ -798,7 +804,7 @@ struct Sbdf2Args {
 };
 
 template <typename T>
-int launch_plain(PlainGroup &g, const DevSolve *S, T *u, int nl, int model, double dt, int K, StepResults R,
+int launch_plain(PlainGroup<T> &g, const DevSolve *S, T *u, int nl, int model, double dt, int K, StepResults R,
                  hipStream_t st, const Sbdf2Args<T> *bdf = nullptr)
 {
     PlainTables tb;
@@ -1258,11 +1264,12 @@ int run_fused_sbdf2(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::
 // Launch order of a split group's tiles: workgroups go round the eight XCDs, and a
 // solve's tiles all go to one of them, whose L2 then holds its field between the
 // passes (64 solves of 128^2: 25.8 us a step, 34.6 in the solves' order).  Solves in order of falling cost, each to the XCD with the least.
-int upload_items(PlainGroup &g, hipStream_t st)
+template <typename T>
+int upload_items(PlainGroup<T> &g, hipStream_t st)
 {
     constexpr int X = 8;
-    std::vector<SplitItem> per[X];
-    std::vector<const std::vector<SplitItem> *> order;
+    std::vector<SplitItem<T>> per[X];
+    std::vector<const std::vector<SplitItem<T>> *> order;
     for (auto &t : g.tiles) order.push_back(&t);
     std::stable_sort(order.begin(), order.end(), [](auto *a, auto *b) { return a->size() > b->size(); });
     for (auto *t : order) {
@@ -1271,18 +1278,18 @@ int upload_items(PlainGroup &g, hipStream_t st)
     }
     size_t most = 0;
     for (auto &x : per) most = std::max(most, x.size());
-    SplitItem none{};
+    SplitItem<T> none{};
     none.b = -1;
     for (size_t k = 0; k < most; ++k)
         for (auto &x : per) g.items.push_back(k < x.size() ? x[k] : none);
-    CIL_HIP(hipMemcpyAsync(g.ditems, g.items.data(), sizeof(SplitItem) * g.items.size(), hipMemcpyHostToDevice, st));
+    CIL_HIP(hipMemcpyAsync(g.ditems, g.items.data(), sizeof(SplitItem<T>) * g.items.size(), hipMemcpyHostToDevice, st));
     return CIL_OK;
 }
 
 // Plain solves: host-driven lockstep loop from a common step `start`; a
 // launch per stage per step, the residual read back every check_every steps.
 template <typename T>
-int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T *state, int64_t start,
+int run_plain(SimCtx &c, std::vector<PlainGroup<T>> &groups, const DevSolve *dS, T *state, int64_t start,
               double floor_coef, StepResults R, int B)
 {
     char *stage;
@@ -1304,18 +1311,23 @@ int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T 
             const int nl = (int)g.active.size();
             CIL_HIP(hipMemcpyAsync(g.dlist, g.active.data(), sizeof(int) * nl, hipMemcpyHostToDevice, c.st));
             hipLaunchKernelGGL(k_clear_results, dim3((nl + 255) / 256), dim3(256), 0, c.st, g.dlist, nl, R);
-            if constexpr (std::is_same<T, double>::value) {
-                if (g.split) {
-                    if (g.items.empty()) CIL_TRY(upload_items(g, c.st));
-                    SplitArgs a{};
-                    a.items = g.ditems;
-                    a.state = state;
-                    a.res = R;
-                    const ProfMark pm = prof_begin(c.scheme ? "split_step_sbdf2_f64" : "split_step_f64", c.st);
-                    CIL_TRY(launch_split(a, (int)g.items.size(), c.model, c.dt, K, c.scheme != 0, step == 0, c.st));
-                    prof_end(pm, c.st);
-                    continue;
+            if (g.split) {
+                if (g.items.empty()) CIL_TRY(upload_items(g, c.st));
+                constexpr bool f32 = std::is_same<T, float>::value;
+                if constexpr (f32) {
+                    if (!g.started) CIL_TRY(launch_split_offsets(dS, g.dlist, nl, state, g.c0, c.model, c.st));
+                    g.started = true;
                 }
+                SplitArgs<T> a{};
+                a.items = g.ditems;
+                a.state = state;
+                a.c0 = g.c0;
+                a.res = R;
+                const ProfMark pm = prof_begin(c.scheme ? (f32 ? "split_step_sbdf2_f32" : "split_step_sbdf2_f64")
+                                                        : (f32 ? "split_step_f32" : "split_step_f64"), c.st);
+                CIL_TRY(launch_split<T>(a, (int)g.items.size(), c.model, c.dt, K, c.scheme != 0, step == 0, c.st));
+                prof_end(pm, c.st);
+                continue;
             }
             const Sbdf2Args<T> bdf{(T *)c.uh, (T *)c.fh, step};
             CIL_TRY(launch_plain<T>(g, dS, state, nl, c.model, c.dt, K, R, c.st, c.scheme ? &bdf : nullptr));
@@ -1354,7 +1366,7 @@ int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T 
             if (g.split && keep.size() < g.active.size()) {
                 g.items.clear();
                 g.tiles.erase(std::remove_if(g.tiles.begin(), g.tiles.end(),
-                                             [&](const std::vector<SplitItem> &t) {
+                                             [&](const std::vector<SplitItem<T>> &t) {
                                                  return std::find(keep.begin(), keep.end(), t[0].b) == keep.end();
                                              }),
                               g.tiles.end());
@@ -1366,24 +1378,25 @@ int run_plain(SimCtx &c, std::vector<PlainGroup> &groups, const DevSolve *dS, T 
 }
 
 // The solves of `byn` as one split group: tables per side, items per tile.
-int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, PlainGroup *g)
+template <typename T>
+int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, PlainGroup<T> *g)
 {
     size_t work = 0;
     for (auto &kv : byn) work += (size_t)2 * mm_padded(kv.first) * mm_padded(kv.first) * kv.second.size();
-    double *w, *h = nullptr;
-    CIL_TRY(c.cb->alloc((void **)&w, sizeof(double) * work));
-    if (c.scheme) CIL_TRY(c.cb->alloc((void **)&h, sizeof(double) * 2 * work));
+    T *w, *h = nullptr;
+    CIL_TRY(c.cb->alloc((void **)&w, sizeof(T) * work));
+    if (c.scheme) CIL_TRY(c.cb->alloc((void **)&h, sizeof(T) * 2 * work));
     size_t most = 0;
     for (auto &kv : byn) {
         MmTables mt;
-        CIL_TRY(make_mm_tables<double>(c, kv.first, kv.second, hs, &mt, c.scheme ? 2.0 * c.dt / 3.0 : 0.0));
+        CIL_TRY(make_mm_tables<T>(c, kv.first, kv.second, hs, &mt, c.scheme ? 2.0 * c.dt / 3.0 : 0.0));
         const int N = mm_padded(kv.first), per = 2 * N * 8;           // values to a tile
         for (int b : kv.second) {
-            std::vector<SplitItem> tiles(N / 8);
+            std::vector<SplitItem<T>> tiles(N / 8);
             for (int t = 0; t < N / 8; ++t) {
                 const size_t div = (size_t)hs[b].tab * 2 * N * N + (size_t)t * per;
-                tiles[t] = SplitItem{hs[b], b, t, (const double *)mt.cst, (const double *)mt.tab + div,
-                                     c.scheme ? (const double *)mt.tab2 + div : nullptr, w,
+                tiles[t] = SplitItem<T>{hs[b], b, t, (const T *)mt.cst, (const T *)mt.tab + div,
+                                     c.scheme ? (const T *)mt.tab2 + div : nullptr, w,
                                      h ? h + (size_t)2 * t * per : nullptr};
             }
             g->tiles.push_back(std::move(tiles));
@@ -1397,27 +1410,28 @@ int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std:
     // the fullest XCD exceeds the average by at most one solve
     size_t all = 0;
     for (auto &t : g->tiles) all += t.size();
-    CIL_TRY(c.cb->alloc((void **)&g->ditems, sizeof(SplitItem) * (all + 8 * most)));
+    CIL_TRY(c.cb->alloc((void **)&g->ditems, sizeof(SplitItem<T>) * (all + 8 * most)));
+    CIL_TRY(c.cb->alloc((void **)&g->c0, sizeof(T) * 2 * hs.size()));
     CIL_TRY(c.cb->alloc((void **)&g->dlist, sizeof(int) * g->active.size()));
     return CIL_OK;
 }
 
 template <typename T>
 int make_plain_groups(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, bool split,
-                      std::vector<PlainGroup> &out)
+                      std::vector<PlainGroup<T>> &out)
 {
     std::map<int, std::vector<int>> tiled;
     if (split)
         for (auto &kv : byn)
-            if (split_supported(kv.first, std::is_same<T, float>::value)) tiled.insert(kv);
+            if (split_supported(kv.first)) tiled.insert(kv);
     if (!tiled.empty()) {
-        PlainGroup g;
+        PlainGroup<T> g;
         CIL_TRY(make_split_group(c, tiled, hs, &g));
         out.push_back(std::move(g));
     }
     for (auto &kv : byn) {
         if (tiled.count(kv.first)) continue;
-        PlainGroup g;
+        PlainGroup<T> g;
         g.n = kv.first;
         g.active = kv.second;
         g.work_cap = kv.second.size();
@@ -1478,11 +1492,12 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         total += elems[b];
     }
 
-    // phase 1: fused sides run persistently, the rest in the lockstep loop (FP64
-    // sides up to 128 tile by tile on the matrix cores, others in plain kernels)
+    // phase 1: fused sides run persistently, the rest in the lockstep loop (sides
+    // of 65 to 128 tile by tile on the matrix cores, others in plain kernels)
     const bool autop = stp->path == CIL_PATH_AUTO;
     std::map<int, std::vector<int>> fused_byn, plain_byn;
-    const bool tiled = autop && tile_by_tile(hs, f32, (int)stp->check_every);
+    int64_t waves = 0;
+    for (const DevSolve &s : hs) waves += mm_padded(s.n) / 8;
     for (int b = 0; b < B; ++b) {
         const int n = hs[b].n;
         const bool fs = persistent_supported(n, f32, stp->path) &&
@@ -1490,11 +1505,11 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         if (stp->path >= CIL_PATH_FUSED && !fs)
             return set_error(CIL_EUNSUPPORTED, "no fused %sstepper for n = %d in %s", scheme ? "second-order " : "", n,
                              f32 ? "FP32" : "FP64");
-        if (fs && !(tiled && split_supported(n, f32))) fused_byn[n].push_back(b);
+        if (fs && !(autop && tile_by_tile(n, f32, waves, stp->check_every))) fused_byn[n].push_back(b);
         else plain_byn[n].push_back(b);
     }
     bool plain_hist = false;                         // the plain kernels keep the history in HBM
-    for (auto &kv : plain_byn) plain_hist |= !(autop && split_supported(kv.first, f32));
+    for (auto &kv : plain_byn) plain_hist |= !(autop && split_supported(kv.first));
     if (scheme && plain_hist) {
         int64_t end = 0;
         for (int b = 0; b < B; ++b) end = std::max<int64_t>(end, hs[b].off + elems[b]);
@@ -1527,14 +1542,15 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         CIL_TRY(cb.alloc((void **)&mx.state64, sizeof(double) * (size_t)end));
         CIL_TRY(cb.alloc((void **)&mx.sw, sizeof(long long) * B));
     }
-    std::vector<PlainGroup> pg;
-    if (f32) CIL_TRY(make_plain_groups<float>(c, plain_byn, hs, autop, pg));
-    else CIL_TRY(make_plain_groups<double>(c, plain_byn, hs, autop, pg));
+    std::vector<PlainGroup<float>> pg32;
+    std::vector<PlainGroup<double>> pg64;
+    if (f32) CIL_TRY(make_plain_groups<float>(c, plain_byn, hs, autop, pg32));
+    else CIL_TRY(make_plain_groups<double>(c, plain_byn, hs, autop, pg64));
     const std::function<int()> lockstep = [&]() -> int {
-        return f32 ? run_plain<float>(c, pg, dS, (float *)state, 0, c.floor_coef32, R, B)
-                   : run_plain<double>(c, pg, dS, (double *)state, 0, 0.0, R, B);
+        return f32 ? run_plain<float>(c, pg32, dS, (float *)state, 0, c.floor_coef32, R, B)
+                   : run_plain<double>(c, pg64, dS, (double *)state, 0, 0.0, R, B);
     };
-    const std::function<int()> *aside = pg.empty() ? nullptr : &lockstep;
+    const std::function<int()> *aside = plain_byn.empty() ? nullptr : &lockstep;
     if (scheme && kind == KIND_LINE) {
         if (f32) CIL_TRY(run_fused_sbdf2<float>(c, fused_byn, hs, dS, (float *)state, c.floor_coef32, dsteps, dres, dstat));
         else CIL_TRY(run_fused_sbdf2<double>(c, fused_byn, hs, dS, (double *)state, 0.0, dsteps, dres, dstat));
@@ -1601,7 +1617,7 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         for (auto &kv : pz) {
             std::map<int, std::vector<int>> one;
             one[kv.first.first] = kv.second;
-            std::vector<PlainGroup> pg;
+            std::vector<PlainGroup<double>> pg;
             CIL_TRY(make_plain_groups<double>(c, one, hs64, autop, pg));
             CIL_HIP(hipMemcpyAsync(dS64, hs64.data(), sizeof(DevSolve) * B, hipMemcpyHostToDevice, st));
             CIL_TRY(run_plain<double>(c, pg, dS64, state64, kv.first.second, 0.0, R, B));

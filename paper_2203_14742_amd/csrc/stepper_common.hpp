@@ -174,24 +174,31 @@ template <typename T>
 int launch_mm(int n, int scheme, int nl, const DevSolve *S, const int *list, T *state, const T *tab, const T *tab2,
               const T *cst, int model, double dt, const PersistArgs &pa, hipStream_t st);
 
-// The same passes as launches over many compute units (stepper_split.hip): FP64,
-// sides 65 .. 128.  One item per tile of eight lines of a solve.
-constexpr bool split_supported(int n, bool f32) { return !f32 && n > 64 && n <= 128; }
+// The same passes as launches over many compute units (stepper_split.hip), sides
+// 65 .. 128.  One item per tile of eight lines of a solve.
+constexpr bool split_supported(int n) { return n > 64 && n <= 128; }
+template <typename T>
 struct SplitItem {                       // all that a wavefront needs, read in one go
     DevSolve s;
     int32_t b, tile;                     // solve (-1: none), tile
-    const double *cst, *div, *div2;      // MmTables of the side, the divisors at the tile
-    double *work, *hist;                 // the solve's field between the passes; the tile's history (second order)
+    const T *cst, *div, *div2;           // MmTables of the side, the divisors at the tile
+    T *work, *hist;                      // the solve's field between the passes; the tile's history (second order)
 };
 enum { SPLIT_LOAD = 1, SPLIT_STORE = 2, SPLIT_CHECK = 4, SPLIT_NEXT = 8 };
+template <typename T>
 struct SplitArgs {
-    const SplitItem *items;
-    double *state;
+    const SplitItem<T> *items;
+    T *state;
+    T *c0;                               // FP32: per solve and species, the constant the transforms leave out
     StepResults res;
     int flags, first;                    // set by launch_split, as the coefficients
-    double k4, kt, k2, kc;
+    T k4, kt, k2, kc;
 };
-int launch_split(SplitArgs a, int nitems, int model, double dt, int K, bool bdf, bool from_start, hipStream_t st);
+// c0 of the solves in `list`, from their states
+int launch_split_offsets(const DevSolve *S, const int *list, int nl, const float *state, float *c0, int model,
+                         hipStream_t st);
+template <typename T>
+int launch_split(SplitArgs<T> a, int nitems, int model, double dt, int K, bool bdf, bool from_start, hipStream_t st);
 
 // FP32 steps and the polish in one launch (or two, by mode), n = 32 and 64.
 int launch_mm_mixed(int n, int nl, const DevSolve *S, const int *list, float *state, double *state64,

@@ -1,5 +1,5 @@
-// The matrix-core stepper over many compute units (FP64): a wavefront per tile
-// of eight grid lines, a launch per pass.
+// The matrix-core stepper over many compute units: a wavefront per tile of
+// eight grid lines, a launch per pass; sides 65 .. 128.
 //
 // The persistent kernel (stepper_mm.hpp) keeps a solve on one compute unit,
 // which holds an FP64 field of side 96 at most and has four matrix cores of
@@ -23,11 +23,8 @@ namespace cil {
 
 namespace {
 
-using T = double;
-using V = Vec4<T>;
-
 // f(Line) for a side of 65 .. 128
-template <typename F>
+template <typename T, typename F>
 __host__ __device__ __forceinline__ void split_dispatch(int n, F &&f)
 {
     if (n == 128) f(Line128<T>{});
@@ -35,9 +32,14 @@ __host__ __device__ __forceinline__ void split_dispatch(int n, F &&f)
     else f(LineDense<T, 3>{});
 }
 
-template <int MODEL, typename Line>
-__device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it)
+// FP32 transforms act on u - u* (steady_value); FP64 ones on u.
+template <int MODEL, typename T>
+constexpr bool kOffset = sizeof(T) == 4 && MODEL != CIL_FHN && MODEL != CIL_HEAT;
+
+template <int MODEL, typename T, typename Line>
+__device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<T> &it)
 {
+    using V = Vec4<T>;
     constexpr int N = Line::N, NS = Line::NS, ROR8 = 0x128;
     constexpr bool RAG = Line::kRagged;
     const int lane = threadIdx.x, c = lane & 15, sp = c >> 3, g4 = 4 * (lane >> 4);
@@ -55,6 +57,8 @@ __device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it
         const unsigned e = (unsigned)((sp * n + rn) * n + slot_pos<Line>(hb, g4 + i, n)) * (unsigned)sizeof(T);
         return !RAG || real(hb, i) ? e : 0xFFFFFF00u;
     };
+    T c0 = T(0);
+    if constexpr (kOffset<MODEL, T>) c0 = a.c0[2 * it.b + sp];
     V x[NS], X[NS];
     if (a.flags & SPLIT_LOAD) {
 #pragma unroll
@@ -65,6 +69,10 @@ __device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it
 #pragma unroll
         for (int hb = 0; hb < NS; ++hb) X[hb] = mm_load(row + hb * 16);
         L.inv(X, x);
+        if constexpr (kOffset<MODEL, T>) {
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb) x[hb] += V(c0);
+        }
     }
     if (a.flags & SPLIT_CHECK) {
         double d = 0.0, m = 0.0;
@@ -73,7 +81,7 @@ __device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it
         for (int hb = 0; hb < NS; ++hb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const double v = x[hb][i], dd = fabs(v - buf_load<T>(ub, at(hb, i), 0));
+                const double v = (double)x[hb][i], dd = fabs(v - (double)buf_load<T>(ub, at(hb, i), 0));
                 if (!RAG || real(hb, i)) {
                     bad |= !isfinite(v);
                     d = fmax(d, isnan(dd) ? 0.0 : dd);
@@ -93,7 +101,7 @@ __device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it
 #pragma unroll
         for (int hb = 0; hb < NS; ++hb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) buf_store<T>(x[hb][i], ub, at(hb, i), 0);
+            for (int i = 0; i < 4; ++i) buf_store<T>((T)x[hb][i], ub, at(hb, i), 0);
     }
     if (!(a.flags & SPLIT_NEXT)) return;
     OwnReaction<MODEL, T> react;
@@ -111,11 +119,11 @@ __device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const T own = x[hb][i], oth = dpp_mov<ROR8>((T)x[hb][i]);
-            const T F = react(own, oth);
+            const T F = react(own, oth), ud = own - c0;
             T q;
-            if (hist) q = fma(a.kc, fma(a.k2, F, -fh[i]), fma(a.k4, own, -uh[i]) * a.kt);
-            else q = fma(a.kc, F, own);
-            un[i] = own;
+            if (hist) q = fma(a.kc, fma(a.k2, F, -fh[i]), fma(a.k4, ud, -uh[i]) * a.kt);
+            else q = fma(a.kc, F, ud);
+            un[i] = ud;
             fn[i] = F;
             if constexpr (RAG) {                              // padding carries no value (and no NaN) on
                 if (!real(hb, i)) q = T(0);
@@ -132,9 +140,10 @@ __device__ __forceinline__ void row_pass(const SplitArgs &a, const SplitItem &it
     for (int hb = 0; hb < NS; ++hb) *reinterpret_cast<V *>(row + hb * 16) = X[hb];
 }
 
-template <typename Line>
-__device__ __forceinline__ void column_pass(const SplitArgs &a, const SplitItem &it)
+template <typename T, typename Line>
+__device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitItem<T> &it)
 {
+    using V = Vec4<T>;
     constexpr int N = Line::N, NS = Line::NS;
     const int lane = threadIdx.x, c = lane & 15, sp = c >> 3, g4 = 4 * (lane >> 4);
     Line L;
@@ -160,58 +169,94 @@ __device__ __forceinline__ void column_pass(const SplitArgs &a, const SplitItem 
 #pragma unroll
     for (int hb = 0; hb < NS; ++hb)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) buf_store<T>(x[hb][i], wb, col, (hb * 16 + i) * N * (int)sizeof(T));
+        for (int i = 0; i < 4; ++i) buf_store<T>((T)x[hb][i], wb, col, (hb * 16 + i) * N * (int)sizeof(T));
+}
+
+template <int MODEL, typename T>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_split_rows(SplitArgs<T> a)
+{
+    const SplitItem<T> it = a.items[blockIdx.x];
+    if (it.b < 0) return;
+    split_dispatch<T>(it.s.n, [&](auto line) __attribute__((always_inline)) {
+        row_pass<MODEL, T, decltype(line)>(a, it);
+    });
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_split_columns(SplitArgs<T> a)
+{
+    const SplitItem<T> it = a.items[blockIdx.x];
+    if (it.b < 0) return;
+    split_dispatch<T>(it.s.n, [&](auto line) __attribute__((always_inline)) { column_pass<T, decltype(line)>(a, it); });
 }
 
 template <int MODEL>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_split_rows(SplitArgs a)
+__global__ __launch_bounds__(256) void k_split_offsets(const DevSolve *S, const int *list, const float *state, float *c0)
 {
-    const SplitItem it = a.items[blockIdx.x];
-    if (it.b < 0) return;
-    split_dispatch(it.s.n, [&](auto line) __attribute__((always_inline)) { row_pass<MODEL, decltype(line)>(a, it); });
-}
-
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_split_columns(SplitArgs a)
-{
-    const SplitItem it = a.items[blockIdx.x];
-    if (it.b < 0) return;
-    split_dispatch(it.s.n, [&](auto line) __attribute__((always_inline)) { column_pass<decltype(line)>(a, it); });
+    __shared__ double top[2][4];
+    const int b = list[blockIdx.x];
+    const DevSolve s = S[b];
+    const int NN = s.n * s.n;
+    for (int sp = 0; sp < 2; ++sp) {
+        double m = 0.0;
+        for (int e = threadIdx.x; e < NN; e += 256) m = fmax(m, fabs((double)state[s.off + (int64_t)sp * NN + e]));
+        m = wave_max(m);
+        if ((threadIdx.x & 63) == 0) top[sp][threadIdx.x >> 6] = m;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {                                    // mm_solve's rule
+        const double *t = top[threadIdx.x], m = fmax(fmax(t[0], t[1]), fmax(t[2], t[3]));
+        const double u0 = steady_value<MODEL>(s.p, threadIdx.x);
+        c0[2 * b + threadIdx.x] = fabs(u0) <= 4.0 * m ? (float)u0 : 0.0f;
+    }
 }
 
 }  // namespace
 
+int launch_split_offsets(const DevSolve *S, const int *list, int nl, const float *state, float *c0, int model,
+                         hipStream_t st)
+{
+    dispatch_model(model, [&](auto MD) {
+        hipLaunchKernelGGL((k_split_offsets<decltype(MD)::value>), dim3(nl), dim3(256), 0, st, S, list, state, c0);
+    });
+    return check_launch("k_split_offsets");
+}
+
 // K steps of the items from the states; from_start: the first of them is the
 // second-order scheme's first, an IMEX-Euler step.
-int launch_split(SplitArgs a, int nitems, int model, double dt, int K, bool bdf, bool from_start, hipStream_t st)
+template <typename T>
+int launch_split(SplitArgs<T> a, int nitems, int model, double dt, int K, bool bdf, bool from_start, hipStream_t st)
 {
     auto rows = [&](int flags, bool first) {
-        SplitArgs r = a;
+        SplitArgs<T> r = a;
         r.flags = flags;
         r.first = first;
         if (bdf && !first) {                                  // as mm_solve's second-order steps
-            r.k4 = 4.0;
-            r.kt = 1.0 / 3.0;
-            r.k2 = 2.0;
-            r.kc = 2.0 * dt / 3.0;
+            r.k4 = T(4);
+            r.kt = T(1.0 / 3.0);
+            r.k2 = T(2);
+            r.kc = T(2.0 * dt / 3.0);
         } else {
-            r.k4 = r.kt = r.k2 = 1.0;
-            r.kc = dt;
+            r.k4 = r.kt = r.k2 = T(1);
+            r.kc = T(dt);
         }
         dispatch_model(model, [&](auto MD) {
-            hipLaunchKernelGGL((k_split_rows<decltype(MD)::value>), dim3(nitems), dim3(64), 0, st, r);
+            hipLaunchKernelGGL((k_split_rows<decltype(MD)::value, T>), dim3(nitems), dim3(64), 0, st, r);
         });
     };
     for (int k = 0; k < K; ++k) {
         const bool first = !bdf || (from_start && k == 0);
         if (k == 0) rows(SPLIT_LOAD | SPLIT_NEXT, first);
-        SplitArgs q = a;
+        SplitArgs<T> q = a;
         q.first = first;
-        hipLaunchKernelGGL(k_split_columns, dim3(nitems), dim3(64), 0, st, q);
+        hipLaunchKernelGGL((k_split_columns<T>), dim3(nitems), dim3(64), 0, st, q);
         // the state of the step before the last is what the stop rule compares with
         if (k < K - 1) rows(SPLIT_NEXT | (k == K - 2 ? SPLIT_STORE : 0), !bdf);
         else rows(SPLIT_CHECK | SPLIT_STORE, !bdf);
     }
     return check_launch("k_split");
 }
+template int launch_split<double>(SplitArgs<double>, int, int, double, int, bool, bool, hipStream_t);
+template int launch_split<float>(SplitArgs<float>, int, int, double, int, bool, bool, hipStream_t);
 
 }  // namespace cil
