@@ -314,17 +314,29 @@ __device__ __forceinline__ double dd_delta(double k, double joins)
     return (4.0 * k * k + 4.0 * k + 64.0 * (joins + 1.0)) * 0x1p-106;
 }
 
+// S += d^2 for S that starts at a power of two top >= every d^2: t = fl(S + d^2)
+// and t - S are then exact in what they keep, and what they lose is one more
+// fused operation, five in all.  After k terms with the sum s, S - top + lo is
+// within (k^2 + k) 2^-106 (top + s) of it: every rest is at most 2^-53 (top + s),
+// rounded once itself and once a term in lo.
+__device__ __forceinline__ void top_square(double &S, double &lo, double d)
+{
+    const double t = fma(d, d, S);
+    lo += fma(d, d, -(t - S));
+    S = t;
+}
+
 // Whether fl(hi + lo) = R, with the rest e, is the correctly rounded value of
-// any sum within delta R of hi + lo: no rounding boundary of R (half an ulp
-// away, except below a power of two, where the spacing halves) lies between.
-__device__ __forceinline__ bool dd_certain(double hi, double lo, double delta, double &R)
+// any sum within delta R + slack of hi + lo: no rounding boundary of R (half an
+// ulp away, except below a power of two, where the spacing halves) lies between.
+__device__ __forceinline__ bool dd_certain(double hi, double lo, double delta, double &R, double slack = 0.0)
 {
     double e;
     two_sum(hi, lo, R, e);
     int ex;
     const double frac = frexp(R, &ex);                   // R = frac 2^ex, frac in [0.5, 1)
     const double half = (e < 0.0 && frac == 0.5) ? ldexp(1.0, ex - 55) : ldexp(1.0, ex - 54);
-    return isfinite(R) && (fabs(e) + delta * R < half || R == 0.0);
+    return isfinite(R) && (fabs(e) + (delta * R + slack) < half || R == 0.0);
 }
 
 constexpr int EXP_CAP = 64;     // a non-overlapping expansion of doubles has < 40 parts
@@ -556,25 +568,76 @@ __device__ __forceinline__ void canonical_pair(const T *A, const T *B, long long
     }
 }
 
+// A power of two above every |x| of the row (infinite if one is), at least 2^-460.
+template <typename T>
+__global__ __launch_bounds__(256) void k_row_tops(const T *A, long long nA, const T *B, long long dim, double *tops,
+                                                  const int *only_if)
+{
+    __shared__ double part[4];
+    if (only_if && *only_if) return;
+    const long long i = blockIdx.x;
+    const T *row = i < nA ? A + i * dim : B + (i - nA) * dim;
+    T m = T(0);
+    auto take = [&](T x) __attribute__((always_inline)) {
+        const T v = x < T(0) ? -x : x;
+        m = v > m ? v : m;
+    };
+    constexpr int W = 16 / sizeof(T);                    // 16-byte loads from the first aligned value on
+    using V = T __attribute__((ext_vector_type(W)));
+    const long long head = min(dim, (long long)(-(intptr_t)row & 15) / (long long)sizeof(T)), body = (dim - head) / W;
+    const V *v = reinterpret_cast<const V *>(row + head);
+    for (long long k = threadIdx.x; k < head; k += 256) take(row[k]);
+    for (long long k = threadIdx.x; k < body; k += 1024) {
+        V x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[u] = v[min(k + 256 * u, body - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int w = 0; w < W; ++w) take(x[u][w]);
+    }
+    for (long long k = head + W * body + threadIdx.x; k < dim; k += 256) take(row[k]);
+    double t = (double)m;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) t = fmax(t, __shfl_xor(t, o, 64));
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        t = fmax(fmax(part[0], part[1]), fmax(part[2], part[3]));
+        int ex = 0;
+        if (isfinite(t)) (void)frexp(t, &ex);
+        tops[i] = isfinite(t) ? ldexp(1.0, t > 0.0 ? max(ex, -460) : -460) : t;
+    }
+}
+
+// A power of two >= every squared difference of two rows with these tops.
+__device__ __forceinline__ double pair_top(double a, double b)
+{
+    const double m = 2.0 * fmax(a, b);
+    return m * m;
+}
+
 // All pairs of two sets at once.  Nothing is listed, so rows can be shared: a
 // wavefront takes RW x CW pairs, its lanes along k, and reads RW + CW values for
 // RW CW terms where a wavefront per pair reads two for one; a block of four takes
-// 4 RW x CW pairs, KW such groups split k between them.  2 x 8 pairs and KW = 1 for
-// many pairs, 1 x 4 and KW = 4 for few.  Bound by FP64 issue (eleven operations a
-// term; the vector units issue in 80 % of the cycles): 62 500 pairs of d = 8192 in
-// FP32 take 247 us, 385 by a wavefront per pair (530 with the tracked sum).  The sums of a wavefront are reduced by halving: at each of log2(RW CW)
-// levels a lane hands over half of its pairs and keeps the rest, then plainly.
+// 4 RW x CW pairs, KW such groups split k between them.  2 x 8 pairs and KW = 2 for
+// many pairs, 1 x 4 and KW = 4 for few.  Bound by FP64 issue: 62 500 pairs of d =
+// 8192 in FP32 take 160 us with top_square (its power of two per pair from the
+// rows' largest entries, k_row_tops), 247 with dd_square's eleven operations a
+// term, 385 by a wavefront per pair.  The sums of a wavefront are reduced by
+// halving: at each of log2(RW CW) levels a lane hands over half of its pairs and
+// keeps the rest, then plainly.
 // With `square` the columns are one of several sets (blockIdx.z, strideB elements
 // apart) and the pairs those within the set, of which only j >= i are formed and
 // written twice, followed by those of A's rows with it (rows nB, nB + 1, ... of
 // d2).  blockIdx.x then counts the tiles that are formed, one after the other, so
 // that every XCD gets its share of them (by rows and columns the eight XCDs, which
 // take workgroups in turn, had 1 to 8 of 36 tiles each: 1430 us for 20 sets of 64
-// patterns of d = 32768 and 8 rows, 1016 so).
+// patterns of d = 32768 and 8 rows, 1016 so; 640 with top_square).
 template <typename T, int RW, int CW, int KW>
 __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) void k_canonical_grid(
-    const T *A, long long nA, const T *B, long long nB, long long dim, double *d2, int square, long long strideB,
-    const int *only_if, int force_exact, unsigned long long *nexact)
+    const T *A, const double *topA, long long nA, const T *B, const double *topB, long long nB, long long dim, double *d2,
+    int square, long long strideB, const int *only_if, int force_exact, unsigned long long *nexact)
 {
     constexpr int NP = RW * CW, TI = 4 * RW;
     static_assert(CW % TI == 0, "a block's rows lie within one column tile");
@@ -599,9 +662,11 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
             bj = (t - ntri) % nct;
         }
         B += blockIdx.z * strideB;
+        topB += blockIdx.z * nB;
         d2 += blockIdx.z * (nA + nB) * nB + (within ? 0 : nB * nB);
         if (within) {
             A = B;
+            topA = topB;
             nA = nB;
         }
     }
@@ -612,8 +677,16 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
     for (int q = 0; q < CW; ++q) rb[q] = B + min(j0 + q, nB - 1) * dim;
     double hi[NP], lo[NP];
+    auto each_top = [&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < NP; ++e) hi[e] = lo[e] = 0.0;
+        for (int r = 0; r < RW; ++r)
+#pragma unroll
+            for (int q = 0; q < CW; ++q) f(r * CW + q, pair_top(topA[min(i0 + r, nA - 1)], topB[min(j0 + q, nB - 1)]));
+    };
+    each_top([&](int e, double top) {
+        hi[e] = top;
+        lo[e] = 0.0;
+    });
     // Blocks start at different k and wrap round: rows are often a power of two
     // apart, and at one k they would all be on one L2 channel (62 500 pairs of d =
     // 8192 in FP32: 325 against 582 us).
@@ -643,11 +716,12 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
 #pragma unroll
             for (int r = 0; r < RW; ++r)
 #pragma unroll
-                for (int q = 0; q < CW; ++q) dd_square(hi[r * CW + q], lo[r * CW + q], av[r] - bv[q]);
+                for (int q = 0; q < CW; ++q) top_square(hi[r * CW + q], lo[r * CW + q], av[r] - bv[q]);
             if (!more) break;
         }
     };
     for (int lap = 0; lap < 2; ++lap) sum_range(lap ? 0u : turn, lap ? turn : (unsigned)dim);
+    each_top([&](int e, double top) { two_sum(hi[e] - top, lo[e], hi[e], lo[e]); });
     int unused = 0;
     int mine = 0;                                        // first of the pairs the lane keeps
 #pragma unroll
@@ -677,8 +751,10 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
         for (int v = 0; v < KW - 1; ++v) dd_add_t(hi[0], lo[0], part[v][wv][mine][0], part[v][wv][mine][1], unused);
     }
     double D;
-    bool certain = dd_certain(hi[0], lo[0], dd_delta((double)((dim + STR - 1) / STR), 6 + KW), D);
     const long long i = i0 + mine / CW, j = j0 + mine % CW;
+    const double k = (double)((dim + STR - 1) / STR), u2 = 2.0 * (k * k + k) * 0x1p-106;
+    bool certain = dd_certain(hi[0], lo[0], dd_delta(0.0, 6 + KW) + u2, D,
+                              u2 * (double)STR * pair_top(topA[min(i, nA - 1)], topB[min(j, nB - 1)]));
     const bool wanted = (lane & (64 / NP - 1)) == 0 && i < nA && j < nB && (!within || j >= i);
     unsigned long long redo = __ballot(wanted && (!certain || force_exact));
     while (redo) {                                       // rare: the whole wavefront sums that pair again
@@ -770,9 +846,13 @@ int launch_canonical_grid(const T *A, long long nA, const T *B, long long nB, lo
     const long long nct = (nB + CW - 1) / CW, nrt = (nA + 4 * RW - 1) / (4 * RW);
     const dim3 grid = sets ? dim3((unsigned)(CW / (4 * RW) * nct * (nct + 1) / 2 + nrt * nct), 1, (unsigned)sets)
                            : dim3((unsigned)nct, (unsigned)nrt);
+    const long long rows = nA + (sets ? sets : 1) * nB;
+    double *tops;
+    CIL_TRY(ws_get(WS_DIST_TOPS, sizeof(double) * rows, (void **)&tops));
     const ProfMark pm = prof_begin("k_canonical_grid", st);
-    hipLaunchKernelGGL((k_canonical_grid<T, RW, CW, KW>), grid, dim3(256 * KW), 0, st, A, nA, B, nB, dim, d2, sets > 0,
-                       strideB, only_if, g_force_exact, nexact);
+    hipLaunchKernelGGL((k_row_tops<T>), dim3((unsigned)rows), dim3(256), 0, st, A, nA, B, dim, tops, only_if);
+    hipLaunchKernelGGL((k_canonical_grid<T, RW, CW, KW>), grid, dim3(256 * KW), 0, st, A, (const double *)tops, nA, B,
+                       (const double *)tops + nA, nB, dim, d2, sets > 0, strideB, only_if, g_force_exact, nexact);
     prof_end(pm, st);
     return check_launch("k_canonical_grid");
 }
@@ -782,7 +862,7 @@ int run_canonical_grid(const T *A, long long nA, const T *B, long long nB, long 
 {
     const long long pairs = sets ? sets * (nA + nB / 2) * nB : nA * nB;
     if (pairs >= kGridPairs)
-        return launch_canonical_grid<T, 2, 8, 1>(A, nA, B, nB, strideB, dim, d2, sets, only_if, nexact, st);
+        return launch_canonical_grid<T, 2, 8, 2>(A, nA, B, nB, strideB, dim, d2, sets, only_if, nexact, st);
     return launch_canonical_grid<T, 1, 4, 4>(A, nA, B, nB, strideB, dim, d2, sets, only_if, nexact, st);
 }
 

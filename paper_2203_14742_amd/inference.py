@@ -32,9 +32,9 @@ from . import (CIL_EINVAL, CIL_SOLVE_NONFINITE, CilError, cil_bootstrap_features
                cil_pair_bins_adaptive, cil_simulate_patterns, cil_synthetic_costs, make_problems)
 
 # Most canonical terms (pairs times dimension) of a proposal for the batched costs.  20 proposals of 8.4e7 terms take
-# 1160 us in one call against 6240 one after the other, two of 3.4e8 take 554 against 762, two of 5.9e8 929 against 747:
-# there the Gram estimates of the separate calls, which leave few pairs to the canonical sum, win.
-_BATCHED_TERMS = 3 << 27
+# 751 us in one call against 6080 one after the other, two of 3.4e8 422 against 752, two of 5.9e8 715 against 737; one of
+# 7.9e8 486 against 475: there the Gram estimates of the separate calls, which leave few pairs to the canonical sum, win.
+_BATCHED_TERMS = 600_000_000
 
 
 class SyntheticCIL:

@@ -48,6 +48,31 @@ def test_grid_equals_list(cil, nA, nB, dim, dtype, kind):
         assert got[w] == exact(a[w // nB], b[w % nB]), w
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+def test_grid_equals_list_at_extreme_scales(cil, dtype):
+    """The rows' largest entries set the scale of the grid's sums: outliers far above the distance, nearly equal rows,
+    rows near the ends of the exponent range (whose squares underflow or overflow)."""
+    g = torch.Generator().manual_seed(11)
+    A = torch.randn(190, 300, generator=g, dtype=torch.float64)
+    B = torch.randn(180, 300, generator=g, dtype=torch.float64)
+    A[10:20, 7], B[10:20, 7] = 2.0 ** 40, 2.0 ** 40                       # equal outliers: no difference left
+    A[20:30, 8] = 2.0 ** 60
+    B[30:60] = A[30:60] + 2.0 ** -30 * torch.randn(30, 300, generator=g, dtype=torch.float64)
+    B[60:70] = A[60:70]
+    A[70], B[70], A[71] = 0.0, 0.0, 2.0 ** -120
+    span = 120 if dtype == torch.float32 else 1000
+    for k, e in enumerate((-span, -span // 2, span // 2, span)):
+        A[80 + k] *= 2.0 ** e
+        B[80 + k] = A[80 + k] * (1 + 2.0 ** -20)
+    A, B = A.to(dtype).cuda(), B.to(dtype).cuda()
+    ii = torch.arange(190, device="cuda").repeat_interleave(180)
+    jj = torch.arange(180, device="cuda").repeat(190)
+    perm = torch.randperm(ii.numel(), generator=g).cuda()
+    grid, listed = cil.cil_canonical_d2(A, B, ii, jj), cil.cil_canonical_d2(A, B, ii[perm], jj[perm])
+    assert torch.allclose(grid[perm], listed, rtol=0, atol=0, equal_nan=True)      # NaN: a sum that overflows
+    assert torch.equal(grid.reshape(190, 180)[torch.arange(60, 71), torch.arange(60, 71)], torch.zeros(11).double().cuda())
+
+
 def test_list_that_only_looks_like_the_grid(cil):
     """One swapped pair, or a column-by-column order: every entry still belongs to its own pair."""
     A = torch.arange(256, device="cuda", dtype=torch.float32)[:, None].repeat(1, 3)
