@@ -169,37 +169,53 @@ __device__ __forceinline__ void approx_pair(const ClassifyArgs &c, long long i, 
     eps = 2.0 * bound;
 }
 
-__global__ __launch_bounds__(256) void k_classify(ClassifyArgs c, long long nA, long long nB)
+// One pair per lane and turn, the pairs in order over the whole grid; a lane's
+// next pair is found by steps of (rows, columns), without a division.  At most
+// 1024 workgroups of 512: the closing atomics all go to a few addresses, and
+// with 4096 of 256 they took longer than the pass.  2048 x 2048 pairs (four partial
+// planes): first range pass 69 us, second 29, bins against 32 thresholds
+// 51 (121, 31, 98 so, and with a division per pair and every threshold compared).
+constexpr int CLS = 512;
+template <int MODE>
+__global__ __launch_bounds__(CLS) void k_classify(ClassifyArgs c, long long nA, long long nB)
 {
     __shared__ unsigned int hist[MAX_M + 1];
     __shared__ double sthr[MAX_M];
-    __shared__ unsigned long long rlo[4], rhi[4];
-    __shared__ int rbad[4];
+    __shared__ unsigned long long rlo[CLS / 64], rhi[CLS / 64];
+    __shared__ int rbad[CLS / 64];
     const int tid = threadIdx.x;
-    if (c.mode == MODE_BINS) {
-        for (int m = tid; m <= c.M; m += 256) hist[m] = 0;
-        for (int m = tid; m < c.M; m += 256) sthr[m] = c.thr[m];
+    int top = 1;                                  // the power of two above M / 2: first step of the threshold search
+    if constexpr (MODE == MODE_BINS) {
+        for (int m = tid; m <= c.M; m += CLS) hist[m] = 0;
+        for (int m = tid; m < c.M; m += CLS) sthr[m] = c.thr[m];
+        while (2 * top <= c.M) top *= 2;
         __syncthreads();
     }
     const long long n = nA * nB;
     unsigned long long lo = ~0ull, hi = 0ull;     // RANGE1: bounds over this thread's pairs
     int bad = 0;
     // grid-stride over the pairs (the grid is capped, so per-block reductions stay few)
-    for (long long e = (long long)blockIdx.x * 256 + tid; e < n; e += (long long)gridDim.x * 256) {
-        const long long i = e / nB, j = e % nB;
+    const long long stride = (long long)gridDim.x * CLS, di = stride / nB, dj = stride % nB;
+    long long e = (long long)blockIdx.x * CLS + tid, i = e / nB, j = e % nB;
+    for (; e < n; e += stride, i += di, j += dj) {
+        if (j >= nB) {
+            j -= nB;
+            ++i;
+        }
         if (c.exclude_diag && i == j && !c.reduced) continue;
         double D, eps;
         approx_pair(c, i, j, nA, nB, D, eps);
         if (c.exclude_diag && i == j) continue;     // summed for the later passes, not part of the range
         const bool finite = isfinite(D) && isfinite(eps);
-        if (c.mode == MODE_BINS) {
+        if constexpr (MODE == MODE_BINS) {
+            // the thresholds fall: bin = how many exceed D, by bisection; the
+            // nearest on either side decides whether one is too close
             int bin = 0;
-            bool amb = !finite;
-            for (int m = 0; m < c.M; ++m) {
-                const double t = sthr[m];
-                if (fabs(D - t) <= eps + c.thr_slack * t) amb = true;
-                bin += (D < t);
-            }
+            for (int w = top; w > 0; w >>= 1)
+                if (bin + w <= c.M && D < sthr[bin + w - 1]) bin += w;
+            const double above = sthr[bin > 0 ? bin - 1 : 0], below = sthr[bin < c.M ? bin : c.M - 1];
+            const bool amb = !finite || fabs(D - above) <= eps + c.thr_slack * above ||
+                             fabs(D - below) <= eps + c.thr_slack * below;
             if (amb) {
                 const unsigned long long slot = atomicAdd(c.nlist, 1ull);
                 if ((long long)slot < c.cap) c.list[slot] = make_int2((int)i, (int)j);
@@ -207,7 +223,7 @@ __global__ __launch_bounds__(256) void k_classify(ClassifyArgs c, long long nA, 
                 atomicAdd(&hist[bin], 1u);
                 if (c.bins) c.bins[i * nB + j] = (uint8_t)bin;
             }
-        } else if (c.mode == MODE_RANGE1) {
+        } else if constexpr (MODE == MODE_RANGE1) {
             // the bit patterns of non-negative doubles order as the values
             if (!finite) {
                 bad = 1;
@@ -217,7 +233,7 @@ __global__ __launch_bounds__(256) void k_classify(ClassifyArgs c, long long nA, 
                 lo = l < lo ? l : lo;
                 hi = h > hi ? h : hi;
             }
-        } else if (c.mode == MODE_RANGE2) {
+        } else if constexpr (MODE == MODE_RANGE2) {
             const double mnub = __longlong_as_double((long long)c.minmax[0]);
             const double mxlb = __longlong_as_double((long long)c.minmax[1]);
             if (D - eps <= mnub || D + eps >= mxlb) {
@@ -229,11 +245,11 @@ __global__ __launch_bounds__(256) void k_classify(ClassifyArgs c, long long nA, 
             c.dump_eps[e] = eps;
         }
     }
-    if (c.mode == MODE_BINS) {
+    if constexpr (MODE == MODE_BINS) {
         __syncthreads();
-        for (int m = tid; m <= c.M; m += 256)
+        for (int m = tid; m <= c.M; m += CLS)
             if (hist[m]) atomicAdd(&c.hist[m], (unsigned long long)hist[m]);
-    } else if (c.mode == MODE_RANGE1) {
+    } else if constexpr (MODE == MODE_RANGE1) {
         // wavefront, then workgroup, then one atomic per workgroup
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
@@ -249,14 +265,15 @@ __global__ __launch_bounds__(256) void k_classify(ClassifyArgs c, long long nA, 
         }
         __syncthreads();
         if (tid == 0) {
-            for (int w = 1; w < 4; ++w) {
+            for (int w = 1; w < CLS / 64; ++w) {
                 lo = rlo[w] < lo ? rlo[w] : lo;
                 hi = rhi[w] > hi ? rhi[w] : hi;
                 bad |= rbad[w];
             }
             if (bad) atomicOr(c.flag, 1ull);          // a non-finite distance
-            if (lo != ~0ull) atomicMin(&c.minmax[0], lo);
-            if (hi != 0ull) atomicMax(&c.minmax[1], hi);
+            // (no atomic where one before it has done as much)
+            if (lo < __hip_atomic_load(&c.minmax[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMin(&c.minmax[0], lo);
+            if (hi > __hip_atomic_load(&c.minmax[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(&c.minmax[1], hi);
         }
     }
 }
@@ -926,10 +943,12 @@ int classify(ClassifyArgs &c, long long nA, long long nB, hipStream_t st)
 {
     const long long n = nA * nB;
     if (n <= 0) return CIL_OK;
-    const long long blocks = std::min<long long>((n + 255) / 256, 4096);
+    const long long blocks = std::min<long long>((n + CLS - 1) / CLS, 1024);
     static const char *const names[] = {"k_classify_bins", "k_classify_range1", "k_classify_range2", "k_classify_dump"};
     const ProfMark pm = prof_begin(names[c.mode], st);
-    hipLaunchKernelGGL(k_classify, dim3((unsigned)blocks), dim3(256), 0, st, c, nA, nB);
+    void (*const kernels[])(ClassifyArgs, long long, long long) = {k_classify<MODE_BINS>, k_classify<MODE_RANGE1>,
+                                                                   k_classify<MODE_RANGE2>, k_classify<MODE_DUMP>};
+    hipLaunchKernelGGL(kernels[c.mode], dim3((unsigned)blocks), dim3(CLS), 0, st, c, nA, nB);
     prof_end(pm, st);
     return check_launch("k_classify");
 }
