@@ -130,7 +130,8 @@ __global__ void k_boot_finish(const unsigned long long *Ycnt, long long n, doubl
 // exact), T_t as bf16 0/1 built from the bin bytes per threshold, FP32
 // accumulation (partial sums are integers <= kA < 2^24: exact); the sum with
 // w_B is taken in integers.  A workgroup owns 32 resamples x 32 columns j;
-// wave w owns thresholds 8 w + 1 .. 8 w + 8.
+// wave w owns thresholds w + 1, w + 5, ... (up to eight: consecutive ones left
+// two of four wavefronts idle at M = 13, 17.8 against 15.9 us at 250 x 250).
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 int g_boot_mfma = 1;         // 0: always the gather kernel (cil_set_option)
@@ -243,7 +244,7 @@ __global__ __launch_bounds__(256) void k_boot_mfma(const uint8_t *bins, long lon
             const uint2 braw = *(const uint2 *)&sT[lane & 31][kofs];
 #pragma unroll
             for (int q = 0; q < BTPW; ++q) {
-                const int t = wv * BTPW + q + 1;
+                const int t = 4 * q + wv + 1;
                 if (t <= M) c[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, thermometer(braw, t), c[q], 0, 0, 0);
             }
         }
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(256) void k_boot_mfma(const uint8_t *bins, long lon
     // barrier (no code motion across it) is the only ordering needed.
 #pragma unroll
     for (int q = 0; q < BTPW; ++q) {
-        const int t = wv * BTPW + q + 1;
+        const int t = 4 * q + wv + 1;
         if (t > M) break;
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
@@ -509,7 +510,6 @@ __global__ __launch_bounds__(256) void k_loglik(const double *Y, int n, int M, c
     __shared__ double Ys[YSTAGE];
     __shared__ int keep[LMAX];
     __shared__ int nk;
-    __shared__ double z[LMAX];
     __shared__ double lgd[LMAX];
     const int p = blockIdx.x;
     const int lane = threadIdx.x;
@@ -605,35 +605,27 @@ __global__ __launch_bounds__(256) void k_loglik(const double *Y, int n, int M, c
             S[ej[t]][ei[t]] = sv;
         }
     __syncthreads();
-    // From here one wavefront works alone: its LDS accesses are performed in
-    // issue order, so a wavefront barrier (no code motion across it) orders
-    // them; the other wavefronts leave.
-    if (lane >= 64) return;
-    auto wsync = [] {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    if (lane == 0) {
-        int c = 0;
-        for (int m = 0; m < M; ++m)
-            if (S[m][m] != 0.0) keep[c++] = m;
-        nk = c;
+    if (lane < 64) {
+        const bool in = lane < M && S[lane < M ? lane : 0][lane < M ? lane : 0] != 0.0;
+        const unsigned long long kept = __ballot(in);
+        if (in) keep[__popcll(kept & ((1ull << lane) - 1))] = lane;
+        if (lane == 0) nk = __popcll(kept);
     }
-    wsync();
+    __syncthreads();
     const int K = nk;
+    auto bcast = [](double x, int src) {               // src uniform
+        const long long v = __double_as_longlong(x);
+        const int lo = __builtin_amdgcn_readlane((int)v, src);
+        const int hi = __builtin_amdgcn_readlane((int)(v >> 32), src);
+        return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+    };
     if (K <= 16) {
+        if (lane >= 64) return;                        // one wavefront works alone
         // Up to 16 kept bins: lane i holds row i of Sigma in registers and
         // reads other lanes' entries with readlane, so no step waits on the
         // LDS.  Right-looking Cholesky and solve: every entry subtracts its
         // terms in index order, the operations of the left-looking form.
         constexpr int R = 16;
-        auto bcast = [](double x, int src) {               // src is a compile-time lane after unrolling
-            const long long v = __double_as_longlong(x);
-            const int lo = __builtin_amdgcn_readlane((int)v, src);
-            const int hi = __builtin_amdgcn_readlane((int)(v >> 32), src);
-            return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-        };
         const int kl = lane < K ? keep[lane] : 0;
         double r[R];
 #pragma unroll
@@ -681,61 +673,50 @@ __global__ __launch_bounds__(256) void k_loglik(const double *Y, int n, int M, c
         }
         return;
     }
-    // compact the kept rows/columns into the leading K x K block (in place:
-    // keep[] is increasing so keep[a] >= a); lane c moves column c
-    for (int a = 0; a < K; ++a) {
-        double v = 0.0;
-        if (lane < K) v = S[keep[a]][keep[lane]];
-        wsync();
-        if (lane < K) S[a][lane] = v;
-        wsync();
-    }
-    // Cholesky, lower triangle in S; a pivot not above K 2^-52 Sigma_jj means
-    // Sigma is singular to working precision.  The dot products subtract
-    // their terms in index order; the loads run four ahead.
-    auto dot_sub = [](double s, const double *x, const double *y, int len) {
-        int k = 0;
-        for (; k + 4 <= len; k += 4) {
-            const double x0 = x[k], x1 = x[k + 1], x2 = x[k + 2], x3 = x[k + 3];
-            const double y0 = y[k], y1 = y[k + 1], y2 = y[k + 2], y3 = y[k + 3];
-            s -= x0 * y0;
-            s -= x1 * y1;
-            s -= x2 * y2;
-            s -= x3 * y3;
+    // More than 16: the four wavefronts together.  Lane i of each holds row i,
+    // wavefront q the columns q, q + 4, ... in registers.  Step j: the owner of
+    // column j divides it by the pivot and leaves it in LDS (row j of S, whose
+    // old values are all in registers), then every column takes its term of
+    // it, so that an entry subtracts its terms in index order, as above.  One
+    // barrier a step: the whole call at 60 bins and 200 rows takes 75 us where
+    // one wavefront's left-looking form, its dot products from LDS, took 152
+    // (32 bins: 39, 69).
+    constexpr int R = LMAX / 4;
+    const int i = lane & 63, q = __builtin_amdgcn_readfirstlane(lane >> 6);
+    const int ki = keep[i < K ? i : 0];
+    double r[R];
+#pragma unroll
+    for (int t = 0; t < R; ++t) r[t] = S[ki][keep[q + 4 * t < K ? q + 4 * t : 0]];
+    if (lane < K) lgd[lane] = S[ki][ki];
+    __syncthreads();
+    static_for<0, LMAX>([&](auto J) {
+        constexpr int j = decltype(J)::value;
+        if (j >= K) return;                            // uniform over the workgroup
+        if (q == (j & 3)) {
+            const double v = r[j >> 2], dgj = lgd[j], sv = bcast(v, j);
+            const double d = (sv > K * 0x1p-52 * dgj) ? sqrt(sv) : NAN;      // as above
+            S[j][i] = i == j ? d : v / d;
         }
-        for (; k < len; ++k) s -= x[k] * y[k];
-        return s;
-    };
-    int ok = 1;
-    for (int j = 0; j < K; ++j) {
-        if (lane == 0) {
-            const double diag = S[j][j];
-            const double sv = dot_sub(diag, S[j], S[j], j);
-            S[j][j] = (sv > K * 0x1p-52 * diag) ? sqrt(sv) : NAN;
-        }
-        wsync();
-        const double d = S[j][j];
-        if (!(d > 0.0)) ok = 0;
-        if (lane > j && lane < K) S[lane][j] = dot_sub(S[lane][j], S[lane], S[j], j) / d;
-        wsync();
+        __syncthreads();
+        const double lij = S[j][i];
+#pragma unroll
+        for (int t = j >> 2; t < R; ++t)
+            if (t > (j >> 2) || q > (j & 3)) r[t] -= lij * S[j][q + 4 * t];
+    });
+    if (q > 0) return;
+    const double diag_own = i < K ? S[i][i] : 1.0;
+    const int ok = __all(diag_own > 0.0);
+    const double lg_own = ok ? log(diag_own) : 0.0;
+    double rhs = i < K ? yobs[(size_t)p * M + ki] - mu[ki] : 0.0, ff = 0.0, ld = 0.0;
+    for (int k = 0; k < K; ++k) {
+        const double zk = bcast(rhs, k) / bcast(diag_own, k);
+        if (i > k) rhs -= S[k][i] * zk;
+        ff += zk * zk;
+        ld += bcast(lg_own, k);
     }
-    if (lane < K) lgd[lane] = ok ? log(S[lane][lane]) : 0.0;   // the logs in parallel, summed in order below
-    wsync();
     if (lane == 0) {
-        double ff = NAN, ll = NAN;
-        if (ok) {
-            double acc = 0.0, ld = 0.0;
-            for (int i = 0; i < K; ++i) {
-                const double sv = dot_sub(yobs[(size_t)p * M + keep[i]] - mu[keep[i]], S[i], z, i);
-                z[i] = sv / S[i][i];
-                acc += z[i] * z[i];
-                ld += lgd[i];
-            }
-            ff = acc;
-            ll = -0.5 * acc - ld - 0.5 * K * log(2.0 * M_PI);
-        }
-        f[p] = ff;
-        loglik[p] = ll;
+        f[p] = ok ? ff : NAN;
+        loglik[p] = ok ? -0.5 * ff - ld - 0.5 * K * log(2.0 * M_PI) : NAN;
         meff[p] = K;
         status[p] = ok ? CIL_OK : CIL_ENOTSPD;
     }
