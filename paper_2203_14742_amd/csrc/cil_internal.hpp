@@ -38,7 +38,7 @@ enum WsSlot {
     WS_STEP_SOLVES = 0, WS_STEP_LIST, WS_STEP_RESID, WS_STEP_TABLES, WS_STEP_WORK_A,
     WS_STEP_WORK_B, WS_STEP_STATE64, WS_STEP_LIST64, WS_STEP_DCT,
     WS_DIST_NORMS, WS_DIST_SPLIT_A, WS_DIST_SPLIT_B, WS_DIST_RECHECK, WS_DIST_COUNTS,
-    WS_DIST_MISC, WS_DIST_SAMPLE, WS_BOOT_MISC, WS_BOOT_MULT, WS_STATS_MISC, WS_FEAT_MISC, WS_FEAT_SEG,
+    WS_DIST_MISC, WS_DIST_SAMPLE, WS_BOOT_MISC, WS_BOOT_MULT, WS_STATS_MISC, WS_FEAT_MISC,
     WS_DIST_REDUCED, WS_COSTS, WS_DIST_TOPS,
     WS_NUM_SLOTS
 };
@@ -46,7 +46,7 @@ int ws_get(int slot, size_t bytes, void **ptr);
 // Pinned host buffers for the small copies between the host and the device
 // inside a call (so they run asynchronously), grow-only, one per (device,
 // slot); freed by cil_shutdown().
-enum HostSlot { HS_DIST = 0, HS_BOOT, HS_STEP, HS_COSTS, HS_NUM_SLOTS };
+enum HostSlot { HS_DIST = 0, HS_BOOT, HS_STEP, HS_COSTS, HS_FEAT, HS_NUM_SLOTS };
 int host_stage(int slot, size_t bytes, void **ptr);
 int current_device(int *dev);
 // Wait for everything issued to `st` (polls, then blocks; CIL_OPT_SYNC_SPIN_US).
@@ -181,6 +181,14 @@ __device__ __forceinline__ void buf_store(T v, __amdgpu_buffer_rsrc_t r, unsigne
                                               voff, soff, 0);
     else
         __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, soff, 0);
+}
+
+// p at a 32-bit byte offset: with a uniform p the load takes its base from
+// scalars and the offset as it is, without a 64-bit address per lane.
+template <typename T>
+__device__ __forceinline__ T at_byte(const T *p, unsigned offset)
+{
+    return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(p) + offset);
 }
 
 // ------------------------------------------------------------ static_for

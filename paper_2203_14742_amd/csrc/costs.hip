@@ -6,7 +6,7 @@
 // and the range, bins and resamples read them directly: nothing is approximated,
 // listed or re-checked.  The host forms the radii from the ranges, as for the
 // other calls, and waits once for those and once for the costs.  20 proposals of
-// 64 patterns of 128^2 take 751 us; one proposal after the other through the
+// 64 patterns of 128^2 take 690 us; one proposal after the other through the
 // pair-statistic calls, with four waits and two dozen launches each, took 6240.
 #include <hip/hip_runtime.h>
 

@@ -639,7 +639,7 @@ __device__ __forceinline__ double pair_top(double a, double b)
 // RW CW terms where a wavefront per pair reads two for one; a block of four takes
 // 4 RW x CW pairs, KW such groups split k between them.  2 x 8 pairs and KW = 2 for
 // many pairs, 1 x 4 and KW = 4 for few.  Bound by FP64 issue: 62 500 pairs of d =
-// 8192 in FP32 take 160 us with top_square (its power of two per pair from the
+// 8192 in FP32 take 140 us with top_square (its power of two per pair from the
 // rows' largest entries, k_row_tops), 247 with dd_square's eleven operations a
 // term, 385 by a wavefront per pair.  The sums of a wavefront are reduced by
 // halving: at each of log2(RW CW) levels a lane hands over half of its pairs and
@@ -650,7 +650,7 @@ __device__ __forceinline__ double pair_top(double a, double b)
 // d2).  blockIdx.x then counts the tiles that are formed, one after the other, so
 // that every XCD gets its share of them (by rows and columns the eight XCDs, which
 // take workgroups in turn, had 1 to 8 of 36 tiles each: 1430 us for 20 sets of 64
-// patterns of d = 32768 and 8 rows, 1016 so; 640 with top_square).
+// patterns of d = 32768 and 8 rows, 1016 so; 520 with top_square).
 template <typename T, int RW, int CW, int KW>
 __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) void k_canonical_grid(
     const T *A, const double *topA, long long nA, const T *B, const double *topB, long long nB, long long dim, double *d2,
@@ -663,14 +663,15 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
     // the wavefront's numbers in scalars: the rows' addresses then take no lane registers
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3),
               kw = KW > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
-    int bi = blockIdx.y, bj = blockIdx.x;
+    const unsigned nct = (unsigned)((nB + CW - 1) / CW);
+    unsigned bi = blockIdx.x / nct, bj = blockIdx.x % nct;
     bool within = false;
     if (square) {
-        constexpr int RT = CW / TI;                      // row tiles to a column tile
-        const int nct = (int)((nB + CW - 1) / CW), ntri = RT * nct * (nct + 1) / 2, t = blockIdx.x;
+        constexpr unsigned RT = CW / TI;                 // row tiles to a column tile
+        const unsigned ntri = RT * nct * (nct + 1) / 2, t = blockIdx.x;
         within = t < ntri;
         if (within) {                                    // column tile bj holds the row tiles 0 .. RT (bj + 1) - 1
-            bj = (int)((sqrtf(8.0f * (t / RT) + 1.0f) - 1.0f) * 0.5f);
+            bj = (unsigned)((sqrtf(8.0f * (t / RT) + 1.0f) - 1.0f) * 0.5f);
             while (RT * (bj + 1) * (bj + 2) / 2 <= t) ++bj;
             while (RT * bj * (bj + 1) / 2 > t) --bj;
             bi = t - RT * bj * (bj + 1) / 2;
@@ -687,6 +688,8 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
             nA = nB;
         }
     }
+    bi = __builtin_amdgcn_readfirstlane(bi);
+    bj = __builtin_amdgcn_readfirstlane(bj);
     const long long i0 = (long long)bi * TI + RW * wv, j0 = (long long)bj * CW;
     const T *ra[RW], *rb[CW];
 #pragma unroll
@@ -709,16 +712,16 @@ __global__ __launch_bounds__(256 * KW) __attribute__((amdgpu_waves_per_eu(4))) v
     // 8192 in FP32: 325 against 582 us).
     constexpr long long STR = 64LL * KW;
     const unsigned chunks = (unsigned)((dim + STR - 1) / STR);
-    const unsigned turn = (blockIdx.x * 5u + blockIdx.y * 3u + blockIdx.z) * 7u % chunks * (unsigned)STR;
+    const unsigned turn = (bj * 5u + bi * 3u + blockIdx.z) * 7u % chunks * (unsigned)STR;
     auto sum_range = [&](unsigned from, unsigned to) __attribute__((always_inline)) {
         unsigned k = from + lane + 64u * kw;
         if (k >= to) return;
         T a[RW], b[CW];                                  // read one round ahead
         auto read = [&](unsigned at) __attribute__((always_inline)) {
 #pragma unroll
-            for (int r = 0; r < RW; ++r) a[r] = ra[r][at];
+            for (int r = 0; r < RW; ++r) a[r] = at_byte(ra[r], at * (unsigned)sizeof(T));
 #pragma unroll
-            for (int q = 0; q < CW; ++q) b[q] = rb[q][at];
+            for (int q = 0; q < CW; ++q) b[q] = at_byte(rb[q], at * (unsigned)sizeof(T));
         };
         read(k);
         while (true) {
@@ -837,6 +840,7 @@ int scratch(long long cap, DistScratch *s)
 }
 
 constexpr long long kGridPairs = 32768;     // pairs from which sixteen a wavefront leave two wavefronts a SIMD
+constexpr long long kGridDim = 1ll << 29;      // rows of less than 4 GB: byte offsets of 32 bits
 
 // Launches waves for pairs co.first .. co.first + nwaves - 1 (in list mode
 // nwaves may exceed the list: the surplus waves leave at once).
@@ -862,7 +866,7 @@ int launch_canonical_grid(const T *A, long long nA, const T *B, long long nB, lo
 {
     const long long nct = (nB + CW - 1) / CW, nrt = (nA + 4 * RW - 1) / (4 * RW);
     const dim3 grid = sets ? dim3((unsigned)(CW / (4 * RW) * nct * (nct + 1) / 2 + nrt * nct), 1, (unsigned)sets)
-                           : dim3((unsigned)nct, (unsigned)nrt);
+                           : dim3((unsigned)(nct * nrt));
     const long long rows = nA + (sets ? sets : 1) * nB;
     double *tops;
     CIL_TRY(ws_get(WS_DIST_TOPS, sizeof(double) * rows, (void **)&tops));
@@ -1451,7 +1455,7 @@ int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, lon
     // A list as long as the grid of all pairs mostly is that grid, row by row:
     // the device looks, and one of the two launches leaves at once (with fewer
     // pairs the shared rows gain nothing: 4608 of d = 32768 173 against 153 us).
-    if (np == nA * nB && np >= kGridPairs && dim < (1ll << 31) && !g_force_exact) {
+    if (np == nA * nB && np >= kGridPairs && dim < kGridDim && !g_force_exact) {
         int *not_grid = (int *)(s.nlist + 2);
         hipLaunchKernelGGL(k_list_is_grid, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, ia, jb, np, nB, not_grid);
         CIL_TRY(check_launch("k_list_is_grid"));

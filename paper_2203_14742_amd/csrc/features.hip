@@ -94,68 +94,105 @@ __global__ __launch_bounds__(256) void k_augment(const T *X, int n, double h, lo
 }
 
 // ------------------------------------------------------- max-abs distances
-// One 64 x 64 tile of pairs and one K range [kb, kb + ksplit) per workgroup;
-// thread (ty, tx) owns rows ty + 16 i and columns tx + 16 j, i, j < 4.  For
-// each segment [e_{s-1}, e_s) the range meets, the tile's partial maxima go
-// to out[(i nB + j) nseg + s] by an atomic max on the bit patterns (the values
-// are non-negative doubles, whose order is that of their bits), so the
-// result is independent of the order of the K ranges; out starts at +0.
-constexpr int MT = 64, MKC = 32, MAX_SEG = 8;
+// A wavefront takes 4 x 8 pairs, its lanes along k, so that it reads twelve
+// values for thirty-two terms; a workgroup of four 16 x 8 pairs and one K range
+// [kb, kb + ksplit).  For each segment [e_{s-1}, e_s) the range meets, the
+// partial maxima go to out[(i nB + j) nseg + s] by an atomic max on the bit
+// patterns (the values are non-negative doubles, whose order is that of their
+// bits), so the result is independent of the order of the K ranges; out starts
+// at +0.  Bound by FP64 issue (a subtraction and a maximum a term) and by the L2
+// behind it: 62 500 pairs of d = 24320 in FP32, three segments, take 161 us (202 by
+// 2 x 8 pairs; 210 by 64 x 64 tiles staged in LDS in FP64).
+constexpr int MAX_SEG = 8;
+struct SegEnds {
+    long long end[MAX_SEG];
+};
+constexpr int PRW = 4, PCW = 8, PNP = PRW * PCW;         // pairs of a wavefront
+constexpr int PTI = 4 * PRW;                              // rows of a workgroup
+
+// max(m, |d|), m where d is not a number: the one instruction (fmax would first
+// quieten d, which a subtraction has done).
+__device__ __forceinline__ double max_abs(double m, double d)
+{
+    double r;
+    asm("v_max_f64 %0, %1, |%2|" : "=v"(r) : "v"(m), "v"(d));
+    return r;
+}
 
 template <typename T>
-__global__ __launch_bounds__(256) void k_pair_maxabs(const T *A, long long nA, const T *B, long long nB, long long dim,
-                                                     const long long *seg_end, int nseg, long long ksplit,
-                                                     unsigned long long *out)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_pair_maxabs(const T *A, long long nA, const T *B, long long nB, long long dim,
+                                                     SegEnds ends, int nseg, long long ksplit, unsigned long long *out)
 {
-    __shared__ double sA[MT][MKC + 1];
-    __shared__ double sB[MT][MKC + 1];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const long long i0 = (long long)blockIdx.y * MT, j0 = (long long)blockIdx.x * MT;
-    const long long kb = (long long)blockIdx.z * ksplit, ke = std::min<long long>(dim, kb + ksplit);
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned nct = (unsigned)((nB + PCW - 1) / PCW);
+    // in scalars, so that the rows' addresses take no lane registers
+    const unsigned bi = __builtin_amdgcn_readfirstlane(blockIdx.x / nct), bj = blockIdx.x - bi * nct;
+    const long long i0 = (long long)bi * PTI + PRW * wv, j0 = (long long)bj * PCW;
+    const long long kb = (long long)blockIdx.y * ksplit, ke = std::min<long long>(dim, kb + ksplit);
     long long sb = 0;
     for (int s = 0; s < nseg; ++s) {
-        const long long se = seg_end[s];
+        const long long se = ends.end[s];
         const long long lo = std::max<long long>(kb, sb), hi = std::min<long long>(ke, se);
         sb = se;
         if (lo >= hi) continue;                     // uniform: this range does not meet segment s
-        double m[4][4];
+        const T *ra[PRW], *rb[PCW];                 // rows past the end repeat the last (not stored)
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
+        for (int r = 0; r < PRW; ++r) ra[r] = A + std::min(i0 + r, nA - 1) * dim + lo;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) m[a][b] = 0.0;
-        for (long long k0 = lo; k0 < hi; k0 += MKC) {
-            __syncthreads();
-            for (int e = tid; e < MT * MKC; e += 256) {
-                const int r = e / MKC, kk = e % MKC;
-                const long long k = k0 + kk, ia = i0 + r, jb = j0 + r;
-                // positions past the range repeat its first element: |a - b|
-                // there is one of the range's own terms, so the max is unchanged
-                const long long kc = k < hi ? k : k0;
-                sA[r][kk] = ia < nA ? to64(A[ia * dim + kc]) : 0.0;
-                sB[r][kk] = jb < nB ? to64(B[jb * dim + kc]) : 0.0;
+        for (int q = 0; q < PCW; ++q) rb[q] = B + std::min(j0 + q, nB - 1) * dim + lo;
+        double m[PNP];
+#pragma unroll
+        for (int e = 0; e < PNP; ++e) m[e] = 0.0;
+        const unsigned len = (unsigned)(hi - lo);
+        // blocks start at different k and wrap round: at one k all rows, often a
+        // multiple of 1 KB apart, would be on one L2 channel
+        const unsigned turn = (bj * 5u + bi * 3u) * 7u % ((len + 63) / 64) * 64u;
+        for (int lap = 0; lap < 2; ++lap) {
+            unsigned k = (lap ? 0u : turn) + lane;
+            const unsigned to = lap ? turn : len;
+            if (k >= to) continue;
+            T a[PRW], b[PCW];                       // read one round ahead
+            auto read = [&](unsigned at) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = 0; r < PRW; ++r) a[r] = at_byte(ra[r], at * (unsigned)sizeof(T));
+#pragma unroll
+                for (int q = 0; q < PCW; ++q) b[q] = at_byte(rb[q], at * (unsigned)sizeof(T));
+            };
+            read(k);
+            while (true) {
+                double av[PRW], bv[PCW];
+#pragma unroll
+                for (int r = 0; r < PRW; ++r) av[r] = to64(a[r]);
+#pragma unroll
+                for (int q = 0; q < PCW; ++q) bv[q] = to64(b[q]);
+                k += 64;
+                const bool more = k < to;
+                read(more ? k : k - 64);
+#pragma unroll
+                for (int r = 0; r < PRW; ++r)
+#pragma unroll
+                    for (int q = 0; q < PCW; ++q) m[r * PCW + q] = max_abs(m[r * PCW + q], av[r] - bv[q]);
+                if (!more) break;
             }
-            __syncthreads();
-#pragma unroll 8
-            for (int kk = 0; kk < MKC; ++kk) {
-                double av[4], bv[4];
+        }
+        // at each level a lane hands over half of its pairs and keeps the rest
+        int mine = 0;
 #pragma unroll
-                for (int a = 0; a < 4; ++a) av[a] = sA[ty + 16 * a][kk];
+        for (int half = PNP / 2; half >= 1; half >>= 1) {
+            const int off = 64 / PNP * half;
+            const bool up = (lane & off) != 0;
+            mine += up ? half : 0;
 #pragma unroll
-                for (int b = 0; b < 4; ++b) bv[b] = sB[tx + 16 * b][kk];
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) m[a][b] = fmax(m[a][b], fabs(av[a] - bv[b]));
+            for (int e = 0; e < half; ++e) {
+                const double x = m[e], y = m[e + half];
+                m[e] = max_abs(up ? y : x, __shfl_xor(up ? x : y, off, 64));
             }
         }
 #pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const long long i = i0 + ty + 16 * a, j = j0 + tx + 16 * b;
-                if (i < nA && j < nB && m[a][b] > 0.0)
-                    atomicMax(&out[(i * nB + j) * nseg + s], (unsigned long long)__double_as_longlong(m[a][b]));
-            }
+        for (int off = 32 / PNP; off >= 1; off >>= 1) m[0] = fmax(m[0], __shfl_xor(m[0], off, 64));
+        const long long i = i0 + mine / PCW, j = j0 + mine % PCW;
+        if ((lane & (64 / PNP - 1)) == 0 && i < nA && j < nB && m[0] > 0.0)
+            atomicMax(&out[(i * nB + j) * nseg + s], (unsigned long long)__double_as_longlong(m[0]));
     }
 }
 
@@ -171,7 +208,9 @@ __global__ void k_combine(const double *D, long long n, int nseg, int mode, doub
     out[p] = v;
 }
 
-// min and max of V (as ordered bit patterns of non-negative doubles)
+// min and max of V (as ordered bit patterns of non-negative doubles, the minimum
+// as the largest complement, so both start at 0).  At most 512 workgroups: their
+// atomics all go to two addresses.
 __global__ __launch_bounds__(256) void k_value_range(const double *V, long long n, unsigned long long *mm)
 {
     __shared__ unsigned long long rlo[4], rhi[4];
@@ -197,7 +236,7 @@ __global__ __launch_bounds__(256) void k_value_range(const double *V, long long 
             lo = rlo[w] < lo ? rlo[w] : lo;
             hi = rhi[w] > hi ? rhi[w] : hi;
         }
-        atomicMin(&mm[0], lo);
+        atomicMax(&mm[0], ~lo);
         atomicMax(&mm[1], hi);
     }
 }
@@ -266,25 +305,24 @@ int pair_maxabs_impl(const void *A, long long nA, const void *B, long long nB, l
         prev = seg_end[s];
     }
     if (nA * nB == 0) return CIL_OK;
-    void *p;
-    CIL_TRY(ws_get(WS_FEAT_SEG, sizeof(long long) * MAX_SEG, &p));
-    long long *dseg = (long long *)p;
-    CIL_HIP(hipMemcpyAsync(dseg, seg_end, sizeof(long long) * nseg, hipMemcpyHostToDevice, st));
     CIL_TRY(fill_zero(D, sizeof(double) * (size_t)(nA * nB * nseg), st));
     if (dim == 0) return CIL_OK;
-    // split K so that the grid holds about 1024 workgroups
-    const long long tiles = ((nA + MT - 1) / MT) * ((nB + MT - 1) / MT), chunks = (dim + MKC - 1) / MKC;
-    const long long splits = std::max<long long>(1, std::min<long long>(chunks, (1024 + tiles - 1) / tiles));
-    const long long ks = (chunks + splits - 1) / splits * MKC;
-    dim3 grid((unsigned)((nB + MT - 1) / MT), (unsigned)((nA + MT - 1) / MT), (unsigned)((dim + ks - 1) / ks));
+    SegEnds ends{};
+    for (int s = 0; s < nseg; ++s) ends.end[s] = seg_end[s];
+    // split k so that the grid holds about 2048 workgroups, in parts of at least 256
+    const long long tiles = ((nA + PTI - 1) / PTI) * ((nB + PCW - 1) / PCW), chunks = (dim + 255) / 256;
+    const long long splits = std::max<long long>({1, std::min<long long>(chunks, (2048 + tiles - 1) / tiles),
+                                                  (dim + (1ll << 28) - 1) >> 28});
+    const long long ks = (chunks + splits - 1) / splits * 256;
+    dim3 grid((unsigned)tiles, (unsigned)((dim + ks - 1) / ks));
     unsigned long long *out = (unsigned long long *)D;
     const ProfMark pm = prof_begin("k_pair_maxabs", st);
     if (prec == CIL_FP32)
         hipLaunchKernelGGL(k_pair_maxabs<float>, grid, dim3(256), 0, st, (const float *)A, nA, (const float *)B, nB,
-                           dim, (const long long *)dseg, nseg, ks, out);
+                           dim, ends, nseg, ks, out);
     else
         hipLaunchKernelGGL(k_pair_maxabs<double>, grid, dim3(256), 0, st, (const double *)A, nA, (const double *)B, nB,
-                           dim, (const long long *)dseg, nseg, ks, out);
+                           dim, ends, nseg, ks, out);
     prof_end(pm, st);
     return check_launch("k_pair_maxabs");
 }
@@ -300,19 +338,16 @@ int value_range_impl(const double *V, long long n, double *vmin, double *vmax, h
 {
     void *p;
     CIL_TRY(ws_get(WS_FEAT_MISC, 2 * sizeof(unsigned long long), &p));
-    unsigned long long *mm = (unsigned long long *)p;
-    const unsigned long long init[2] = {~0ull, 0ull};
-    CIL_HIP(hipMemcpyAsync(mm, init, sizeof(init), hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_value_range, dim3(grid_for(n)), dim3(256), 0, st, V, n, mm);
+    unsigned long long *mm = (unsigned long long *)p, *h;
+    CIL_TRY(host_stage(HS_FEAT, 4096, (void **)&h));
+    CIL_TRY(fill_zero(mm, 2 * sizeof(unsigned long long), st));
+    hipLaunchKernelGGL(k_value_range, dim3(grid_for(n, 512)), dim3(256), 0, st, V, n, mm);
     CIL_TRY(check_launch("k_value_range"));
-    unsigned long long h[2];
-    CIL_HIP(hipMemcpyAsync(h, mm, sizeof(h), hipMemcpyDeviceToHost, st));
+    CIL_HIP(hipMemcpyAsync(h, mm, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     CIL_TRY(stream_wait(st));
-    double lo, hi;
-    std::memcpy(&lo, &h[0], 8);
-    std::memcpy(&hi, &h[1], 8);
-    *vmin = lo;
-    *vmax = hi;
+    const unsigned long long lo = ~h[0], hi = h[1];
+    std::memcpy(vmin, &lo, 8);
+    std::memcpy(vmax, &hi, 8);
     return CIL_OK;
 }
 
@@ -325,17 +360,20 @@ int bin_values_impl(const double *V, long long n, const double *radii, int M, ui
     unsigned long long *hist = (unsigned long long *)p;
     double *dr = (double *)(hist + M + 1);
     CIL_TRY(fill_zero(hist, sizeof(unsigned long long) * (M + 1), st));
-    CIL_HIP(hipMemcpyAsync(dr, radii, sizeof(double) * M, hipMemcpyHostToDevice, st));
+    char *h;
+    CIL_TRY(host_stage(HS_FEAT, 4096, (void **)&h));
+    std::memcpy(h, radii, sizeof(double) * M);
+    CIL_HIP(hipMemcpyAsync(dr, h, sizeof(double) * M, hipMemcpyHostToDevice, st));
     if (n > 0) {
-        hipLaunchKernelGGL(k_bin_values, dim3(grid_for(n)), dim3(256), 0, st, V, n, dr, M, bins, hist);
+        hipLaunchKernelGGL(k_bin_values, dim3(grid_for(n, 512)), dim3(256), 0, st, V, n, dr, M, bins, hist);
         CIL_TRY(check_launch("k_bin_values"));
     }
-    std::vector<unsigned long long> h(M + 1);
-    CIL_HIP(hipMemcpyAsync(h.data(), hist, sizeof(unsigned long long) * (M + 1), hipMemcpyDeviceToHost, st));
+    unsigned long long *hh = (unsigned long long *)(h + sizeof(double) * VMAX_M);
+    CIL_HIP(hipMemcpyAsync(hh, hist, sizeof(unsigned long long) * (M + 1), hipMemcpyDeviceToHost, st));
     CIL_TRY(stream_wait(st));
     unsigned long long tail = 0;
     for (int m = M; m >= 1; --m) {
-        tail += h[m];
+        tail += hh[m];
         counts[m - 1] = (int64_t)tail;
     }
     return CIL_OK;

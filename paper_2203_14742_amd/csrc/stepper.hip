@@ -1292,11 +1292,11 @@ template <typename T>
 int run_plain(SimCtx &c, std::vector<PlainGroup<T>> &groups, const DevSolve *dS, T *state, int64_t start,
               double floor_coef, StepResults R, int B)
 {
-    char *stage;
-    const size_t b8 = sizeof(unsigned long long) * (size_t)B, rbytes = 2 * b8 + sizeof(int) * (size_t)B;
-    CIL_TRY(host_stage(HS_STEP, rbytes, (void **)&stage));
-    const unsigned long long *h_resid = (const unsigned long long *)stage, *h_maxabs = h_resid + B;
-    const int *h_bad = (const int *)(stage + 2 * b8);
+    // the results as R holds them: residuals, maxima, flags (half a word each)
+    std::vector<unsigned long long> stage(2 * (size_t)B + (B + 1) / 2);
+    const size_t rbytes = (2 * sizeof(unsigned long long) + sizeof(int)) * (size_t)B;
+    const unsigned long long *h_resid = stage.data(), *h_maxabs = h_resid + B;
+    const int *h_bad = (const int *)(h_maxabs + B);
     int64_t step = start;
     auto any_active = [&]() {
         for (auto &g : groups)
@@ -1332,7 +1332,7 @@ int run_plain(SimCtx &c, std::vector<PlainGroup<T>> &groups, const DevSolve *dS,
             const Sbdf2Args<T> bdf{(T *)c.uh, (T *)c.fh, step};
             CIL_TRY(launch_plain<T>(g, dS, state, nl, c.model, c.dt, K, R, c.st, c.scheme ? &bdf : nullptr));
         }
-        CIL_HIP(hipMemcpyAsync(stage, R.resid, rbytes, hipMemcpyDeviceToHost, c.st));
+        CIL_HIP(hipMemcpyAsync(stage.data(), R.resid, rbytes, hipMemcpyDeviceToHost, c.st));
         CIL_TRY(stream_wait(c.st));
         step = next;
         for (auto &g : groups) {

@@ -32,8 +32,9 @@ from . import (CIL_EINVAL, CIL_SOLVE_NONFINITE, CilError, cil_bootstrap_features
                cil_pair_bins_adaptive, cil_simulate_patterns, cil_synthetic_costs, make_problems)
 
 # Most canonical terms (pairs times dimension) of a proposal for the batched costs.  20 proposals of 8.4e7 terms take
-# 751 us in one call against 6080 one after the other, two of 3.4e8 422 against 752, two of 5.9e8 715 against 737; one of
-# 7.9e8 486 against 475: there the Gram estimates of the separate calls, which leave few pairs to the canonical sum, win.
+# 690 us in one call against 6360 one after the other, two of 3.4e8 404 against 764, two of 5.9e8 687 against 743; one of
+# 7.9e8 466 against 478, one of 1.2e9 669 against 485: there the Gram estimates of the separate calls, which leave few
+# pairs to the canonical sum, win.
 _BATCHED_TERMS = 600_000_000
 
 
@@ -83,7 +84,7 @@ class SyntheticCIL:
         P = S.shape[0] // ns
         n_set, dim = self.data.shape[0], int(np.prod(S.shape[1:]))
         if (2 <= ns <= 4096 and n_set <= 4096 and 1 <= self.M <= 64 and 1 <= P <= 65535
-                and 2 <= self.n_boot == self.idx[0].shape[0] and dim < 2 ** 31
+                and 2 <= self.n_boot == self.idx[0].shape[0] and dim < 2 ** 29
                 and ns * (ns // 2 + n_set) * dim <= _BATCHED_TERMS):
             f, ll, status = cil_synthetic_costs(S, self.data, ns, self.M, *self.idx)
             self.last_degenerate = status == CIL_EINVAL
