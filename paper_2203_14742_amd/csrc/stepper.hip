@@ -614,13 +614,13 @@ FusedKind fused_kind(int path)
 
 // Whether side n has a persistent kernel on this path.  AUTO takes the matrix
 // cores for any side whose field fits the LDS (192 FP64 solves of sides 20 to
-// 96: 34 us a step against 378 for the plain path); an explicit path has the
-// sides it names.
+// 96: 34 us a step against 378 for the plain path); an explicit path, and a
+// quad-lane code shape chosen by option, have the sides they name.
 bool persistent_supported(int n, bool f32, int path)
 {
     if (path == CIL_PATH_PLAIN) return false;
     if (fused_supported(n, f32)) return true;
-    return path == CIL_PATH_AUTO && n >= 2 && n <= mm_max_side(f32);
+    return path == CIL_PATH_AUTO && g_quad_shape_option < 0 && n >= 2 && n <= mm_max_side(f32);
 }
 
 // Whether a side that has both a persistent and a tile-by-tile kernel takes the
@@ -1505,7 +1505,7 @@ int simulate_impl(cil_model model, cil_precision prec, const cil_problem *probs,
         if (stp->path >= CIL_PATH_FUSED && !fs)
             return set_error(CIL_EUNSUPPORTED, "no fused %sstepper for n = %d in %s", scheme ? "second-order " : "", n,
                              f32 ? "FP32" : "FP64");
-        if (fs && !(autop && tile_by_tile(n, f32, waves, stp->check_every))) fused_byn[n].push_back(b);
+        if (fs && !(autop && kind == KIND_MM && tile_by_tile(n, f32, waves, stp->check_every))) fused_byn[n].push_back(b);
         else plain_byn[n].push_back(b);
     }
     bool plain_hist = false;                         // the plain kernels keep the history in HBM

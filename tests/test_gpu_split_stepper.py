@@ -93,3 +93,24 @@ def test_nonfinite_solve_is_reported_alone(cil, dtype):
     for k in (0, 2, 3, 4):
         e = offs[k] + 2 * sides[k] ** 2
         assert torch.equal(st[offs[k]:e], clean[offs[k]:e])
+
+
+@pytest.mark.parametrize("scheme", ["euler", "sbdf2"])
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+def test_with_a_quad_code_shape_chosen(cil, dtype, scheme):
+    """A quad-lane code shape chosen by option is for the sides that have one; every other side still runs."""
+    sides = [50, 32, 72, 128, 100, 64]
+    ref, offs, probs = batch(cil, 0, sides, 600, dtype)
+    got = ref.clone()
+    cil.cil_simulate_patterns(0, ref, probs, MODELS[0][3], 20, check_every=10, path=cil.CIL_PATH_PLAIN, polish=0,
+                              offsets=offs, scheme=scheme)
+    cil.cil_set_option(cil.CIL_OPT_QUAD_SHAPE, 1)
+    try:
+        rep = cil.cil_simulate_patterns(0, got, probs, MODELS[0][3], 20, check_every=10, polish=0, offsets=offs,
+                                        scheme=scheme)
+    finally:
+        cil.cil_set_option(cil.CIL_OPT_QUAD_SHAPE, -1)
+    assert np.all(rep["status"] == 0)
+    for n, o in zip(sides, offs):
+        a, b = got[o:o + 2 * n * n].double(), ref[o:o + 2 * n * n].double()
+        assert float((a - b).abs().max()) <= BARS[dtype] * float(b.abs().max()), n
