@@ -85,9 +85,10 @@ typedef struct {
 } cil_problem;
 
 typedef enum {
-    CIL_PATH_AUTO = 0,        /* fused LDS-resident stepper where supported, else plain */
+    CIL_PATH_AUTO = 0,        /* on the matrix cores for n <= 128 (one persistent workgroup
+                                 per solve, or tile by tile over the chip), else plain */
     CIL_PATH_PLAIN = 1,       /* one kernel per stage, host-driven step loop           */
-    CIL_PATH_FUSED = 2,       /* fused stepper (default variant); CIL_EUNSUPPORTED
+    CIL_PATH_FUSED = 2,       /* persistent stepper (matrix cores); CIL_EUNSUPPORTED
                                  where not available (n not in {32, 64, 128}; FP64 n = 128) */
     CIL_PATH_FUSED_LINE = 3,  /* fused, one lane transforms a whole grid line        */
     CIL_PATH_FUSED_QUAD = 4   /* fused, a quad of lanes transforms a grid line       */
@@ -100,7 +101,7 @@ typedef enum {
  * the FP32 floor fp32_floor_ulps * 2^-24 * max|u| / dt (the state can no
  * longer resolve the residual) and tol is below that floor, polish != 0
  * continues the solve on the GPU until tol is met, the result rounded back to
- * FP32 (on the fused quad-lane path at n = 32 and 64 inside the same
+ * FP32 (on the matrix-core and quad-lane paths at n = 32 and 64 inside the same
  * persistent launch, see CIL_OPT_POLISH_SEPARATE):
  *   CIL_POLISH_FP64 (1): FP64 steps;
  *   CIL_POLISH_REFINE (2): the same steps in the refinement form u = U + v,
@@ -108,8 +109,8 @@ typedef enum {
  *     against the FP64 residual of U (five-point stencil) and the exact
  *     change of the reaction terms, so FP32 rounding scales with the size of
  *     v and the iteration has no FP32 floor; U absorbs v every 200 steps or
- *     so.  On the fused quad-lane path at n = 32 and 64 (default shapes);
- *     elsewhere as CIL_POLISH_FP64.  The stop rule and its FP64 residual are
+ *     so.  On the matrix-core and quad-lane paths at n = 32 and 64 (default
+ *     shapes); elsewhere as CIL_POLISH_FP64.  The stop rule and its FP64 residual are
  *     those above.
  * polish == 0 stops the solve at its floor with status CIL_SOLVE_FP32_FLOOR.
  * Other values: CIL_EINVAL. */
@@ -202,8 +203,8 @@ int cil_simulate_patterns_sbdf2(cil_model model, cil_precision prec, const cil_p
  *     FP32_FLOOR), else CIL_EINVAL.  Allocates; synchronises `hip_stream`.
  *     *plan receives an owned handle (free with cil_sim_plan_destroy).
  *   cil_sim_plan_tune: the autotuner.  For each grid side, times every code
- *     shape of the quad-lane stepper (the 4 values of CIL_OPT_QUAD_SHAPE) on
- *     that side's solves alone from a device copy of the bound state (which it
+ *     shape of the quad-lane stepper (the 4 values of CIL_OPT_QUAD_SHAPE) and the
+ *     matrix-core kernel (an untuned plan's) on that side's solves alone from a device copy of the bound state (which it
  *     leaves unchanged): `steps` > 0 fixed steps per trial (no stop rule), or
  *     with steps = 0 the plan's own stepping (stop rule and max_steps, so the
  *     trial time is the side's real completion time).  Keeps the fastest shape
@@ -446,8 +447,10 @@ int cil_synthetic_costs(const void *S, int32_t P, int64_t n_syn, const void *dat
  *   the exact (slow) summation instead of the certified double-double one;
  *   for testing that path.
  * CIL_OPT_QUAD_SHAPE (value -1..3): code shape of the fused quad-lane stepper,
- *   -1 = chosen by grid side and precision (default: 1 for n = 32, else 2
- *   in FP32 and 0 in FP64); 0 = both species of a grid line in
+ *   -1 = none (default: paths AUTO and FUSED run on the matrix cores, path
+ *   FUSED_QUAD with shape 1 for n = 32, else 2 in FP32 and 0 in FP64); any
+ *   other value makes AUTO and FUSED take the quad-lane stepper at the sides
+ *   it has: 0 = both species of a grid line in
  *   one lane, 4n threads per solve; 1 = one species per lane, 8n threads;
  *   2, 3 = shapes 0, 1 with the column-pass divisor applied in the split
  *   step's complex form (fewer operations, a larger table).  Every shape
@@ -475,7 +478,7 @@ int cil_synthetic_costs(const void *S, int32_t P, int64_t n_syn, const void *dat
  *   are unchanged (priority changes timing only).  CIL_EINVAL for 1 or
  *   values outside the range.
  * CIL_OPT_POLISH_SEPARATE (value 0/1): FP32 solves with polish != 0 on the
- *   fused quad-lane path at n = 32 or 64 (default shapes) continue from their
+ *   matrix-core and quad-lane paths at n = 32 or 64 (default shapes) continue from their
  *   FP32 floor inside the same persistent launch (0, default); 1 = the same
  *   kernel runs twice, the FP32 phase of the whole batch, then the polish of
  *   the solves at their floor.  Both give identical results.  (Other sides
