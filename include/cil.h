@@ -436,7 +436,7 @@ int cil_statistic_adaptive(const void *setA, int64_t nA, const void *setB, int64
  *   checked on the device (CIL_EINVAL).  f, loglik, status host[P]: status
  *   CIL_OK, CIL_ENOTSPD or, for distances without a range, CIL_EINVAL (f =
  *   loglik = NaN for either).  CIL_ENONFINITE for a non-finite distance within
- *   a set.  2 <= n_syn <= 4096, M <= 64, n_boot >= 2.  Synchronises. */
+ *   a set.  dim >= 1, 2 <= n_syn <= 4096, M <= 64, n_boot >= 2.  Synchronises. */
 int cil_synthetic_costs(const void *S, int32_t P, int64_t n_syn, const void *data, int64_t n_set, int64_t dim,
                         cil_precision prec, int32_t M, int32_t law, const int32_t *idx1, int32_t k1,
                         const int32_t *idx2, int32_t k2, const int32_t *subset, int32_t ks, int32_t n_boot, double *f,

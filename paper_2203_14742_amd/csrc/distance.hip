@@ -1455,7 +1455,8 @@ int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, lon
     // A list as long as the grid of all pairs mostly is that grid, row by row:
     // the device looks, and one of the two launches leaves at once (with fewer
     // pairs the shared rows gain nothing: 4608 of d = 32768 173 against 153 us).
-    if (np == nA * nB && np >= kGridPairs && dim < kGridDim && !g_force_exact) {
+    // (The grid kernel reads at least one value of a row.)
+    if (np == nA * nB && np >= kGridPairs && dim > 0 && dim < kGridDim && !g_force_exact) {
         int *not_grid = (int *)(s.nlist + 2);
         hipLaunchKernelGGL(k_list_is_grid, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, ia, jb, np, nB, not_grid);
         CIL_TRY(check_launch("k_list_is_grid"));

@@ -1,0 +1,27 @@
+"""Argument checks of cil_synthetic_costs, made before any device work (no GPU needed)."""
+import ctypes
+
+import numpy as np
+import pytest
+
+import paper_2203_14742_amd as cil
+
+GOOD = dict(P=2, n_syn=8, n_set=2, dim=16, prec=cil.CIL_FP32, M=5, law=0, k1=2, k2=6, ks=6, n_boot=10)
+
+
+def call(**change):
+    a = {**GOOD, **change}
+    out = np.zeros(64)
+    p, o = ctypes.c_void_p(4096), ctypes.c_void_p(out.ctypes.data)      # p: never read before the device check
+    return cil.lib().cil_synthetic_costs(p, a["P"], a["n_syn"], p, a["n_set"], a["dim"], a["prec"], a["M"], a["law"], p,
+                                         a["k1"], p, a["k2"], p, a["ks"], a["n_boot"], o, o, o, None)
+
+
+@pytest.mark.parametrize("change", [dict(dim=0), dict(dim=-1), dict(n_syn=1), dict(n_set=0), dict(k1=0), dict(n_boot=1),
+                                    dict(M=0), dict(M=65), dict(law=2), dict(P=-1)])
+def test_refused_before_the_device(change):
+    assert call(**change) == cil.CIL_EINVAL
+
+
+def test_no_proposals():
+    assert call(P=0) == cil.CIL_OK
