@@ -875,7 +875,9 @@ int cil_synthetic_costs(const void *S, int32_t P, int64_t n_syn, const void *dat
     CIL_TRY(check_sets(S, n_syn, data, n_set, dim, prec));
     if (dim < 1 || n_syn < 2 || n_set < 1 || k1 < 1 || k2 < 1 || ks < 1 || n_boot < 2)
         return set_error(CIL_EINVAL, "need n_syn >= 2, dim, n_set, k1, k2, ks >= 1 and n_boot >= 2");
-    if (n_syn > 4096 || n_set > 4096 || (int64_t)k1 * k2 > INT32_MAX || (int64_t)n_set * ks > INT32_MAX ||
+    // a resample's pairs are walked 64 at a time by 32-bit positions
+    constexpr int64_t most = INT32_MAX - 63;
+    if (n_syn > 4096 || n_set > 4096 || (int64_t)k1 * k2 > most || (int64_t)n_set * ks > most ||
         dim >= ((int64_t)1 << 29))
         return set_error(CIL_EINVAL, "sizes out of range");
     if (M < 1 || M > 64) return set_error(CIL_EINVAL, "M must be in [1, 64]");

@@ -25,3 +25,10 @@ def test_refused_before_the_device(change):
 
 def test_no_proposals():
     assert call(P=0) == cil.CIL_OK
+
+
+@pytest.mark.parametrize("change", [dict(k1=2 ** 31 - 1, k2=1), dict(k1=1, k2=2 ** 31 - 20), dict(ks=2 ** 31 - 1, n_set=1),
+                                    dict(k1=65536, k2=65536), dict(dim=2 ** 29), dict(n_syn=4097)])
+def test_sizes_beyond_the_positions_of_the_walk(change):
+    """Pairs of a resample are walked 64 at a time by 32-bit positions: the last round must not pass 2^31."""
+    assert call(**change) == cil.CIL_EINVAL
