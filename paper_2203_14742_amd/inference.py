@@ -72,6 +72,16 @@ class SyntheticCIL:
         self.last_nonfinite = (rep["status"] == CIL_SOLVE_NONFINITE).reshape(P, ns).any(axis=1)
         return st.reshape(P * ns, 2 * self.n * self.n)
 
+    def _batched(self, P: int, dim: int) -> bool:
+        """Whether P proposals of patterns with `dim` values take the one-call costs: the sizes that call accepts (lists
+        of at most 4096, so that every resample's pairs fit its 32-bit positions) and, per proposal, few enough terms.
+        Any other sizes go through the separate calls, with their own limits."""
+        ns, n_set = self.n_syn, self.data.shape[0]
+        lists = [n_set] + [x.shape[1] for x in self.idx]
+        return (2 <= ns <= 4096 and 1 <= min(lists) and max(lists) <= 4096 and 1 <= self.M <= 64 and 1 <= P <= 65535
+                and 2 <= self.n_boot == self.idx[0].shape[0] == self.idx[1].shape[0] and 1 <= dim < 2 ** 29
+                and ns * (ns // 2 + n_set) * dim <= _BATCHED_TERMS)
+
     def costs_from_patterns(self, S):
         """f(theta) per proposal and the log-likelihoods, from the synthetic
         patterns S [P n_syn, 2 n^2] (proposal-major).  np.inf and -np.inf
@@ -82,10 +92,7 @@ class SyntheticCIL:
         import torch
         ns = self.n_syn
         P = S.shape[0] // ns
-        n_set, dim = self.data.shape[0], int(np.prod(S.shape[1:]))
-        if (2 <= ns <= 4096 and n_set <= 4096 and 1 <= self.M <= 64 and 1 <= P <= 65535
-                and 2 <= self.n_boot == self.idx[0].shape[0] and dim < 2 ** 29
-                and ns * (ns // 2 + n_set) * dim <= _BATCHED_TERMS):
+        if self._batched(P, int(np.prod(S.shape[1:]))):
             f, ll, status = cil_synthetic_costs(S, self.data, ns, self.M, *self.idx)
             self.last_degenerate = status == CIL_EINVAL
             return np.where(status == 0, f, np.inf), np.where(status == 0, ll, -np.inf)

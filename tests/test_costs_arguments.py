@@ -32,3 +32,37 @@ def test_no_proposals():
 def test_sizes_beyond_the_positions_of_the_walk(change):
     """Pairs of a resample are walked 64 at a time by 32-bit positions: the last round must not pass 2^31."""
     assert call(**change) == cil.CIL_EINVAL
+
+
+class Taken(Exception):
+    pass
+
+
+def route(monkeypatch, n_syn, n_set, k1, k2, ks, P=1, dim=8, n_boot=2, n_boot2=None):
+    """True if SyntheticCIL takes the one-call costs for these sizes, False for the separate calls."""
+    torch = pytest.importorskip("torch")
+    import paper_2203_14742_amd.inference as inf
+
+    def taken(*a, **k):
+        raise Taken
+
+    def separate(*a, **k):
+        raise cil.CilError(cil.CIL_EINVAL, "no range")
+    monkeypatch.setattr(inf, "cil_synthetic_costs", taken)
+    monkeypatch.setattr(inf, "cil_pair_bins_adaptive", separate)
+    lists = (np.zeros((n_boot, k1), np.int32), np.zeros((n_boot2 or n_boot, k2), np.int32), np.zeros(ks, np.int32))
+    ev = inf.SyntheticCIL(0, 2, 1.0, (0.1, 0.1), lambda t: (1.0, 1.0, 1.0), torch.zeros(n_set, dim), n_syn, n_boot, 3,
+                          0.1, 1, np.zeros((1, 2, 2, 2)), lists)
+    try:
+        f, ll = ev.costs_from_patterns(torch.zeros(P * n_syn, dim))
+    except Taken:
+        return True
+    assert np.all(f == np.inf) and np.all(ll == -np.inf) and ev.last_degenerate.all()
+    return False
+
+
+def test_sizes_the_one_call_costs_refuse_take_the_separate_calls(monkeypatch):
+    assert route(monkeypatch, 64, 8, 8, 56, 56)
+    for sizes in (dict(k1=65536, k2=65536), dict(k1=5000), dict(k2=5000), dict(ks=5000), dict(k1=0), dict(ks=0),
+                  dict(dim=0), dict(n_set=0), dict(n_set=4097), dict(n_boot2=3)):
+        assert not route(monkeypatch, **{**dict(n_syn=64, n_set=8, k1=8, k2=56, ks=56), **sizes}), sizes
