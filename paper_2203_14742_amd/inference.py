@@ -37,6 +37,13 @@ from . import (CIL_EINVAL, CIL_SOLVE_NONFINITE, CilError, cil_bootstrap_features
 # pairs to the canonical sum, win.
 _BATCHED_TERMS = 600_000_000
 
+# Most microseconds per proposal that the batched costs may spend where one proposal does not fill the chip: the range
+# of a proposal's pairs by one workgroup (256 pairs in 0.3 us) and a resample's pairs by one wavefront (64 in 0.95 us),
+# for all proposals at a time; each proposal saves 250 us of waits and launches.  Patterns of 16^2, one call / separate
+# calls: one proposal of 300 patterns, 20 observed 330 / 410, 150 observed 565 / 419; of 600 734 / 452; two of 300, 150
+# observed 587 / 708, of 600 828 / 749; four of 600 928 / 1370, of 1000 2109 / 1695; twenty of 1000 4516 / 7755.
+_BATCHED_WALK_US = 250
+
 
 class SyntheticCIL:
     def __init__(self, model: int, n: int, L: float, nu, params_of_theta, data, n_syn: int, n_boot: int, M: int,
@@ -74,13 +81,15 @@ class SyntheticCIL:
 
     def _batched(self, P: int, dim: int) -> bool:
         """Whether P proposals of patterns with `dim` values take the one-call costs: the sizes that call accepts (lists
-        of at most 4096, so that every resample's pairs fit its 32-bit positions) and, per proposal, few enough terms.
-        Any other sizes go through the separate calls, with their own limits."""
+        of at most 4096, so that every resample's pairs fit its 32-bit positions) and, per proposal, few enough terms
+        and pairs.  Any other sizes go through the separate calls, with their own limits."""
         ns, n_set = self.n_syn, self.data.shape[0]
         lists = [n_set] + [x.shape[1] for x in self.idx]
+        k1, k2, ks = lists[1:]
+        walk = 0.3 * (ns * ns / 256) + 0.95 * (max(k1 * k2, n_set * ks) / 64)
         return (2 <= ns <= 4096 and 1 <= min(lists) and max(lists) <= 4096 and 1 <= self.M <= 64 and 1 <= P <= 65535
                 and 2 <= self.n_boot == self.idx[0].shape[0] == self.idx[1].shape[0] and 1 <= dim < 2 ** 29
-                and ns * (ns // 2 + n_set) * dim <= _BATCHED_TERMS)
+                and ns * (ns // 2 + n_set) * dim <= _BATCHED_TERMS and walk <= _BATCHED_WALK_US * P)
 
     def costs_from_patterns(self, S):
         """f(theta) per proposal and the log-likelihoods, from the synthetic

@@ -66,3 +66,12 @@ def test_sizes_the_one_call_costs_refuse_take_the_separate_calls(monkeypatch):
     for sizes in (dict(k1=65536, k2=65536), dict(k1=5000), dict(k2=5000), dict(ks=5000), dict(k1=0), dict(ks=0),
                   dict(dim=0), dict(n_set=0), dict(n_set=4097), dict(n_boot2=3)):
         assert not route(monkeypatch, **{**dict(n_syn=64, n_set=8, k1=8, k2=56, ks=56), **sizes}), sizes
+
+
+@pytest.mark.parametrize("n_syn,n_set,P,batched", [
+    (64, 8, 1, True), (300, 20, 1, True), (300, 150, 1, False), (600, 20, 1, False), (300, 150, 2, True), (600, 20, 2, False),
+    (600, 20, 4, True), (1000, 20, 4, False), (1000, 20, 20, True)])
+def test_many_short_patterns_take_the_faster_calls(monkeypatch, n_syn, n_set, P, batched):
+    """One workgroup ranges a proposal's pairs and one wavefront walks a resample: many pairs of few proposals leave the
+    chip idle there, and the separate calls are faster (sides as measured)."""
+    assert route(monkeypatch, n_syn, n_set, n_set, n_syn - n_set, n_syn - n_set, P=P) == batched
