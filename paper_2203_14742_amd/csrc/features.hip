@@ -209,8 +209,7 @@ __global__ void k_combine(const double *D, long long n, int nseg, int mode, doub
 }
 
 // min and max of V (as ordered bit patterns of non-negative doubles, the minimum
-// as the largest complement, so both start at 0).  At most 512 workgroups: their
-// atomics all go to two addresses.
+// as the largest complement, so both start at 0).
 __global__ __launch_bounds__(256) void k_value_range(const double *V, long long n, unsigned long long *mm)
 {
     __shared__ unsigned long long rlo[4], rhi[4];
@@ -263,9 +262,22 @@ __global__ __launch_bounds__(256) void k_bin_values(const double *V, long long n
         if (h[m]) atomicAdd(&hist[m], (unsigned long long)h[m]);
 }
 
-unsigned grid_for(long long n, long long cap = 4096)
+unsigned grid_for(long long n, long long cap)
 {
     return (unsigned)std::max<long long>(1, std::min<long long>(cap, (n + 255) / 256));
+}
+
+// Workgroups of the passes over n values.  Their closing atomics all go to a few
+// addresses (22 ns a workgroup for the range, 25 for ten bins), so few values take
+// few workgroups; many need more in flight.  us at 512 / 1024 / 2048 / 4096:
+//   range         1e6 32 / 44 / 67 / 109, 1e7 52 / 55 / 76 / 118, 3e7 94 / 79 / 95 / 130, 1e8 368 / 234 / 188 / 216
+//   bins, M = 10  1e6 42 / 45 / 56 / 125, 4e6 67 / 59 / 63 / 142, 1e7 117 / 87 / 82 / 162, 1e8 1007 / 606 / 503 / 480
+//   bins, M = 255 3e5 94 / 73 / 77 / 76, 1e6 202 / 161 / 145 / 154, 2e6 358 / 260 / 233 / 225, 1e8 16435 / .. / 9427
+unsigned range_grid(long long n) { return grid_for(n, n <= 10000000 ? 512 : n <= 60000000 ? 1024 : 2048); }
+unsigned bins_grid(long long n, int M)
+{
+    const double q = (double)n * (M + 10);               // the threshold search grows with M
+    return grid_for(n, q < 4e7 ? 512 : q < 1.3e8 ? 1024 : q < 5e8 ? 2048 : 4096);
 }
 
 }  // namespace
@@ -341,7 +353,7 @@ int value_range_impl(const double *V, long long n, double *vmin, double *vmax, h
     unsigned long long *mm = (unsigned long long *)p, *h;
     CIL_TRY(host_stage(HS_FEAT, 4096, (void **)&h));
     CIL_TRY(fill_zero(mm, 2 * sizeof(unsigned long long), st));
-    hipLaunchKernelGGL(k_value_range, dim3(grid_for(n, 512)), dim3(256), 0, st, V, n, mm);
+    hipLaunchKernelGGL(k_value_range, dim3(range_grid(n)), dim3(256), 0, st, V, n, mm);
     CIL_TRY(check_launch("k_value_range"));
     CIL_HIP(hipMemcpyAsync(h, mm, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     CIL_TRY(stream_wait(st));
@@ -365,7 +377,7 @@ int bin_values_impl(const double *V, long long n, const double *radii, int M, ui
     std::memcpy(h, radii, sizeof(double) * M);
     CIL_HIP(hipMemcpyAsync(dr, h, sizeof(double) * M, hipMemcpyHostToDevice, st));
     if (n > 0) {
-        hipLaunchKernelGGL(k_bin_values, dim3(grid_for(n, 512)), dim3(256), 0, st, V, n, dr, M, bins, hist);
+        hipLaunchKernelGGL(k_bin_values, dim3(bins_grid(n, M)), dim3(256), 0, st, V, n, dr, M, bins, hist);
         CIL_TRY(check_launch("k_bin_values"));
     }
     unsigned long long *hh = (unsigned long long *)(h + sizeof(double) * VMAX_M);
