@@ -842,6 +842,20 @@ int scratch(long long cap, DistScratch *s)
 constexpr long long kGridPairs = 32768;     // pairs from which sixteen a wavefront leave two wavefronts a SIMD
 constexpr long long kGridDim = 1ll << 29;      // rows of less than 4 GB: byte offsets of 32 bits
 
+// Whether all nA nB pairs gain by shared rows: the tiles of 8 x 8 pairs must not
+// be mostly padding, and the rows long enough for the sums to outweigh the rows'
+// tops and two launches.  us, shared rows / wavefront per pair, FP32: 40000 x 1
+// of d = 512 170 / 79; 20000 x 2 of 512 108 / 78, of 4096 282 / 221; 10000 x 4 of
+// 2 71 / 59, of 64 64 / 59, of 512 75 / 76, of 4096 154 / 212; 7000 x 7 of 2 67 / 62,
+// of 64 60 / 63; 256 x 256 of 2 70 / 70, of 64 58 / 71, of 4096 118 / 311.
+// (k_row_tops takes a workgroup of 256 per row, of at most 2^32 threads.)
+bool grid_gains(long long nA, long long nB, long long dim)
+{
+    const long long np = nA * nB, padded = (nA + 7) / 8 * 8 * ((nB + 7) / 8 * 8);
+    return np >= kGridPairs && padded <= 2 * np && dim >= (padded <= np + np / 4 ? 32 : 512) && dim < kGridDim &&
+           nA + nB < 1ll << 24;
+}
+
 // Launches waves for pairs co.first .. co.first + nwaves - 1 (in list mode
 // nwaves may exceed the list: the surplus waves leave at once).
 template <typename T>
@@ -1456,7 +1470,7 @@ int canonical_pairs_impl(const T *A, long long nA, const T *B, long long nB, lon
     // the device looks, and one of the two launches leaves at once (with fewer
     // pairs the shared rows gain nothing: 4608 of d = 32768 173 against 153 us).
     // (The grid kernel reads at least one value of a row.)
-    if (np == nA * nB && np >= kGridPairs && dim > 0 && dim < kGridDim && !g_force_exact) {
+    if (np == nA * nB && dim > 0 && grid_gains(nA, nB, dim) && !g_force_exact) {
         int *not_grid = (int *)(s.nlist + 2);
         hipLaunchKernelGGL(k_list_is_grid, dim3((unsigned)((np + 255) / 256)), dim3(256), 0, st, ia, jb, np, nB, not_grid);
         CIL_TRY(check_launch("k_list_is_grid"));

@@ -30,3 +30,22 @@ def test_patterns_of_dimension_zero_are_at_distance_zero(cil, prec):
     p = [ctypes.c_void_p(t.data_ptr()) for t in (sets, ia, jb, d2)]
     assert cil.lib().cil_canonical_d2(p[0], nA, p[0], nB, 0, prec, p[1], p[2], nA * nB, p[3], None) == cil.CIL_OK
     assert torch.equal(d2, torch.zeros_like(d2))
+
+
+@pytest.mark.parametrize("nA,nB,dim,shared", [
+    (40000, 1, 512, False), (1, 40000, 64, False), (2, 20000, 4096, False), (13000, 3, 600, False), (10000, 4, 64, False),
+    (4, 10000, 512, True), (7000, 7, 31, False), (7, 7000, 32, True), (256, 256, 2, False), (256, 256, 64, True),
+    (181, 181, 64, False), (182, 181, 64, True)])
+def test_tiles_that_are_mostly_padding_take_a_wavefront_per_pair(cil, nA, nB, dim, shared):
+    """Either way the same doubles as for a list in another order."""
+    g = torch.Generator(device="cuda").manual_seed(nA + dim)
+    A, B = (torch.randn(n, dim, device="cuda", generator=g) for n in (nA, nB))
+    ia, jb = grid(nA, nB)
+    cil.cil_profile(True)
+    try:
+        got = cil.cil_canonical_d2(A, B, ia, jb)
+        assert ("k_canonical_grid" in cil.cil_profile_names()) == shared
+    finally:
+        cil.cil_profile(False)
+    perm = torch.randperm(nA * nB, device="cuda", generator=g)
+    assert torch.equal(got[perm], cil.cil_canonical_d2(A, B, ia[perm], jb[perm]))
