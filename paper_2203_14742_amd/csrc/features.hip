@@ -196,6 +196,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     }
 }
 
+// The same by tiles of 64 x 64 pairs staged through LDS in FP64, 32 values of k at
+// a time; thread (ty, tx) owns rows ty + 16 i and columns tx + 16 j, i, j < 4.
+// Reads each row once per 64 others and ends a segment with one atomic a pair, so
+// it wins where rows are FP64 (the reads through L2 bound k_pair_maxabs there) and
+// where segments are short (k_pair_maxabs reduces over its lanes at each end).
+constexpr int MT = 64, MKC = 32;
+template <typename T>
+__global__ __launch_bounds__(256) void k_pair_maxabs_tiles(const T *A, long long nA, const T *B, long long nB,
+                                                           long long dim, SegEnds ends, int nseg, long long ksplit,
+                                                           unsigned long long *out)
+{
+    __shared__ double sA[MT][MKC + 1];
+    __shared__ double sB[MT][MKC + 1];
+    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const unsigned nct = (unsigned)((nB + MT - 1) / MT);
+    const long long i0 = (long long)(blockIdx.x / nct) * MT, j0 = (long long)(blockIdx.x % nct) * MT;
+    const long long kb = (long long)blockIdx.y * ksplit, ke = std::min<long long>(dim, kb + ksplit);
+    long long sb = 0;
+    for (int s = 0; s < nseg; ++s) {
+        const long long se = ends.end[s];
+        const long long lo = std::max<long long>(kb, sb), hi = std::min<long long>(ke, se);
+        sb = se;
+        if (lo >= hi) continue;                     // uniform: this range does not meet segment s
+        double m[4][4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) m[a][b] = 0.0;
+        for (long long k0 = lo; k0 < hi; k0 += MKC) {
+            __syncthreads();
+            for (int e = tid; e < MT * MKC; e += 256) {
+                const int r = e / MKC, kk = e % MKC;
+                const long long k = k0 + kk, ia = i0 + r, jb = j0 + r;
+                // positions past the range repeat its first element: |a - b|
+                // there is one of the range's own terms, so the max is unchanged
+                const long long kc = k < hi ? k : k0;
+                sA[r][kk] = ia < nA ? to64(A[ia * dim + kc]) : 0.0;
+                sB[r][kk] = jb < nB ? to64(B[jb * dim + kc]) : 0.0;
+            }
+            __syncthreads();
+#pragma unroll 8
+            for (int kk = 0; kk < MKC; ++kk) {
+                double av[4], bv[4];
+#pragma unroll
+                for (int a = 0; a < 4; ++a) av[a] = sA[ty + 16 * a][kk];
+#pragma unroll
+                for (int b = 0; b < 4; ++b) bv[b] = sB[tx + 16 * b][kk];
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) m[a][b] = fmax(m[a][b], fabs(av[a] - bv[b]));
+            }
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const long long i = i0 + ty + 16 * a, j = j0 + tx + 16 * b;
+                if (i < nA && j < nB && m[a][b] > 0.0)
+                    atomicMax(&out[(i * nB + j) * nseg + s], (unsigned long long)__double_as_longlong(m[a][b]));
+            }
+    }
+}
+
 // out[p] over D[p][0..nseg-1]: mode 0 max, 1 left-to-right sum, 2 left-to-right
 // sum of the (correctly rounded) square roots
 __global__ void k_combine(const double *D, long long n, int nseg, int mode, double *out)
@@ -280,6 +344,42 @@ unsigned bins_grid(long long n, int M)
     return grid_for(n, q < 4e7 ? 512 : q < 1.3e8 ? 1024 : q < 5e8 ? 2048 : 4096);
 }
 
+// The max-abs kernel's workgroups and its split of k: about 1024 tiles staged in
+// LDS, or 2048 workgroups of wavefronts in parts of at least 256.
+struct MaxabsGrid {
+    bool lds;
+    long long tiles, splits, ks;
+};
+MaxabsGrid maxabs_grid(bool lds, long long nA, long long nB, long long dim)
+{
+    const long long ti = lds ? MT : PTI, tj = lds ? MT : PCW, part = lds ? MKC : 256, full = lds ? 1024 : 2048;
+    const long long tiles = ((nA + ti - 1) / ti) * ((nB + tj - 1) / tj), chunks = (dim + part - 1) / part;
+    const long long splits = std::max<long long>({1, std::min<long long>(chunks, (full + tiles - 1) / tiles),
+                                                  (dim + (1ll << 28) - 1) >> 28});
+    const long long ks = (chunks + splits - 1) / splits * part;
+    return MaxabsGrid{lds, tiles, (dim + ks - 1) / ks, ks};
+}
+// The faster of the two, by a fit to 890 sizes (1 x 1000 to 4000 x 4000 pairs, d = 8
+// .. 24320, 1, 3 and 8 segments): a call's overhead, the terms of its padded
+// pairs, and per segment met the reduction over the lanes or the atomics (whose
+// lines the segments of a pair share).  us, wavefronts / tiles: FP64 250^2 of d =
+// 8192 122 / 102, 1000^2 of 2048 381 / 244, of 24320 4866 / 2526; FP32 250^2 of 24320
+// 174 / 201, 1000^2 of 200 73 / 63, 2048^2 of 20 148 / 60, of 8192 2677 / 3238; three
+// segments 1000^2 of 200 115 / 127, 2048^2 of 20 343 / 223.
+MaxabsGrid choose_maxabs(long long nA, long long nB, long long dim, int nseg, cil_precision prec)
+{
+    const MaxabsGrid w = maxabs_grid(false, nA, nB, dim), t = maxabs_grid(true, nA, nB, dim);
+    const double np = (double)nA * nB, d = (double)dim;
+    auto met = [&](const MaxabsGrid &g) { return (double)(nseg > 1 ? nseg + g.splits - 1 : g.splits); };
+    double tw = 31.0 + (double)w.tiles * PTI * PCW * (2.2e-5 * met(w) + (prec == CIL_FP32 ? 8.1e-8 : 1.6e-7) * d);
+    double tt = 40.0 + (double)t.tiles * MT * MT * 9.4e-8 * (d + 16.0 * nseg);
+    if (nseg > 1) {
+        tw += np * 7.5e-6 * met(w);
+        tt += np * 3.8e-6 * nseg * met(t);
+    }
+    return tt < tw ? t : w;
+}
+
 }  // namespace
 
 int minmax_scale_impl(const void *X, long long count, int n, cil_precision prec, void *Y, hipStream_t st)
@@ -321,22 +421,19 @@ int pair_maxabs_impl(const void *A, long long nA, const void *B, long long nB, l
     if (dim == 0) return CIL_OK;
     SegEnds ends{};
     for (int s = 0; s < nseg; ++s) ends.end[s] = seg_end[s];
-    // split k so that the grid holds about 2048 workgroups, in parts of at least 256
-    const long long tiles = ((nA + PTI - 1) / PTI) * ((nB + PCW - 1) / PCW), chunks = (dim + 255) / 256;
-    const long long splits = std::max<long long>({1, std::min<long long>(chunks, (2048 + tiles - 1) / tiles),
-                                                  (dim + (1ll << 28) - 1) >> 28});
-    const long long ks = (chunks + splits - 1) / splits * 256;
-    dim3 grid((unsigned)tiles, (unsigned)((dim + ks - 1) / ks));
     unsigned long long *out = (unsigned long long *)D;
-    const ProfMark pm = prof_begin("k_pair_maxabs", st);
+    const MaxabsGrid g = choose_maxabs(nA, nB, dim, nseg, prec);
+    const char *name = g.lds ? "k_pair_maxabs_tiles" : "k_pair_maxabs";
+    const dim3 grid((unsigned)g.tiles, (unsigned)g.splits);
+    const ProfMark pm = prof_begin(name, st);
     if (prec == CIL_FP32)
-        hipLaunchKernelGGL(k_pair_maxabs<float>, grid, dim3(256), 0, st, (const float *)A, nA, (const float *)B, nB,
-                           dim, ends, nseg, ks, out);
+        hipLaunchKernelGGL(g.lds ? k_pair_maxabs_tiles<float> : k_pair_maxabs<float>, grid, dim3(256), 0, st,
+                           (const float *)A, nA, (const float *)B, nB, dim, ends, nseg, g.ks, out);
     else
-        hipLaunchKernelGGL(k_pair_maxabs<double>, grid, dim3(256), 0, st, (const double *)A, nA, (const double *)B, nB,
-                           dim, ends, nseg, ks, out);
+        hipLaunchKernelGGL(g.lds ? k_pair_maxabs_tiles<double> : k_pair_maxabs<double>, grid, dim3(256), 0, st,
+                           (const double *)A, nA, (const double *)B, nB, dim, ends, nseg, g.ks, out);
     prof_end(pm, st);
-    return check_launch("k_pair_maxabs");
+    return check_launch(name);
 }
 
 int combine_segments_impl(const double *D, long long n, int nseg, int mode, double *out, hipStream_t st)
