@@ -176,7 +176,7 @@ template <typename T>
 struct Line32 {
     using V = Vec4<T>;
     static constexpr int N = 32, NS = 2;                  // NS: blocks of 16 slots
-    static constexpr bool kRagged = false;
+    static constexpr bool kRagged = false, kShort = false;
     V C2, C2T, C4;
     __device__ __forceinline__ void init(const T *, int lane)
     {
@@ -210,7 +210,7 @@ template <typename T>
 struct Line64 {
     using V = Vec4<T>;
     static constexpr int N = 64, NS = 4;
-    static constexpr bool kRagged = false;
+    static constexpr bool kRagged = false, kShort = false;
     V C2, C2T, C4, S2, S2T, rc, rs;
     T keep;                                               // 0 for label 0 (register 0 of group 0), else 1
     __device__ __forceinline__ void init(const T *, int lane)
@@ -281,7 +281,7 @@ template <typename T>
 struct Line128 {
     using V = Vec4<T>;
     static constexpr int N = 128, NS = 8;
-    static constexpr bool kRagged = false;
+    static constexpr bool kRagged = false, kShort = false;
     Line64<T> h;
     V S4, rc0, rs0, rc1, rs1;
     __device__ __forceinline__ void init(const T *, int lane)
@@ -359,7 +359,7 @@ template <typename T, int NB>
 struct LineDense {
     using V = Vec4<T>;
     static constexpr int N = 32 * NB, NS = 2 * NB;        // padded side
-    static constexpr bool kRagged = true;
+    static constexpr bool kRagged = true, kShort = false;
     static constexpr bool kHeld = NB == 1;
     static constexpr int kMats = 3 * NB * NB;
     V held[kHeld ? kMats : 1];
@@ -437,6 +437,13 @@ struct LineDense {
         const int k = hb < NB ? 2 * (16 * hb + lab) : 2 * (16 * (hb - NB) + lab) + 1;
         return k < n ? k : -1;
     }
+};
+
+// n <= 16: the lines' slots 8 .. 15 of either half, and so every second tile of
+// eight lines, are padding.  The transforms are the same, for half the lines.
+template <typename T>
+struct LineShort : LineDense<T, 1> {
+    static constexpr bool kShort = true;
 };
 
 // Uniform access to the slot maps of both kinds of line.

@@ -100,7 +100,9 @@ __device__ __forceinline__ double steady_value(const double *p, int sp)
 template <typename T, typename Line, int TPW>
 struct MmShape {
     static constexpr int N = Line::N, NS = Line::NS;          // N: padded side
-    static constexpr int WAVES = N / (8 * TPW), THREADS = 64 * WAVES;
+    // lines from one tile that is formed to the next: 8, or 16 where every second tile is padding
+    static constexpr int PITCH = Line::kShort ? 16 : 8;
+    static constexpr int WAVES = N / (PITCH * TPW), THREADS = 64 * WAVES;
     static constexpr int LD = N + 4, SP = N * LD + 8;         // LDS strides, in values
     static constexpr int LDS = 2 * SP;
     // divisors in registers: 4 NS values a lane, where that is at most 16 VGPRs;
@@ -129,12 +131,13 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
     using V = Vec4<T>;
     using SH = MmShape<T, Line, TPW>;
     constexpr int NS = Line::NS, LD = SH::LD, SP = SH::SP, WAVES = SH::WAVES, THREADS = SH::THREADS;
+    constexpr int PITCH = SH::PITCH, TILE = PITCH / 8 * NS * 256;     // TILE: divisors from wavefront to wavefront
     constexpr bool RAG = Line::kRagged;
     constexpr int ROR8 = 0x128;                               // DPP: rotate by 8 within 16 lanes
-    constexpr int STEP = 8 * WAVES;                           // lines between a wavefront's tiles
+    constexpr int STEP = PITCH * WAVES;                       // lines between a wavefront's tiles
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, sp = c >> 3, g4 = 4 * (lane >> 4);
-    const int line = 8 * wave + (c & 7);                      // the lane's row (and column) slot in its first tile
+    const int line = PITCH * wave + (c & 7);                  // the lane's row (and column) slot in its first tile
     const int n = RAG ? s.n : Line::N;
     const int NN = n * n;
     Line L;
@@ -145,8 +148,8 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
     T *const row = sm + sp * SP + line * LD + g4;             // slots hb * 16 + g4 + i of the lane's row
     T *const col = sm + sp * SP + g4 * LD + line;             // the same of its column, stride LD
     const size_t dsz = (size_t)2 * SH::N * SH::N;
-    const T *dp = dtab + s.tab * dsz + (size_t)wave * NS * 256 + lane * 4;
-    const T *dp2 = SCHEME ? dtab2 + s.tab * dsz + (size_t)wave * NS * 256 + lane * 4 : dp;
+    const T *dp = dtab + s.tab * dsz + (size_t)wave * TILE + lane * 4;
+    const T *dp2 = SCHEME ? dtab2 + s.tab * dsz + (size_t)wave * TILE + lane * 4 : dp;
     const auto ub = make_rsrc(state + s.off, 2u * NN * sizeof(T));
 
     // Element offset of slot (hb, i) of tile k within the solve's state; -1:
@@ -187,6 +190,11 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
         else
             return __int_as_float(__float_as_int(v) & m);
     };
+    // the rows of tiles that are not formed stay zero: the constants' zero rows keep them
+    if constexpr (Line::kShort) {
+#pragma unroll
+        for (int hb = 0; hb < NS; ++hb) *reinterpret_cast<V *>(row + 8 * LD + hb * 16) = V(T(0));
+    }
     // f(k, hb, i, element) over the lane's slots
     auto each = [&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
@@ -231,7 +239,7 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
         c0 = fabs(u0) <= 4.0 * a ? T(u0) : T(0);              // (NaN compares false)
         __syncthreads();
     }
-    constexpr int DT = WAVES * NS * 256;                      // divisors between a wavefront's tiles
+    constexpr int DT = WAVES * TILE;                          // divisors between a wavefront's tiles
     V dv[TPW][NS];
     auto load_div = [&](const T *p, int k) __attribute__((always_inline)) {
 #pragma unroll
