@@ -791,8 +791,7 @@ struct PlainGroup {
     std::vector<std::vector<SplitItem<T>>> tiles;    // per active solve
     std::vector<SplitItem<T>> items;              // in launch order
     SplitItem<T> *ditems = nullptr;
-    T *c0 = nullptr;
-    bool started = false;
+    T *c0 = nullptr, *ct = nullptr;
 };
 
 // History of the second-order stepper for one plain launch: u^{s-2} and
@@ -1314,14 +1313,11 @@ int run_plain(SimCtx &c, std::vector<PlainGroup<T>> &groups, const DevSolve *dS,
             if (g.split) {
                 if (g.items.empty()) CIL_TRY(upload_items(g, c.st));
                 constexpr bool f32 = std::is_same<T, float>::value;
-                if constexpr (f32) {
-                    if (!g.started) CIL_TRY(launch_split_offsets(dS, g.dlist, nl, state, g.c0, c.model, c.st));
-                    g.started = true;
-                }
                 SplitArgs<T> a{};
                 a.items = g.ditems;
                 a.state = state;
                 a.c0 = g.c0;
+                a.ct = f32 && c.model != CIL_FHN && c.model != CIL_HEAT ? g.ct : nullptr;     // (kOffset)
                 a.res = R;
                 const ProfMark pm = prof_begin(c.scheme ? (f32 ? "split_step_sbdf2_f32" : "split_step_sbdf2_f64")
                                                         : (f32 ? "split_step_f32" : "split_step_f64"), c.st);
@@ -1412,6 +1408,7 @@ int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std:
     for (auto &t : g->tiles) all += t.size();
     CIL_TRY(c.cb->alloc((void **)&g->ditems, sizeof(SplitItem<T>) * (all + 8 * most)));
     CIL_TRY(c.cb->alloc((void **)&g->c0, sizeof(T) * 2 * hs.size()));
+    CIL_TRY(c.cb->alloc((void **)&g->ct, sizeof(T) * 32 * hs.size()));
     CIL_TRY(c.cb->alloc((void **)&g->dlist, sizeof(int) * g->active.size()));
     return CIL_OK;
 }

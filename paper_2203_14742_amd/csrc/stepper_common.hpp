@@ -189,14 +189,12 @@ template <typename T>
 struct SplitArgs {
     const SplitItem<T> *items;
     T *state;
-    T *c0;                               // FP32: per solve and species, the constant the transforms leave out
+    T *c0;                               // FP32: per solve and species, the constant the field in `work` leaves out
+    T *ct;                               // FP32 (or null): the tiles' own constants of the step, [solve][species][16]
     StepResults res;
     int flags, first;                    // set by launch_split, as the coefficients
     T k4, kt, k2, kc;
 };
-// c0 of the solves in `list`, from their states
-int launch_split_offsets(const DevSolve *S, const int *list, int nl, const float *state, float *c0, int model,
-                         hipStream_t st);
 template <typename T>
 int launch_split(SplitArgs<T> a, int nitems, int model, double dt, int K, bool bdf, bool from_start, hipStream_t st);
 

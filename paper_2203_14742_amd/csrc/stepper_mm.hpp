@@ -74,9 +74,15 @@ struct OwnReaction {
 
 // The homogeneous steady state of the lane's species (Sec. 4.1), or 0.  The
 // diffusion solve leaves a constant as it is, so FP32 transforms act on
-// u - u* instead of u: their rounding is then relative to the pattern's
-// amplitude and not to its mean (0 where the state is far smaller than u*,
-// which would cost digits instead).
+// u - u* instead of u where u is of the size of u*: their rounding is then
+// relative to the pattern's amplitude and not to its mean (largest error of 100
+// steps near u*: 5e-7 of the field against 4e-6).  Where parts of the field are far
+// smaller than u* that would cost their digits, and they act on u.
+// A step chooses from the state it starts from and nothing else, so that an
+// IMEX-Euler run cut anywhere and carried on from its state rounds as the whole
+// run does.  Every tile of eight rows chooses for itself (StepOffset); the field
+// between the passes leaves out u* if all tiles do, else 0, and the column of the
+// rows' means takes up the difference where a tile chose otherwise (join_offsets).
 template <int MODEL>
 __device__ __forceinline__ double steady_value(const double *p, int sp)
 {
@@ -92,6 +98,49 @@ __device__ __forceinline__ double steady_value(const double *p, int sp)
         w = p[1] / p[0];
     }
     return sp ? w : v;
+}
+
+// Whether a kernel leaves a constant out of its transforms.
+template <int MODEL, typename T>
+constexpr bool kOffset = sizeof(T) == 4 && MODEL != CIL_FHN && MODEL != CIL_HEAT;
+
+// A step's choice for one tile: u0 = u* if every |u| of it is at least |u*| / 4.
+template <int MODEL>
+struct StepOffset {
+    float u0, least;
+    __device__ __forceinline__ void init(const double *p, int sp)
+    {
+        const double u = steady_value<MODEL>(p, sp), q = 0.25 * fabs(u);
+        const bool ok = fabs(u) <= (double)__FLT_MAX__;                      // (a NaN is none)
+        u0 = ok ? (float)u : 0.0f;
+        least = ok ? (float)q : __builtin_nanf("");                          // NaN: never
+        if ((double)least < q) least = __int_as_float(__float_as_int(least) + 1);     // least float >= q
+    }
+    // the lanes' species (bit 0: v, bit 1: w) whose values in the tile all reach
+    // `least`; abs(hb, i): the lane's values, infinite for padding
+    template <int NS, typename F>
+    __device__ __forceinline__ unsigned species(F &&abs) const
+    {
+        float part[4], m;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                        // four chains side by side
+            part[i] = __builtin_inff();
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb) part[i] = fminf(part[i], abs(hb, i));
+        }
+        m = fminf(fminf(part[0], part[1]), fminf(part[2], part[3]));
+        const unsigned long long b = __ballot(!(m >= least)), v = 0x00FF00FF00FF00FFull;      // lanes of species v
+        return ((b & v) ? 0u : 1u) | ((b & ~v) ? 0u : 2u);
+    }
+};
+// Rows' means (column slot 0, unnormalised: n times the mean), x from a tile that
+// left out ct to a field that leaves out cf.  Bit i of `rows`: x[i] is the mean of
+// a row (not of padding, which a fold adds to the middle row of an odd side).
+__device__ __forceinline__ Vec4<float> join_offsets(Vec4<float> x, float n, float ct, float cf, unsigned rows)
+{
+#pragma unroll
+    for (int i = 0; i < 4; ++i) x[i] = (rows >> i & 1u) && ct != cf ? fmaf(n, ct - cf, x[i]) : x[i];
+    return x;
 }
 
 // TPW: tiles of eight lines per wavefront (tile = wavefront + WAVES k).  Two
@@ -216,29 +265,12 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
         buf_store<E>(v, rsrc, e < 0 ? 0xFFFFFF00u : (unsigned)e * (unsigned)sizeof(E), 0);
     };
     if constexpr (LOAD) each([&](int k, int hb, int i, int e) { x[k][hb][i] = ld(ub, T(0), e); });
-    // constant the transforms leave out (FP32 without a correction form)
+    // constant the transforms leave out in this step (FP32 without a correction form)
+    constexpr bool OFF = kOffset<MODEL, T> && !RF;
     T c0 = T(0);
-    if constexpr (sizeof(T) == 4 && !RF && MODEL != CIL_FHN && MODEL != CIL_HEAT) {
-        double a = 0.0;
-#pragma unroll
-        for (int k = 0; k < TPW; ++k)
-#pragma unroll
-            for (int hb = 0; hb < NS; ++hb)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) a = fmax(a, fabs((double)x[k][hb][i]));
-        // over the lanes of one species, then over the wavefronts
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1)
-            if (o != 8) a = fmax(a, __shfl_xor(a, o, 64));
-        __syncthreads();
-        if ((lane & ~8) == 0) red[sp * WAVES + wave] = a;
-        __syncthreads();
-        a = 0.0;
-        for (int w = 0; w < WAVES; ++w) a = fmax(a, red[sp * WAVES + w]);
-        const double u0 = steady_value<MODEL>(s.p, sp);
-        c0 = fabs(u0) <= 4.0 * a ? T(u0) : T(0);              // (NaN compares false)
-        __syncthreads();
-    }
+    [[maybe_unused]] std::conditional_t<OFF, StepOffset<MODEL>, int> offset;
+    if constexpr (OFF) offset.init(s.p, sp);
+    uint8_t *const chose = reinterpret_cast<uint8_t *>(sbad + WAVES);          // OFF: the tiles' species(), a byte each
     constexpr int DT = WAVES * TILE;                          // divisors between a wavefront's tiles
     V dv[TPW][NS];
     auto load_div = [&](const T *p, int k) __attribute__((always_inline)) {
@@ -335,6 +367,14 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
             for (int k = 0; k < TPW; ++k) {
                 // explicit reaction
                 V X[NS];
+                if constexpr (OFF) {
+                    const unsigned has = offset.template species<NS>([&](int hb, int i) __attribute__((always_inline)) {
+                        if constexpr (RAG) return (real[k] >> (hb * 4 + i) & 1u) ? fabsf(x[k][hb][i]) : __builtin_inff();
+                        else return fabsf(x[k][hb][i]);
+                    });
+                    chose[wave + WAVES * k] = (uint8_t)has;       // (every lane: no branch)
+                    c0 = (has >> sp) & 1u ? offset.u0 : 0.0f;
+                }
 #pragma unroll
                 for (int hb = 0; hb < NS; ++hb) {
                     V r;
@@ -351,8 +391,9 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
                             q = own + tdt * (r[i] + (sp ? gg : f));
                         } else if constexpr (SCHEME == 1) {
                             const T F = react(own, oth), ud = own - c0;
-                            q = fma(kc, fma(k2, F, -fh[k][hb][i]), fma(k4, ud, -uh[k][hb][i]) * kt);
-                            uh[k][hb][i] = ud;
+                            const T up = uh[k][hb][i] - (dsel == dp2 ? c0 : T(0));        // (first step: none)
+                            q = fma(kc, fma(k2, F, -fh[k][hb][i]), fma(k4, ud, -up) * kt);
+                            uh[k][hb][i] = own;
                             fh[k][hb][i] = F;
                         } else {
                             q = fma(tdt, react(own, oth), own - c0);
@@ -377,6 +418,38 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
                 if constexpr (!SH::DREG && !SH::DLATE) {
                     if (k > 0) load_div(dsel, k);
                 }
+                if constexpr (OFF) {
+                    if (k == 0) {                             // (behind the column's reads: its latency is theirs)
+                        constexpr int TILES = WAVES * TPW;
+                        const unsigned ones = TILES == 2 ? 0x0101u : 0x01010101u;
+                        unsigned any = 0, all = ~0u;
+                        if constexpr (TILES == 2) {
+                            any = all = *reinterpret_cast<const uint16_t *>(chose);
+                        } else {
+#pragma unroll
+                            for (int w = 0; w < TILES / 4; ++w) {
+                                const unsigned f = (unsigned)sbad[WAVES + w];
+                                any |= f;
+                                all &= f;
+                            }
+                        }
+                        c0 = (all & (ones << sp)) == ones << sp ? offset.u0 : 0.0f;
+                        if (__builtin_amdgcn_readfirstlane(wave) == 0) {
+                            any = __builtin_amdgcn_readfirstlane(any);
+                            all = __builtin_amdgcn_readfirstlane(all);
+                            // some tile left out another constant than the field
+                            if (((any & ones) && (all & ones) != ones) || ((any & 2 * ones) && (all & 2 * ones) != 2 * ones)) {
+#pragma unroll
+                                for (int hb = 0; hb < NS; ++hb) {         // the lane's rows are of tile 2 hb + g / 2
+                                    const int t = (2 * hb + (lane >> 5)) / (PITCH / 8);
+                                    const float ct = (chose[t] >> sp) & 1u ? offset.u0 : 0.0f;
+                                    const unsigned rows = (c & 7) != 0 ? 0u : RAG ? real[0] >> (4 * hb) : 15u;     // (their own slots)
+                                    x[k][hb] = join_offsets(x[k][hb], (float)n, ct, c0, rows);
+                                }
+                            }
+                        }
+                    }
+                }
                 L.fwd(x[k], X);
                 if constexpr (SH::DLATE) load_div(dsel, k);
 #pragma unroll
@@ -394,7 +467,7 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
 #pragma unroll
                 for (int hb = 0; hb < NS; ++hb) X[hb] = *reinterpret_cast<const V *>(row + STEP * LD * k + hb * 16);
                 L.inv(X, x[k]);
-                if constexpr (sizeof(T) == 4 && !RF && MODEL != CIL_FHN && MODEL != CIL_HEAT) {
+                if constexpr (kOffset<MODEL, T> && !RF) {
 #pragma unroll
                     for (int hb = 0; hb < NS; ++hb) x[k][hb] += V(c0);
                 }
@@ -481,7 +554,7 @@ __global__ __launch_bounds__((MmShape<T, Line, TPW>::THREADS)) __attribute__((am
     using SH = MmShape<T, Line, TPW>;
     __shared__ __align__(16) T sm[SH::LDS];
     __shared__ double red[2 * SH::WAVES];
-    __shared__ int sbad[SH::WAVES];
+    __shared__ int sbad[SH::WAVES + 4];
     const int b = list[blockIdx.x];
     const DevSolve s = S[b];
     long long step = pa.steps[b];
@@ -505,7 +578,7 @@ void k_mm_mixed(const DevSolve *S, const int *list, float *state, double *state6
     // the refinement form keeps R behind the field
     __shared__ __align__(16) double sm[RF ? SF::LDS / 2 + N * N : SD::LDS];
     __shared__ double red[2 * SF::WAVES];
-    __shared__ int sbad[SF::WAVES];
+    __shared__ int sbad[SF::WAVES + 4];
     const int b = list[blockIdx.x];
     const DevSolve s = S[b];
     long long step = pa32.steps[b];

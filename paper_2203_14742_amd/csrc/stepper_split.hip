@@ -32,10 +32,6 @@ __host__ __device__ __forceinline__ void split_dispatch(int n, F &&f)
     else f(LineDense<T, 3>{});
 }
 
-// FP32 transforms act on u - u* (steady_value); FP64 ones on u.
-template <int MODEL, typename T>
-constexpr bool kOffset = sizeof(T) == 4 && MODEL != CIL_FHN && MODEL != CIL_HEAT;
-
 template <int MODEL, typename T, typename Line>
 __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<T> &it)
 {
@@ -57,6 +53,7 @@ __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<
         const unsigned e = (unsigned)((sp * n + rn) * n + slot_pos<Line>(hb, g4 + i, n)) * (unsigned)sizeof(T);
         return !RAG || real(hb, i) ? e : 0xFFFFFF00u;
     };
+    // FP32 transforms act on u - u* (steady_value); FP64 ones on u
     T c0 = T(0);
     if constexpr (kOffset<MODEL, T>) c0 = a.c0[2 * it.b + sp];
     V x[NS], X[NS];
@@ -106,6 +103,16 @@ __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<
     if (!(a.flags & SPLIT_NEXT)) return;
     OwnReaction<MODEL, T> react;
     react.init(s.p, sp);
+    if constexpr (kOffset<MODEL, T>) {                        // the tile's own choice, for the column pass
+        StepOffset<MODEL> offset;
+        offset.init(s.p, sp);
+        const unsigned has = offset.template species<NS>([&](int hb, int i) __attribute__((always_inline)) {
+            return !RAG || real(hb, i) ? fabsf(x[hb][i]) : __builtin_inff();
+        });
+        c0 = (has >> sp) & 1u ? offset.u0 : 0.0f;
+        if ((lane & ~8) == 0) a.ct[(2 * it.b + sp) * 16 + it.tile] = c0;
+    }
+    const T cp = a.first ? T(0) : c0;                         // (no history yet)
     // history of the second-order scheme: u and F in the lane's own order
     T *const hist = it.hist ? it.hist + lane * 4 : nullptr;
 #pragma unroll
@@ -121,9 +128,9 @@ __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<
             const T own = x[hb][i], oth = dpp_mov<ROR8>((T)x[hb][i]);
             const T F = react(own, oth), ud = own - c0;
             T q;
-            if (hist) q = fma(a.kc, fma(a.k2, F, -fh[i]), fma(a.k4, ud, -uh[i]) * a.kt);
+            if (hist) q = fma(a.kc, fma(a.k2, F, -fh[i]), fma(a.k4, ud, -(uh[i] - cp)) * a.kt);
             else q = fma(a.kc, F, ud);
-            un[i] = ud;
+            un[i] = own;
             fn[i] = F;
             if constexpr (RAG) {                              // padding carries no value (and no NaN) on
                 if (!real(hb, i)) q = T(0);
@@ -160,6 +167,29 @@ __device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitIt
 #pragma unroll
         for (int hb = 0; hb < NS; ++hb) dv[hb] = mm_load(dp + hb * 256);
     };
+    if constexpr (sizeof(T) == 4) {
+        if (a.ct && it.tile == 0) {                           // the column of the rows' means, as in mm_solve
+            float ct[NS], cf = 0.0f;
+            bool all = true;
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb) {
+                ct[hb] = a.ct[(2 * it.b + sp) * 16 + 2 * hb + (lane >> 5)];
+                all = all && ct[hb] != 0.0f;
+                cf = ct[hb];
+            }
+            // (the other half of the species' tiles is 32 lanes on)
+            if (!(__shfl_xor((int)all, 32, 64) && all)) cf = 0.0f;
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb) {
+                unsigned rows = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    rows |= ((c & 7) == 0 && slot_valid<Line>(hb, g4 + i, it.s.n) ? 1u : 0u) << i;
+                x[hb] = join_offsets(x[hb], (float)it.s.n, ct[hb], cf, rows);
+            }
+            if ((lane & ~8) == 0) a.c0[2 * it.b + sp] = cf;
+        }
+    }
     if constexpr (NS < 8) divisors();                         // ahead of the transform where registers are left
     L.fwd(x, X);
     if constexpr (NS >= 8) divisors();
@@ -190,37 +220,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     split_dispatch<T>(it.s.n, [&](auto line) __attribute__((always_inline)) { column_pass<T, decltype(line)>(a, it); });
 }
 
-template <int MODEL>
-__global__ __launch_bounds__(256) void k_split_offsets(const DevSolve *S, const int *list, const float *state, float *c0)
-{
-    __shared__ double top[2][4];
-    const int b = list[blockIdx.x];
-    const DevSolve s = S[b];
-    const int NN = s.n * s.n;
-    for (int sp = 0; sp < 2; ++sp) {
-        double m = 0.0;
-        for (int e = threadIdx.x; e < NN; e += 256) m = fmax(m, fabs((double)state[s.off + (int64_t)sp * NN + e]));
-        m = wave_max(m);
-        if ((threadIdx.x & 63) == 0) top[sp][threadIdx.x >> 6] = m;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {                                    // mm_solve's rule
-        const double *t = top[threadIdx.x], m = fmax(fmax(t[0], t[1]), fmax(t[2], t[3]));
-        const double u0 = steady_value<MODEL>(s.p, threadIdx.x);
-        c0[2 * b + threadIdx.x] = fabs(u0) <= 4.0 * m ? (float)u0 : 0.0f;
-    }
-}
-
 }  // namespace
-
-int launch_split_offsets(const DevSolve *S, const int *list, int nl, const float *state, float *c0, int model,
-                         hipStream_t st)
-{
-    dispatch_model(model, [&](auto MD) {
-        hipLaunchKernelGGL((k_split_offsets<decltype(MD)::value>), dim3(nl), dim3(256), 0, st, S, list, state, c0);
-    });
-    return check_launch("k_split_offsets");
-}
 
 // K steps of the items from the states; from_start: the first of them is the
 // second-order scheme's first, an IMEX-Euler step.
