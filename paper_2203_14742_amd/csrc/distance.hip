@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "cil_internal.hpp"
+#include "dd_round.hpp"
 #include "distance_async.hpp"
 #include "radii_dd.hpp"
 
@@ -291,13 +292,6 @@ __global__ __launch_bounds__(CLS) void k_classify(ClassifyArgs c, long long nA, 
 // (Shewchuk's exact summation), lane 0 merges the 64 expansions and rounds
 // once, half to even.
 
-__device__ __forceinline__ void two_sum(double a, double b, double &s, double &e)
-{
-    s = a + b;
-    const double bb = s - a;
-    e = (a - (s - bb)) + (b - bb);
-}
-
 // (hi, lo) += (bh, bl); inexact |= some rounding lost bits
 __device__ __forceinline__ void dd_add_t(double &hi, double &lo, double bh, double bl, int &inexact)
 {
@@ -341,19 +335,6 @@ __device__ __forceinline__ void top_square(double &S, double &lo, double d)
     const double t = fma(d, d, S);
     lo += fma(d, d, -(t - S));
     S = t;
-}
-
-// Whether fl(hi + lo) = R, with the rest e, is the correctly rounded value of
-// any sum within delta R + slack of hi + lo: no rounding boundary of R (half an
-// ulp away, except below a power of two, where the spacing halves) lies between.
-__device__ __forceinline__ bool dd_certain(double hi, double lo, double delta, double &R, double slack = 0.0)
-{
-    double e;
-    two_sum(hi, lo, R, e);
-    int ex;
-    const double frac = frexp(R, &ex);                   // R = frac 2^ex, frac in [0.5, 1)
-    const double half = (e < 0.0 && frac == 0.5) ? ldexp(1.0, ex - 55) : ldexp(1.0, ex - 54);
-    return isfinite(R) && (fabs(e) + (delta * R + slack) < half || R == 0.0);
 }
 
 constexpr int EXP_CAP = 64;     // a non-overlapping expansion of doubles has < 40 parts
