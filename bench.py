@@ -564,8 +564,10 @@ def uneven_main(args):
                    "steps_per_solve": w["max_steps"], "stepping": "fp32 fused persistent, one HIP graph launch "
                    "(one kernel per side on forked streams)", "parallelism": "none (1 GPU)"},
         "autotune": {"trial_steps": args.tune_steps, "seconds": round(t_tune, 3), "plan_seconds": round(t_plan, 3),
-                     "sides": [{"n": g["n"], "solves": g["count"], "shape": g["shape"],
-                                "trial_ms": [round(m, 3) for m in g["tuned_ms"]]} for g in info]},
+                     "sides": [{"n": g["n"], "solves": g["count"],
+                                "kernel": ("line lanes", "quad lanes", "matrix cores")[g["kernel"]], "quad_shape": g["shape"],
+                                "quad_trial_ms": [round(m, 3) for m in g["tuned_ms"]],
+                                "matrix_trial_ms": round(g["matrix_ms"], 3)} for g in info]},
         "all_ok": bool(np.all(rep["status"] == 0) and np.all(rep["steps_taken"] == w["max_steps"])),
         "roofline": roof,
         "cpu_baseline": None,

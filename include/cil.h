@@ -218,11 +218,16 @@ int cil_simulate_patterns_sbdf2(cil_model model, cil_precision prec, const cil_p
  *     results (steps_fp64 is 0), reports host[B] or NULL.  Synchronises.
  *     Returns CIL_ENONFINITE if a solve ended NONFINITE.
  *   cil_sim_plan_groups / cil_sim_plan_group_info: the grid sides in launch
- *     order (most work first): side n, solve count, chosen shape, and the
- *     tuning times in ms (host[CIL_QUAD_SHAPES] or NULL; 0 before tuning).
+ *     order (most work first): side n, solve count, the quad-lane code shape (the
+ *     fastest one tried; it runs where the group's kernel is the quad-lane one),
+ *     and the shapes' tuning times in ms (host[CIL_QUAD_SHAPES] or NULL; 0 before
+ *     tuning).
+ *   cil_sim_plan_group_kernel: the kernel a group's launches run (cil_kernel), and
+ *     the matrix-core kernel's tuning time in ms (or NULL; 0 if not timed).
  *   cil_sim_plan_destroy: synchronises the device, frees the plan (NULL ok). */
 typedef struct cil_sim_plan_s cil_sim_plan;
 enum { CIL_QUAD_SHAPES = 4 };
+typedef enum { CIL_KERNEL_LINE = 0, CIL_KERNEL_QUAD = 1, CIL_KERNEL_MATRIX = 2 } cil_kernel;
 int cil_sim_plan_create(cil_model model, cil_precision prec, const cil_problem *probs, int32_t B, void *state,
                         const int64_t *elem_offsets, const cil_stepping *stepping, void *hip_stream,
                         cil_sim_plan **plan);
@@ -232,6 +237,7 @@ int cil_sim_plan_report(cil_sim_plan *plan, cil_solve_report *reports, void *hip
 int cil_sim_plan_groups(const cil_sim_plan *plan);
 int cil_sim_plan_group_info(const cil_sim_plan *plan, int32_t group, int32_t *n, int32_t *count, int32_t *shape,
                             double *tuned_ms);
+int cil_sim_plan_group_kernel(const cil_sim_plan *plan, int32_t group, int32_t *kernel, double *matrix_ms);
 int cil_sim_plan_destroy(cil_sim_plan *plan);
 
 /* ------------------------------------------------------- CIL statistic */

@@ -34,6 +34,7 @@ CIL_OPT_POLISH_SEPARATE = 7
 CIL_OPT_SYNC_SPIN_US = 8
 CIL_OPT_STAT_DEVICE_RADII = 9
 CIL_QUAD_SHAPES = 4
+CIL_KERNEL_LINE, CIL_KERNEL_QUAD, CIL_KERNEL_MATRIX = 0, 1, 2
 
 
 class CilError(RuntimeError):
@@ -134,13 +135,14 @@ def lib() -> ctypes.CDLL:
         L.cil_sim_plan_report.argtypes = [vp, vp, vp]
         L.cil_sim_plan_groups.argtypes = [vp]
         L.cil_sim_plan_group_info.argtypes = [vp, i32, vp, vp, vp, vp]
+        L.cil_sim_plan_group_kernel.argtypes = [vp, i32, vp, vp]
         L.cil_sim_plan_destroy.argtypes = [vp]
         for name in ("cil_homogeneous_state", "cil_simulate_patterns", "cil_features", "cil_pair_bins",
                      "cil_distance_range", "cil_canonical_d2", "cil_radii", "cil_last_distance_stats",
                      "cil_bootstrap_features", "cil_bootstrap_features_noalloc", "cil_gaussian_loglik", "cil_set_option", "cil_shutdown",
                      "cil_profile", "cil_profile_read", "cil_profile_names", "cil_sim_plan_create",
                      "cil_sim_plan_tune", "cil_sim_plan_launch", "cil_sim_plan_report", "cil_sim_plan_groups",
-                     "cil_sim_plan_group_info", "cil_sim_plan_destroy", "cil_minmax_scale", "cil_augment_patterns",
+                     "cil_sim_plan_group_info", "cil_sim_plan_group_kernel", "cil_sim_plan_destroy", "cil_minmax_scale", "cil_augment_patterns",
                      "cil_pair_maxabs", "cil_combine_segments", "cil_value_range", "cil_bin_values"):
             getattr(L, name).restype = ctypes.c_int
         _lib = L
@@ -283,17 +285,22 @@ class SimPlan:
                                          ctypes.byref(stp), _stream(state), ctypes.byref(self._h)))
 
     def tune(self, steps: int = 100):
-        """Autotune the code shape per grid side; returns group_info()."""
+        """Autotune the kernel per grid side; returns group_info()."""
         _check(lib().cil_sim_plan_tune(self._h, int(steps), _stream(self.state)))
         return self.group_info()
 
     def group_info(self):
+        """Per grid side: n, count, the quad-lane shape and the shapes' tuning times, the kernel that the launches run
+        (CIL_KERNEL_*; `shape` runs only with CIL_KERNEL_QUAD) and the matrix-core kernel's tuning time."""
         out = []
         for g in range(_nonneg(lib().cil_sim_plan_groups(self._h))):
             n, c, s = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
             ms = (ctypes.c_double * CIL_QUAD_SHAPES)()
             _check(lib().cil_sim_plan_group_info(self._h, g, ctypes.byref(n), ctypes.byref(c), ctypes.byref(s), ms))
-            out.append(dict(n=n.value, count=c.value, shape=s.value, tuned_ms=list(ms)))
+            k, mm = ctypes.c_int32(), ctypes.c_double()
+            _check(lib().cil_sim_plan_group_kernel(self._h, g, ctypes.byref(k), ctypes.byref(mm)))
+            out.append(dict(n=n.value, count=c.value, shape=s.value, tuned_ms=list(ms), kernel=k.value,
+                            matrix_ms=mm.value))
         return out
 
     def launch(self):

@@ -516,6 +516,13 @@ int cil_sim_plan_group_info(const cil_sim_plan *plan, int32_t group, int32_t *n,
     return plan_group_info(as_cplan(plan), group, n, count, shape, tuned_ms);
 }
 
+int cil_sim_plan_group_kernel(const cil_sim_plan *plan, int32_t group, int32_t *kernel, double *matrix_ms)
+{
+    API_BEGIN();
+    if (!plan) return set_error(CIL_EINVAL, "null plan");
+    return plan_group_kernel(as_cplan(plan), group, kernel, matrix_ms);
+}
+
 int cil_sim_plan_destroy(cil_sim_plan *plan)
 {
     API_BEGIN();

@@ -150,6 +150,7 @@ int plan_launch(SimPlan *p, hipStream_t st);
 int plan_report(SimPlan *p, cil_solve_report *reports, hipStream_t st);
 int plan_groups(const SimPlan *p);
 int plan_group_info(const SimPlan *p, int g, int *n, int *count, int *shape, double *tuned_ms);
+int plan_group_kernel(const SimPlan *p, int g, int *kernel, double *matrix_ms);
 void plan_destroy(SimPlan *p);
 
 // Radii ladder from a squared-distance range (host; shared by cil_radii and the

@@ -1658,7 +1658,7 @@ struct SimPlan {
         MmTables mm;                          // matrix-core kernel's
         bool use_mm = false;
         int *dl = nullptr;
-        double tuned_ms[kQuadShapes] = {};
+        double tuned_ms[kQuadShapes] = {}, mm_ms = 0.0;
     };
     int dev = 0;
     int model = 0;
@@ -1907,6 +1907,7 @@ int plan_tune(SimPlan *p, int64_t steps, hipStream_t st)
             }
             if (rc != CIL_OK) break;
             if (mm) {
+                g.mm_ms = ms;
                 g.use_mm = ms <= g.tuned_ms[best];
                 break;
             }
@@ -1962,6 +1963,15 @@ int plan_group_info(const SimPlan *p, int g, int *n, int *count, int *shape, dou
     if (shape) *shape = G.shape;
     if (tuned_ms)
         for (int s = 0; s < kQuadShapes; ++s) tuned_ms[s] = G.tuned_ms[s];
+    return CIL_OK;
+}
+
+int plan_group_kernel(const SimPlan *p, int g, int *kernel, double *matrix_ms)
+{
+    if (g < 0 || g >= (int)p->groups.size()) return set_error(CIL_EINVAL, "group %d out of range", g);
+    const SimPlan::Group &G = p->groups[g];
+    if (kernel) *kernel = G.use_mm ? CIL_KERNEL_MATRIX : p->quad ? CIL_KERNEL_QUAD : CIL_KERNEL_LINE;
+    if (matrix_ms) *matrix_ms = G.mm_ms;
     return CIL_OK;
 }
 
