@@ -83,8 +83,8 @@ REACTION_FLOPS = {0: 12, 1: 13, 2: 13, 3: 13, 4: 4}   # kinetics + the explicit 
 
 # Sources that define the fused stepper kernels (device code, launch shape).
 STEPPER_SOURCES = ["stepper.hip", "stepper_common.hpp", "stepper_mm.hpp", "stepper_mm_launch.hpp",
-                   "stepper_mm_f32.hip", "stepper_mm_f64.hip", "stepper_mm_mixed.hip", "dct_mfma.hpp",
-                   "cil_internal.hpp"]
+                   "stepper_mm_f32.hip", "stepper_mm_f64.hip", "stepper_mm_mixed.hip", "stepper_split.hip",
+                   "dct_mfma.hpp", "dct_quad.hpp", "dct_reg.hpp", "cil_internal.hpp"]
 TRAFFIC_PROFILES = os.path.join(ROOT, "profiles", "*_hbm_bytes.md")
 
 
