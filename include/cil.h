@@ -507,8 +507,8 @@ int cil_set_option(int32_t option, int64_t value);
 
 /* Kernel timing.  cil_profile(1) clears the accumulators and starts timing:
  * every hot kernel launch is then bracketed by two HIP events recorded on the
- * stream it is launched on; cil_profile(2) does the same for the fused
- * stepper kernels only (no events on the statistic's short launches);
+ * stream it is launched on; cil_profile(2) does the same for the fused and
+ * tile-by-tile steppers only (no events on the statistic's short launches);
  * cil_profile(0) stops.  cil_profile_read gives the
  * number of timed launches and their total duration in milliseconds for one
  * kernel name (0 and 0.0 if none); cil_profile_names writes the timed kernel

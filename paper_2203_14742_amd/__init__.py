@@ -596,7 +596,7 @@ def cil_set_option(option: int, value: int):
 
 
 def cil_profile(enable):
-    """False/0: off; True/1: every hot kernel; 2: the fused stepper kernels only."""
+    """False/0: off; True/1: every hot kernel; 2: the fused and tile-by-tile steppers only."""
     _check(lib().cil_profile(2 if enable == 2 else int(bool(enable))))
 
 

@@ -256,7 +256,9 @@ ProfMark prof_begin(const char *name, hipStream_t st)
 {
     ProfMark m;
     if (!g_prof_on) return m;
-    if (g_prof_steppers_only && strncmp(name, "k_fused", 7) != 0 && strncmp(name, "k_mm", 4) != 0) return m;
+    if (g_prof_steppers_only && strncmp(name, "k_fused", 7) != 0 && strncmp(name, "k_mm", 4) != 0 &&
+        strncmp(name, "split_step", 10) != 0)
+        return m;
     // a stream being captured into a graph gets no timing events
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cs) != hipSuccess) {

@@ -203,7 +203,7 @@ __device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitIt
 }
 
 template <int MODEL, typename T>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_split_rows(SplitArgs<T> a)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_tile_rows(SplitArgs<T> a)
 {
     const SplitItem<T> it = a.items[blockIdx.x];
     if (it.b < 0) return;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 }
 
 template <typename T>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_split_columns(SplitArgs<T> a)
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_tile_columns(SplitArgs<T> a)
 {
     const SplitItem<T> it = a.items[blockIdx.x];
     if (it.b < 0) return;
@@ -241,7 +241,7 @@ int launch_split(SplitArgs<T> a, int nitems, int model, double dt, int K, bool b
             r.kc = T(dt);
         }
         dispatch_model(model, [&](auto MD) {
-            hipLaunchKernelGGL((k_split_rows<decltype(MD)::value, T>), dim3(nitems), dim3(64), 0, st, r);
+            hipLaunchKernelGGL((k_tile_rows<decltype(MD)::value, T>), dim3(nitems), dim3(64), 0, st, r);
         });
     };
     for (int k = 0; k < K; ++k) {
@@ -249,7 +249,7 @@ int launch_split(SplitArgs<T> a, int nitems, int model, double dt, int K, bool b
         if (k == 0) rows(SPLIT_LOAD | SPLIT_NEXT, first);
         SplitArgs<T> q = a;
         q.first = first;
-        hipLaunchKernelGGL((k_split_columns<T>), dim3(nitems), dim3(64), 0, st, q);
+        hipLaunchKernelGGL((k_tile_columns<T>), dim3(nitems), dim3(64), 0, st, q);
         // the state of the step before the last is what the stop rule compares with
         if (k < K - 1) rows(SPLIT_NEXT | (k == K - 2 ? SPLIT_STORE : 0), !bdf);
         else rows(SPLIT_CHECK | SPLIT_STORE, !bdf);
