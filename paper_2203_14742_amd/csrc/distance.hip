@@ -402,15 +402,15 @@ __device__ double exact_d2_wave(const T *a, const T *b, long long dim, int lane)
     return lane == 0 ? exp_round(part, np) : 0.0;
 }
 
-// The pairs the untracked sum cannot certify (ties, and one in 2^30 or so): the
-// tracked sum by one wavefront, then where that cannot either the exact one.
+// The sum over k = from, from + stride, ... of one wavefront's lanes with a record of
+// lost bits, joined over the lanes.
 template <typename T>
-__device__ __attribute__((noinline)) double canonical_tracked(const T *a, const T *b, long long dim, int lane,
-                                                              int force_exact, unsigned long long *nexact)
+__device__ __forceinline__ void tracked_sum(const T *a, const T *b, long long dim, long long from, long long stride,
+                                            double &hi, double &lo, int &inexact)
 {
-    double hi = 0.0, lo = 0.0;
-    int inexact = 0;
-    for (long long k = lane; k < dim; k += 64) {
+    hi = lo = 0.0;
+    inexact = 0;
+    for (long long k = from; k < dim; k += stride) {
         const double d = ld(a + k) - ld(b + k);
         const double p = d * d;
         dd_add_t(hi, lo, p, fma(d, d, -p), inexact);
@@ -421,8 +421,17 @@ __device__ __attribute__((noinline)) double canonical_tracked(const T *a, const 
         dd_add_t(hi, lo, oh, ol, inexact);
         inexact |= __shfl_xor(inexact, off, 64);
     }
+}
+
+// The rounding of a tracked sum, by one wavefront: as it is where no bit was lost or
+// the certificate holds, else by the exact summation.  (Lane 0's value counts.)
+template <typename T>
+__device__ __attribute__((noinline)) double tracked_round(const T *a, const T *b, long long dim, int lane, double hi,
+                                                          double lo, int inexact, int force_exact,
+                                                          unsigned long long *nexact)
+{
     double D;
-    int certain = dd_certain(hi, lo, (double)(dim + 129) * 0x1p-100, D);   // relative error bound
+    int certain = dd_certain(hi, lo, (double)(dim + 65 * 17) * 0x1p-100, D);   // relative error bound
     certain = isfinite(D) && (certain || !inexact);
     certain = __shfl(certain, 0, 64);
     D = __shfl(D, 0, 64);
@@ -431,6 +440,19 @@ __device__ __attribute__((noinline)) double canonical_tracked(const T *a, const 
         if (lane == 0) atomicAdd(nexact, 1ull);
     }
     return D;
+}
+
+// The pairs the untracked sum cannot certify, by one wavefront: ties, and one in
+// 2^30 or so.  (Of FP32 sets one in some tens: the squares' last bits lie few
+// places below their sum's, so that many sums end on a rounding boundary.)
+template <typename T>
+__device__ __attribute__((noinline)) double canonical_tracked(const T *a, const T *b, long long dim, int lane,
+                                                              int force_exact, unsigned long long *nexact)
+{
+    double hi, lo;
+    int inexact;
+    tracked_sum(a, b, dim, lane, 64, hi, lo, inexact);
+    return tracked_round(a, b, dim, lane, hi, lo, inexact, force_exact, nexact);
 }
 
 struct CanonOut {
@@ -531,21 +553,47 @@ __device__ __forceinline__ void canonical_pair(const T *A, const T *B, long long
         const double oh = __shfl_xor(hi, off, 64), ol = __shfl_xor(lo, off, 64);
         dd_add_t(hi, lo, oh, ol, unused);
     }
+    double D;
+    const double delta = dd_delta((double)((dim + STR - 1) / STR), 6 + WPP);
     if constexpr (WPP > 1) {      // combine the pair's wavefronts; wavefront 0 finishes
         __shared__ double phi[WPP], plo[WPP];
+        __shared__ int pin[WPP], again;
         if (lane == 0) {
             phi[sub] = hi;
             plo[sub] = lo;
         }
         __syncthreads();
+        if (sub == 0) {
+            for (int v = 1; v < WPP; ++v) dd_add_t(hi, lo, phi[v], plo[v], unused);
+            const bool certain = dd_certain(hi, lo, delta, D);
+            if (lane == 0) again = !certain || o.force_exact;
+            D = __shfl(D, 0, 64);
+        }
+        __syncthreads();
+        if (again) {              // uniform: all of them sum it again (678 pairs of d = 8192, FP32: 77 us by one alone, 42 so)
+            int inexact;
+            tracked_sum(a, b, dim, lane + 64LL * sub, STR, hi, lo, inexact);
+            if (lane == 0) {
+                phi[sub] = hi;
+                plo[sub] = lo;
+                pin[sub] = inexact;
+            }
+            __syncthreads();
+            if (sub == 0) {
+                for (int v = 1; v < WPP; ++v) {
+                    dd_add_t(hi, lo, phi[v], plo[v], inexact);
+                    inexact |= pin[v];
+                }
+                D = tracked_round(a, b, dim, lane, hi, lo, inexact, o.force_exact, o.nexact);
+            }
+        }
         if (sub != 0) return;
-        for (int v = 1; v < WPP; ++v) dd_add_t(hi, lo, phi[v], plo[v], unused);
+    } else {
+        int certain = dd_certain(hi, lo, delta, D);
+        certain = __shfl(certain, 0, 64);                // lane 0 decides for the wavefront
+        D = __shfl(D, 0, 64);
+        if (!certain || o.force_exact) D = canonical_tracked(a, b, dim, lane, o.force_exact, o.nexact);
     }
-    double D;
-    int certain = dd_certain(hi, lo, dd_delta((double)((dim + STR - 1) / STR), 6 + WPP), D);
-    certain = __shfl(certain, 0, 64);                    // lane 0 decides for the wavefront
-    D = __shfl(D, 0, 64);
-    if (!certain || o.force_exact) D = canonical_tracked(a, b, dim, lane, o.force_exact, o.nexact);
     if (lane == 0) {
         if (o.d2) o.d2[w] = D;
         if (o.range_mm) {       // non-negative doubles order as their bit patterns
@@ -838,7 +886,9 @@ bool grid_gains(long long nA, long long nB, long long dim)
 }
 
 // Launches waves for pairs co.first .. co.first + nwaves - 1 (in list mode
-// nwaves may exceed the list: the surplus waves leave at once).
+// nwaves may exceed the list: the surplus waves leave at once).  Few pairs of long
+// rows take four or sixteen wavefronts each (re-checks of d = 2048, FP32: 30 pairs
+// 15.6 us by four, 21.8 by one; 2740 52.8 and 64.6; of d = 512 one is as good).
 template <typename T>
 int run_canonical(const T *A, const T *B, long long dim, CanonOut &co, long long nwaves, hipStream_t st)
 {
@@ -846,7 +896,7 @@ int run_canonical(const T *A, const T *B, long long dim, CanonOut &co, long long
     const ProfMark pm = prof_begin("k_canonical", st);
     if (nwaves < 2048 && dim >= 4096)
         hipLaunchKernelGGL((k_canonical<T, 16>), dim3((unsigned)nwaves), dim3(1024), 0, st, A, B, dim, co);
-    else if (nwaves < kGridPairs && dim >= 4096)
+    else if ((nwaves < kGridPairs && dim >= 4096) || (nwaves <= 2048 && dim >= 1024))
         hipLaunchKernelGGL((k_canonical<T, 4>), dim3((unsigned)nwaves), dim3(256), 0, st, A, B, dim, co);
     else
         hipLaunchKernelGGL((k_canonical<T, 1>), dim3((unsigned)((nwaves + 3) / 4)), dim3(256), 0, st, A, B, dim, co);
@@ -1223,7 +1273,7 @@ __global__ void k_range_radii(const unsigned long long *cnt, long long cap, int 
 }
 
 // Re-check launches over a list whose length stays on the device: for
-// d < 4096 one launch of 2048 waves striding over it; for longer vectors a
+// d < 4096 one launch of 2048 slots striding over it; for longer vectors a
 // first launch of 256 pairs at sixteen waves each (the usual short list at
 // the latency of one pair), then a strided launch of 2048 slots of four waves
 // for the rest, which leaves at once when there is none (2769 pairs of d = 32768

@@ -1,7 +1,9 @@
 """Edges of the all-pairs route of cil_canonical_d2: what takes the kernel that
 shares rows, and the calls that must not."""
 import ctypes
+from fractions import Fraction
 
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +51,20 @@ def test_tiles_that_are_mostly_padding_take_a_wavefront_per_pair(cil, nA, nB, di
         cil.cil_profile(False)
     perm = torch.randperm(nA * nB, device="cuda", generator=g)
     assert torch.equal(got[perm], cil.cil_canonical_d2(A, B, ia[perm], jb[perm]))
+
+
+@pytest.mark.parametrize("dim", [700, 1024, 3000, 4096, 5001])
+@pytest.mark.parametrize("npairs", [5, 2048, 2050])
+def test_sums_on_a_rounding_boundary(cil, dim, npairs):
+    """FP32 rows whose squares leave a few bits below the sum's last: many sums end half way between two doubles, where
+    the untracked sum decides nothing and the pair is summed again by one, four or sixteen wavefronts."""
+    r = np.random.default_rng(dim)
+    a = r.integers(1, 2 ** 24, (8, dim)).astype(np.float32) * np.float32(2.0 ** -24)
+    b = r.integers(1, 2 ** 24, (8, dim)).astype(np.float32) * np.float32(2.0 ** -24)
+    exact = [[sum(Fraction(int(x)) ** 2 for x in (a[i].astype(np.float64) - b[j].astype(np.float64)) * 2.0 ** 24) / 2 ** 48
+              for j in range(8)] for i in range(8)]
+    want = np.array([[float(v) for v in row] for row in exact])
+    ties = sum(abs(v - Fraction(float(v))) == Fraction(float(np.spacing(float(v)))) / 2 for row in exact for v in row)
+    ia, jb = torch.arange(npairs) % 8, torch.arange(npairs) // 8 % 8
+    got = cil.cil_canonical_d2(torch.tensor(a).cuda(), torch.tensor(b).cuda(), ia, jb).cpu().numpy()
+    assert np.array_equal(got, want[ia.numpy(), jb.numpy()]), ties
