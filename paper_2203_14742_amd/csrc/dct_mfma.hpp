@@ -431,6 +431,8 @@ struct LineDense {
     {
         return hb < NB ? 16 * hb + lab < (n + 1) / 2 : 16 * (hb - NB) + lab < n / 2;
     }
+    // whether all labels of a block are valid: with NB the least that holds n, all blocks but the last of either half
+    __host__ __device__ static constexpr bool full(int hb) { return hb % NB < NB - 1; }
     // -1: no such mode
     __host__ __device__ static constexpr int mode(int hb, int lab, int n)
     {
@@ -451,6 +453,12 @@ template <typename Line>
 __host__ __device__ constexpr bool slot_valid(int hb, int lab, int n)
 {
     if constexpr (Line::kRagged) return Line::valid(hb, lab, n);
+    else return true;
+}
+template <typename Line>
+__host__ __device__ constexpr bool slot_full(int hb)
+{
+    if constexpr (Line::kRagged) return Line::full(hb);
     else return true;
 }
 template <typename Line>

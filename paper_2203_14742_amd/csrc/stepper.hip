@@ -1393,7 +1393,8 @@ int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std:
                 const size_t div = (size_t)hs[b].tab * 2 * N * N + (size_t)t * per;
                 tiles[t] = SplitItem<T>{hs[b], b, t, (const T *)mt.cst, (const T *)mt.tab + div,
                                      c.scheme ? (const T *)mt.tab2 + div : nullptr, w,
-                                     h ? h + (size_t)2 * t * per : nullptr};
+                                     h ? h + (size_t)2 * t * per : nullptr, {}, {}};
+                split_offsets(c.model, hs[b].p, tiles[t].u0, tiles[t].least);
             }
             g->tiles.push_back(std::move(tiles));
             g->active.push_back(b);

@@ -183,6 +183,7 @@ struct SplitItem {                       // all that a wavefront needs, read in 
     int32_t b, tile;                     // solve (-1: none), tile
     const T *cst, *div, *div2;           // MmTables of the side, the divisors at the tile
     T *work, *hist;                      // the solve's field between the passes; the tile's history (second order)
+    float u0[2], least[2];               // FP32: StepOffset of either species (its divisions would be every launch's)
 };
 enum { SPLIT_LOAD = 1, SPLIT_STORE = 2, SPLIT_CHECK = 4, SPLIT_NEXT = 8 };
 template <typename T>
@@ -195,6 +196,7 @@ struct SplitArgs {
     int flags, first;                    // set by launch_split, as the coefficients
     T k4, kt, k2, kc;
 };
+void split_offsets(int model, const double *p, float (&u0)[2], float (&least)[2]);
 template <typename T>
 int launch_split(SplitArgs<T> a, int nitems, int model, double dt, int K, bool bdf, bool from_start, hipStream_t st);
 

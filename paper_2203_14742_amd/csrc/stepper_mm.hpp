@@ -84,7 +84,7 @@ struct OwnReaction {
 // between the passes leaves out u* if all tiles do, else 0, and the column of the
 // rows' means takes up the difference where a tile chose otherwise (join_offsets).
 template <int MODEL>
-__device__ __forceinline__ double steady_value(const double *p, int sp)
+__host__ __device__ __forceinline__ double steady_value(const double *p, int sp)
 {
     double v = 0.0, w = 0.0;
     if constexpr (MODEL == CIL_GM) {
@@ -108,18 +108,19 @@ constexpr bool kOffset = sizeof(T) == 4 && MODEL != CIL_FHN && MODEL != CIL_HEAT
 template <int MODEL>
 struct StepOffset {
     float u0, least;
-    __device__ __forceinline__ void init(const double *p, int sp)
+    __host__ __device__ __forceinline__ void init(const double *p, int sp)
     {
         const double u = steady_value<MODEL>(p, sp), q = 0.25 * fabs(u);
         const bool ok = fabs(u) <= (double)__FLT_MAX__;                      // (a NaN is none)
         u0 = ok ? (float)u : 0.0f;
         least = ok ? (float)q : __builtin_nanf("");                          // NaN: never
-        if ((double)least < q) least = __int_as_float(__float_as_int(least) + 1);     // least float >= q
+        if ((double)least < q) least = __builtin_bit_cast(float, __builtin_bit_cast(int, least) + 1);     // least float >= q
     }
     // the lanes' species (bit 0: v, bit 1: w) whose values in the tile all reach
-    // `least`; abs(hb, i): the lane's values, infinite for padding
+    // `least`; abs(hb, i): the lane's values, infinite for padding (any, where the
+    // lane's whole row is: `row` false)
     template <int NS, typename F>
-    __device__ __forceinline__ unsigned species(F &&abs) const
+    __device__ __forceinline__ unsigned species(bool row, F &&abs) const
     {
         float part[4], m;
 #pragma unroll
@@ -129,7 +130,7 @@ struct StepOffset {
             for (int hb = 0; hb < NS; ++hb) part[i] = fminf(part[i], abs(hb, i));
         }
         m = fminf(fminf(part[0], part[1]), fminf(part[2], part[3]));
-        const unsigned long long b = __ballot(!(m >= least)), v = 0x00FF00FF00FF00FFull;      // lanes of species v
+        const unsigned long long b = __ballot(row && !(m >= least)), v = 0x00FF00FF00FF00FFull;      // lanes of species v
         return ((b & v) ? 0u : 1u) | ((b & ~v) ? 0u : 2u);
     }
 };
@@ -355,10 +356,10 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
     long long last_rebase = step;
     if constexpr (RF) rebase(true);
     // the stop rule's snapshot of the step before an evaluation: in registers where
-    // they are free (sides 32, FP64 64; 300 FP64 solves of 64^2 evaluated at every
+    // they are free (FP32 32, FP64 64; 300 FP64 solves of 64^2 evaluated at every
     // step 17.5 us a step, 27.9 through the state; 3000 FP32 ones of 32^2 14.3, 20.5),
     // else in the state
-    constexpr bool SNAP = (sizeof(T) == 8 || Line::N == 32) && TPW == 1 && SCHEME == 0 && !RAG && !RF;
+    constexpr bool SNAP = Line::N == (sizeof(T) == 8 ? 64 : 32) && TPW == 1 && SCHEME == 0 && !RAG && !RF;
     V snap[SNAP ? NS : 1];
     int fin = -1;
     while (step < pa.max_steps) {
@@ -381,9 +382,9 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
                 // explicit reaction
                 V X[NS];
                 if constexpr (OFF) {
-                    const unsigned has = offset.template species<NS>([&](int hb, int i) __attribute__((always_inline)) {
-                        if constexpr (RAG) return (real[k] >> (hb * 4 + i) & 1u) ? fabsf(x[k][hb][i]) : __builtin_inff();
-                        else return fabsf(x[k][hb][i]);
+                    const bool isrow = !RAG || (real[k] & 1u);       // (slot 0 is a position of every row)
+                    const unsigned has = offset.template species<NS>(isrow, [&](int hb, int i) __attribute__((always_inline)) {
+                        return slot_full<Line>(hb) || (real[k] >> (hb * 4 + i) & 1u) ? fabsf(x[k][hb][i]) : __builtin_inff();
                     });
                     chose[wave + WAVES * k] = (uint8_t)has;       // (every lane: no branch)
                     c0 = (has >> sp) & 1u ? offset.u0 : 0.0f;

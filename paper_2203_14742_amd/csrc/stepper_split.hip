@@ -104,10 +104,9 @@ __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<
     OwnReaction<MODEL, T> react;
     react.init(s.p, sp);
     if constexpr (kOffset<MODEL, T>) {                        // the tile's own choice, for the column pass
-        StepOffset<MODEL> offset;
-        offset.init(s.p, sp);
-        const unsigned has = offset.template species<NS>([&](int hb, int i) __attribute__((always_inline)) {
-            return !RAG || real(hb, i) ? fabsf(x[hb][i]) : __builtin_inff();
+        const StepOffset<MODEL> offset{sp ? it.u0[1] : it.u0[0], sp ? it.least[1] : it.least[0]};
+        const unsigned has = offset.template species<NS>(rok, [&](int hb, int i) __attribute__((always_inline)) {
+            return slot_full<Line>(hb) || real(hb, i) ? fabsf(x[hb][i]) : __builtin_inff();
         });
         c0 = (has >> sp) & 1u ? offset.u0 : 0.0f;
         if ((lane & ~8) == 0) a.ct[(2 * it.b + sp) * 16 + it.tile] = c0;
@@ -159,6 +158,24 @@ __device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitIt
     const unsigned col = (unsigned)((sp * N + g4) * N + 8 * it.tile + (c & 7)) * (unsigned)sizeof(T);   // its column's slots g4 ..
     const T *dp = (a.first ? it.div : it.div2) + lane * 4;
     V x[NS], X[NS], dv[NS];
+    // the column of the rows' means, as in mm_solve: the tiles' constants and the field's
+    [[maybe_unused]] float ct[NS], cf = 0.0f;
+    [[maybe_unused]] bool differ = false;
+    if constexpr (sizeof(T) == 4) {
+        if (a.ct && it.tile == 0) {
+            bool all = true;
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb) {
+                ct[hb] = a.ct[(2 * it.b + sp) * 16 + 2 * hb + (lane >> 5)];
+                all = all && ct[hb] != 0.0f;
+            }
+            // (the other half of the species' tiles is 32 lanes on)
+            cf = __shfl_xor((int)all, 32, 64) && all ? ct[0] : 0.0f;
+#pragma unroll
+            for (int hb = 0; hb < NS; ++hb) differ = differ || ct[hb] != cf;
+            if ((lane & ~8) == 0) a.c0[2 * it.b + sp] = cf;
+        }
+    }
 #pragma unroll
     for (int hb = 0; hb < NS; ++hb)
 #pragma unroll
@@ -168,17 +185,7 @@ __device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitIt
         for (int hb = 0; hb < NS; ++hb) dv[hb] = mm_load(dp + hb * 256);
     };
     if constexpr (sizeof(T) == 4) {
-        if (a.ct && it.tile == 0) {                           // the column of the rows' means, as in mm_solve
-            float ct[NS], cf = 0.0f;
-            bool all = true;
-#pragma unroll
-            for (int hb = 0; hb < NS; ++hb) {
-                ct[hb] = a.ct[(2 * it.b + sp) * 16 + 2 * hb + (lane >> 5)];
-                all = all && ct[hb] != 0.0f;
-                cf = ct[hb];
-            }
-            // (the other half of the species' tiles is 32 lanes on)
-            if (!(__shfl_xor((int)all, 32, 64) && all)) cf = 0.0f;
+        if (__ballot(differ)) {
 #pragma unroll
             for (int hb = 0; hb < NS; ++hb) {
                 unsigned rows = 0;
@@ -187,7 +194,6 @@ __device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitIt
                     rows |= ((c & 7) == 0 && slot_valid<Line>(hb, g4 + i, it.s.n) ? 1u : 0u) << i;
                 x[hb] = join_offsets(x[hb], (float)it.s.n, ct[hb], cf, rows);
             }
-            if ((lane & ~8) == 0) a.c0[2 * it.b + sp] = cf;
         }
     }
     if constexpr (NS < 8) divisors();                         // ahead of the transform where registers are left
@@ -221,6 +227,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 }
 
 }  // namespace
+
+void split_offsets(int model, const double *p, float (&u0)[2], float (&least)[2])
+{
+    dispatch_model(model, [&](auto MD) {
+        for (int sp = 0; sp < 2; ++sp) {
+            StepOffset<decltype(MD)::value> o;
+            o.init(p, sp);
+            u0[sp] = o.u0;
+            least[sp] = o.least;
+        }
+    });
+}
 
 // K steps of the items from the states; from_start: the first of them is the
 // second-order scheme's first, an IMEX-Euler step.
