@@ -1317,7 +1317,7 @@ int run_plain(SimCtx &c, std::vector<PlainGroup<T>> &groups, const DevSolve *dS,
                 a.items = g.ditems;
                 a.state = state;
                 a.c0 = g.c0;
-                a.ct = f32 && c.model != CIL_FHN && c.model != CIL_HEAT ? g.ct : nullptr;     // (kOffset)
+                a.ct = g.ct;
                 a.res = R;
                 const ProfMark pm = prof_begin(c.scheme ? (f32 ? "split_step_sbdf2_f32" : "split_step_sbdf2_f64")
                                                         : (f32 ? "split_step_f32" : "split_step_f64"), c.st);
@@ -1377,9 +1377,16 @@ int run_plain(SimCtx &c, std::vector<PlainGroup<T>> &groups, const DevSolve *dS,
 template <typename T>
 int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector<DevSolve> &hs, PlainGroup<T> *g)
 {
-    size_t work = 0;
-    for (auto &kv : byn) work += (size_t)2 * mm_padded(kv.first) * mm_padded(kv.first) * kv.second.size();
+    size_t work = 0, solves = 0;
+    for (auto &kv : byn) {
+        work += (size_t)2 * mm_padded(kv.first) * mm_padded(kv.first) * kv.second.size();
+        solves += kv.second.size();
+    }
     T *w, *h = nullptr;
+    if (std::is_same<T, float>::value && c.model != CIL_FHN && c.model != CIL_HEAT) {    // (kOffset)
+        CIL_TRY(c.cb->alloc((void **)&g->c0, sizeof(T) * 2 * solves));
+        CIL_TRY(c.cb->alloc((void **)&g->ct, sizeof(T) * 32 * solves));
+    }
     CIL_TRY(c.cb->alloc((void **)&w, sizeof(T) * work));
     if (c.scheme) CIL_TRY(c.cb->alloc((void **)&h, sizeof(T) * 2 * work));
     size_t most = 0;
@@ -1391,7 +1398,7 @@ int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std:
             std::vector<SplitItem<T>> tiles(N / 8);
             for (int t = 0; t < N / 8; ++t) {
                 const size_t div = (size_t)hs[b].tab * 2 * N * N + (size_t)t * per;
-                tiles[t] = SplitItem<T>{hs[b], b, t, (const T *)mt.cst, (const T *)mt.tab + div,
+                tiles[t] = SplitItem<T>{hs[b], b, t, (int)g->tiles.size(), 0, (const T *)mt.cst, (const T *)mt.tab + div,
                                      c.scheme ? (const T *)mt.tab2 + div : nullptr, w,
                                      h ? h + (size_t)2 * t * per : nullptr, {}, {}};
                 split_offsets(c.model, hs[b].p, tiles[t].u0, tiles[t].least);
@@ -1408,8 +1415,6 @@ int make_split_group(SimCtx &c, const std::map<int, std::vector<int>> &byn, std:
     size_t all = 0;
     for (auto &t : g->tiles) all += t.size();
     CIL_TRY(c.cb->alloc((void **)&g->ditems, sizeof(SplitItem<T>) * (all + 8 * most)));
-    CIL_TRY(c.cb->alloc((void **)&g->c0, sizeof(T) * 2 * hs.size()));
-    CIL_TRY(c.cb->alloc((void **)&g->ct, sizeof(T) * 32 * hs.size()));
     CIL_TRY(c.cb->alloc((void **)&g->dlist, sizeof(int) * g->active.size()));
     return CIL_OK;
 }

@@ -180,7 +180,7 @@ constexpr bool split_supported(int n) { return n > 64 && n <= 128; }
 template <typename T>
 struct SplitItem {                       // all that a wavefront needs, read in one go
     DevSolve s;
-    int32_t b, tile;                     // solve (-1: none), tile
+    int32_t b, tile, k, pad;             // solve (-1: none), tile, the solve's place in the group
     const T *cst, *div, *div2;           // MmTables of the side, the divisors at the tile
     T *work, *hist;                      // the solve's field between the passes; the tile's history (second order)
     float u0[2], least[2];               // FP32: StepOffset of either species (its divisions would be every launch's)
@@ -190,8 +190,8 @@ template <typename T>
 struct SplitArgs {
     const SplitItem<T> *items;
     T *state;
-    T *c0;                               // FP32: per solve and species, the constant the field in `work` leaves out
-    T *ct;                               // FP32 (or null): the tiles' own constants of the step, [solve][species][16]
+    T *c0;                               // FP32 (or null): constants left out by the field in `work` [k][species]
+    T *ct;                               // and by the tiles [k][species][16]
     StepResults res;
     int flags, first;                    // set by launch_split, as the coefficients
     T k4, kt, k2, kc;

@@ -55,7 +55,7 @@ __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<
     };
     // FP32 transforms act on u - u* (steady_value); FP64 ones on u
     T c0 = T(0);
-    if constexpr (kOffset<MODEL, T>) c0 = a.c0[2 * it.b + sp];
+    if constexpr (kOffset<MODEL, T>) c0 = a.c0[2 * it.k + sp];
     V x[NS], X[NS];
     if (a.flags & SPLIT_LOAD) {
 #pragma unroll
@@ -109,7 +109,7 @@ __device__ __forceinline__ void row_pass(const SplitArgs<T> &a, const SplitItem<
             return slot_full<Line>(hb) || real(hb, i) ? fabsf(x[hb][i]) : __builtin_inff();
         });
         c0 = (has >> sp) & 1u ? offset.u0 : 0.0f;
-        if ((lane & ~8) == 0) a.ct[(2 * it.b + sp) * 16 + it.tile] = c0;
+        if ((lane & ~8) == 0) a.ct[(2 * it.k + sp) * 16 + it.tile] = c0;
     }
     const T cp = a.first ? T(0) : c0;                         // (no history yet)
     // history of the second-order scheme: u and F in the lane's own order
@@ -166,14 +166,14 @@ __device__ __forceinline__ void column_pass(const SplitArgs<T> &a, const SplitIt
             bool all = true;
 #pragma unroll
             for (int hb = 0; hb < NS; ++hb) {
-                ct[hb] = a.ct[(2 * it.b + sp) * 16 + 2 * hb + (lane >> 5)];
+                ct[hb] = a.ct[(2 * it.k + sp) * 16 + 2 * hb + (lane >> 5)];
                 all = all && ct[hb] != 0.0f;
             }
             // (the other half of the species' tiles is 32 lanes on)
             cf = __shfl_xor((int)all, 32, 64) && all ? ct[0] : 0.0f;
 #pragma unroll
             for (int hb = 0; hb < NS; ++hb) differ = differ || ct[hb] != cf;
-            if ((lane & ~8) == 0) a.c0[2 * it.b + sp] = cf;
+            if ((lane & ~8) == 0) a.c0[2 * it.k + sp] = cf;
         }
     }
 #pragma unroll
