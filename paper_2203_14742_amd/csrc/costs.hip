@@ -6,8 +6,10 @@
 // and the range, bins and resamples read them directly: nothing is approximated,
 // listed or re-checked.  The host forms the radii from the ranges, as for the
 // other calls, and waits once for those and once for the costs.  20 proposals of
-// 64 patterns of 128^2 take 690 us; one proposal after the other through the
-// pair-statistic calls, with four waits and two dozen launches each, took 6240.
+// 64 stationary patterns of 128^2 take 591 us (of noise, whose sums end on a rounding
+// boundary more often and are then formed twice, 688); one proposal after the
+// other through the pair-statistic calls, with four waits and two dozen launches
+// each, take 6280.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -24,8 +24,10 @@
 // of the dense transform; partners of every fold share a lane, so the folds
 // are register adds.  Any other N <= 128 takes the first fold only
 // (LineDense), padded to a multiple of 32 with zero rows and columns in the
-// constants.  Cosines are unnormalised (the constant mode's gain is exactly
-// one); the weights 1/n, 2/n of the inverse sit in the spectral divisor.
+// constants.  Cosines are unnormalised; the weights 1/n, 2/n of the inverse sit
+// in the spectral divisor (so the constant mode's gain over a step is exactly one
+// where n is a power of two, elsewhere the rounded 1/n^2 times n^2, the same
+// within half a unit in the last place at every step).
 //
 // Positions and modes are kept in slot order: slot (hb, label) of a line is
 // grid position pos(hb, label), and of its spectrum mode(hb, label).

@@ -6,9 +6,10 @@
 // that lane l ^ 8 (a rotation by eight within the row of 16 lanes) holds the
 // other species at the same points.  n/8 wavefronts cover the grid.  The field
 // lives in LDS in slot order, [species][row slot][column slot], rows padded by
-// four values: the row pass's 16-byte accesses and the column pass's strided
-// ones are then both free of bank conflicts (a half wavefront's addresses
-// fall on distinct banks; the species' planes are eight values apart).
+// four values and the species' planes eight values apart: the column pass's
+// strided accesses fall on distinct banks; of the row pass's 16-byte ones species
+// v of line k + 2 shares banks with species w of line k (32 conflict cycles per
+// wavefront and step at 64^2 in FP32 and 128 at 128^2, 1 to 2 % of a step).
 // One step is two passes, each in place on the wavefront's own lines and each
 // ending with the workgroup barrier:
 //   row pass     row inverse (u^s in registers), stop rule and snapshot at
@@ -17,10 +18,10 @@
 // The constants of the transforms and (where they fit) the divisors stay in
 // registers from the first step to the last.
 //
-// What bounds it: the matrix cores' issue.  A step of a 64^2 solve is 64
-// products of 32 cycles (FP32) per wavefront and two wavefronts a SIMD, 4096
-// cycles, with the folds, rotations and reaction issued beside them by the
-// other wavefront.
+// What bounds it: issue.  FP32 and FP64 matrix and vector instructions of one SIMD
+// do not overlap on gfx950 (measured: their times add), so a step costs its
+// products (a 64^2 solve in FP32: 64 of 32 cycles per wavefront) plus the folds,
+// rotations and reaction.
 #pragma once
 
 #include "dct_mfma.hpp"

@@ -31,10 +31,10 @@ import numpy as np
 from . import (CIL_EINVAL, CIL_SOLVE_NONFINITE, CilError, cil_bootstrap_features, cil_gaussian_loglik, cil_pair_bins,
                cil_pair_bins_adaptive, cil_simulate_patterns, cil_synthetic_costs, make_problems)
 
-# Most canonical terms (pairs times dimension) of a proposal for the batched costs.  20 proposals of 8.4e7 terms take
-# 690 us in one call against 6360 one after the other, two of 3.4e8 404 against 764, two of 5.9e8 687 against 743; one of
-# 7.9e8 466 against 478, one of 1.2e9 669 against 485: there the Gram estimates of the separate calls, which leave few
-# pairs to the canonical sum, win.
+# Most canonical terms (pairs times dimension) of a proposal for the batched costs.  us, one call / one proposal after the
+# other, patterns of 128^2 (noise): 20 proposals of 8.4e7 terms 688 / 6277, two of 3.4e8 400 / 886, two of 5.9e8 571 / 908,
+# one of 7.9e8 464 / 537, one of 1.2e9 634 / 625: towards there the Gram estimates of the separate calls, which leave few
+# pairs to the canonical sum, catch up.
 _BATCHED_TERMS = 600_000_000
 
 # Most microseconds per proposal that the batched costs may spend where one proposal does not fill the chip: the range
