@@ -46,7 +46,7 @@ int ws_get(int slot, size_t bytes, void **ptr);
 // Pinned host buffers for the small copies between the host and the device
 // inside a call (so they run asynchronously), grow-only, one per (device,
 // slot); freed by cil_shutdown().
-enum HostSlot { HS_DIST = 0, HS_BOOT, HS_STEP, HS_COSTS, HS_FEAT, HS_NUM_SLOTS };
+enum HostSlot { HS_DIST = 0, HS_BOOT, HS_COSTS, HS_FEAT, HS_NUM_SLOTS };
 int host_stage(int slot, size_t bytes, void **ptr);
 int current_device(int *dev);
 // Wait for everything issued to `st` (polls, then blocks; CIL_OPT_SYNC_SPIN_US).

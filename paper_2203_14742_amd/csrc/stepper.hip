@@ -557,31 +557,104 @@ int plain_tables(int n, PlainTables *out)
 }
 
 // Auxiliary streams (default priority) for running the persistent kernels of
-// different grid sides side by side, and fork/join events; per device.
+// different grid sides side by side, and fork/join events.  A call leases a set
+// for as long as it runs (calls of several threads at once have one each: a shared
+// fork event would be recorded anew between another call's record and its waits)
+// and gives it back; up to kKept sets stay per device.
+constexpr size_t kKept = 8;
+std::mutex g_lease_mu;
 struct AuxStreams {
     std::vector<hipStream_t> st;
     std::vector<hipEvent_t> ev;     // ev[0] fork, ev[1 + g] join of stream g
+    ~AuxStreams()
+    {
+        for (hipStream_t s : st) (void)hipStreamDestroy(s);
+        for (hipEvent_t e : ev) (void)hipEventDestroy(e);
+    }
 };
-std::map<int, AuxStreams> g_aux;
+// device -> sets not in use (never destroyed: the runtime may be gone by then)
+auto &g_aux = *new std::map<int, std::vector<std::unique_ptr<AuxStreams>>>;
 
-int aux_streams(int streams, int joins, AuxStreams **out)
-{
-    int dev;
-    CIL_TRY(current_device(&dev));
-    AuxStreams &a = g_aux[dev];
-    while ((int)a.st.size() < streams) {
-        hipStream_t s;
-        CIL_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
-        a.st.push_back(s);
+struct AuxLease {
+    std::unique_ptr<AuxStreams> set;
+    int dev = 0;
+    ~AuxLease()
+    {
+        if (!set) return;
+        std::lock_guard<std::mutex> lk(g_lease_mu);
+        if (g_aux[dev].size() < kKept) g_aux[dev].push_back(std::move(set));
     }
-    while ((int)a.ev.size() < joins + 1) {
-        hipEvent_t e;
-        CIL_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        a.ev.push_back(e);
+    int take(int streams, int joins)
+    {
+        CIL_TRY(current_device(&dev));
+        {
+            std::lock_guard<std::mutex> lk(g_lease_mu);
+            auto &free_sets = g_aux[dev];
+            if (!free_sets.empty()) {
+                set = std::move(free_sets.back());
+                free_sets.pop_back();
+            }
+        }
+        if (!set) set.reset(new AuxStreams);
+        while ((int)set->st.size() < streams) {
+            hipStream_t s;
+            CIL_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+            set->st.push_back(s);
+        }
+        while ((int)set->ev.size() < joins + 1) {
+            hipEvent_t e;
+            CIL_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            set->ev.push_back(e);
+        }
+        return CIL_OK;
     }
-    *out = &a;
-    return CIL_OK;
-}
+};
+
+// Pinned blocks that results come back through, leased likewise: one that a call
+// has not read yet is no other call's.
+std::map<int, std::multimap<size_t, void *>> g_stage;              // device -> (capacity, block) not in use
+struct StageLease {
+    void *p = nullptr;
+    size_t cap = 0;
+    int dev = 0;
+    ~StageLease()
+    {
+        if (!p) return;
+        void *drop = nullptr;
+        {
+            std::lock_guard<std::mutex> lk(g_lease_mu);
+            auto &m = g_stage[dev];
+            m.emplace(cap, p);
+            if (m.size() > kKept) {                      // the smallest goes
+                drop = m.begin()->second;
+                m.erase(m.begin());
+            }
+        }
+        if (drop) (void)hipHostFree(drop);
+    }
+    int take(size_t bytes)
+    {
+        CIL_TRY(current_device(&dev));
+        {
+            std::lock_guard<std::mutex> lk(g_lease_mu);
+            auto &m = g_stage[dev];
+            auto it = m.lower_bound(bytes);
+            if (it != m.end()) {
+                cap = it->first;
+                p = it->second;
+                m.erase(it);
+                return CIL_OK;
+            }
+        }
+        cap = std::max<size_t>(64 * 1024, bytes + bytes / 4);
+        if (hipHostMalloc(&p, cap, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            p = nullptr;
+            return set_error(CIL_ENOMEM, "pinned host buffer of %zu bytes failed", cap);
+        }
+        return CIL_OK;
+    }
+};
 
 // How a persistent group runs: one lane or a quad of lanes per grid line, or
 // the matrix cores.
@@ -688,12 +761,17 @@ int stepper_release()
         (void)hipFree(kv.second.lam);
     }
     g_plain_tables.clear();
-    for (auto &kv : g_aux) {
-        (void)hipSetDevice(kv.first);
-        for (hipStream_t st : kv.second.st) (void)hipStreamDestroy(st);
-        for (hipEvent_t e : kv.second.ev) (void)hipEventDestroy(e);
+    {
+        std::lock_guard<std::mutex> lk(g_lease_mu);
+        for (auto &kv : g_aux) {
+            (void)hipSetDevice(kv.first);
+            kv.second.clear();
+        }
+        for (auto &kv : g_stage) {
+            for (auto &b : kv.second) (void)hipHostFree(b.second);
+            kv.second.clear();
+        }
     }
-    g_aux.clear();
     {
         std::lock_guard<std::mutex> lk(g_pool_mu);
         for (auto &kv : g_pool) {
@@ -989,6 +1067,7 @@ int make_mm_tables(SimCtx &c, int n, const std::vector<int> &ids, std::vector<De
 // mixed launches, the switch step) back to the host: pinned staging, so the
 // copies are queued without blocking, and one wait.
 struct HostResults {
+    StageLease block;                     // (what the pointers point into)
     const long long *steps;
     const double *res;
     const int *stat;
@@ -997,9 +1076,9 @@ struct HostResults {
 int fetch_results(SimCtx &c, int B, const long long *dsteps, const double *dres, const int *dstat,
                   const long long *dsw, HostResults *out)
 {
-    char *hb;
     const size_t b8 = sizeof(long long) * (size_t)B;
-    CIL_TRY(host_stage(HS_STEP, 3 * b8 + sizeof(int) * (size_t)B, (void **)&hb));
+    CIL_TRY(out->block.take(3 * b8 + sizeof(int) * (size_t)B));
+    char *const hb = (char *)out->block.p;
     out->steps = (const long long *)hb;
     out->res = (const double *)(hb + b8);
     out->sw = dsw ? (const long long *)(hb + 2 * b8) : nullptr;
@@ -1097,12 +1176,14 @@ int run_fused(SimCtx &c, const std::map<int, std::vector<int>> &byn, std::vector
         CIL_HIP(hipMemcpyAsync(dl, kv.second.data(), sizeof(int) * kv.second.size(), hipMemcpyHostToDevice, c.st));
         dls.push_back(dl);
     }
+    AuxLease lease;
     AuxStreams *aux = nullptr;
     const int ng = (int)byn.size();
     // a side per stream, at most eight streams (a batch may hold a hundred sides; four hardware queues serve them)
     const int nst = std::min(ng, 8);
     if (ng > 1 || aside) {
-        CIL_TRY(aux_streams(nst, ng, &aux));
+        CIL_TRY(lease.take(nst, ng));
+        aux = lease.set.get();
         CIL_HIP(hipEventRecord(aux->ev[0], c.st));
     }
     std::vector<const std::pair<const int, std::vector<int>> *> groups;
