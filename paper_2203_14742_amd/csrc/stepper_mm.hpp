@@ -173,7 +173,7 @@ struct MmShape {
 // in u64, the FP32 correction v in x, R = f(U) + nu Lap U rounded to FP32 in
 // LDS behind the field (lane-major, 16 bytes a lane).  Lap U is formed in FP64
 // from one species' U at a time, staged in the LDS of the field.
-template <typename T, typename Line, int TPW, int MODEL, int SCHEME, bool RF, bool LOAD, typename TS>
+template <typename T, typename Line, int TPW, int MODEL, int SCHEME, bool RF, bool LOAD, typename TS, bool SNAP = false>
 __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const DevSolve &s, int b, T *state, TS *out,
                                         const T *dtab, const T *dtab2, const T *cst, double dt, const PersistArgs &pa,
                                         long long &step, Vec4<T> (&x)[TPW][Line::NS], double *u64 = nullptr)
@@ -356,11 +356,8 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
     const T *dsel = dp;                                       // the divisors of the step
     long long last_rebase = step;
     if constexpr (RF) rebase(true);
-    // the stop rule's snapshot of the step before an evaluation: in registers where
-    // they are free (FP32 32, FP64 64; 300 FP64 solves of 64^2 evaluated at every
-    // step 17.5 us a step, 27.9 through the state; 3000 FP32 ones of 32^2 14.3, 20.5),
-    // else in the state
-    constexpr bool SNAP = Line::N == (sizeof(T) == 8 ? 64 : 32) && TPW == 1 && SCHEME == 0 && !RAG && !RF;
+    // the stop rule's snapshot of the step before an evaluation: in registers (SNAP), or in the state
+    static_assert(!SNAP || (TPW == 1 && SCHEME == 0 && !RAG && !RF), "");
     V snap[SNAP ? NS : 1];
     int fin = -1;
     while (step < pa.max_steps) {
@@ -564,7 +561,7 @@ __device__ __forceinline__ int mm_solve(T *sm, double *red, int *sbad, const Dev
 
 // One kernel per model (the host picks it).  WPE: wavefronts per SIMD that the
 // register allocation aims at.
-template <int MODEL, typename T, typename Line, int SCHEME, int TPW, int WPE>
+template <int MODEL, typename T, typename Line, int SCHEME, int TPW, int WPE, bool SNAP>
 __global__ __launch_bounds__((MmShape<T, Line, TPW>::THREADS)) __attribute__((amdgpu_waves_per_eu(WPE))) void k_mm(
     const DevSolve *S, const int *list, T *state, const T *dtab, const T *dtab2, const T *cst, double dt,
     PersistArgs pa)
@@ -577,7 +574,7 @@ __global__ __launch_bounds__((MmShape<T, Line, TPW>::THREADS)) __attribute__((am
     const DevSolve s = S[b];
     long long step = pa.steps[b];
     Vec4<T> x[TPW][Line::NS];
-    mm_solve<T, Line, TPW, MODEL, SCHEME, false, true, T>(sm, red, sbad, s, b, state, state, dtab, dtab2, cst, dt, pa, step,
+    mm_solve<T, Line, TPW, MODEL, SCHEME, false, true, T, SNAP>(sm, red, sbad, s, b, state, state, dtab, dtab2, cst, dt, pa, step,
                                                      x);
 }
 
@@ -626,14 +623,30 @@ void k_mm_mixed(const DevSolve *S, const int *list, float *state, double *state6
     if (threadIdx.x == 0 && mode != 2) switch_step[b] = sw;
 }
 
+// Whether a kernel has a form that keeps the stop rule's snapshot in registers, for
+// runs evaluated every few steps (at most kSnapCheck apart): 300 FP64 solves of 64^2
+// evaluated at every step 17.5 us a step so, 27.9 through the state; 3000 FP32 ones
+// of 32^2 14.3 and 20.5, at every fifth 10.6 and 10.9.  Its registers cost 3 % of
+// a step where evaluations are rare.
+template <typename T, typename Line, int SCHEME>
+constexpr bool kHasSnap = SCHEME == 0 && Line::N == (sizeof(T) == 8 ? 64 : 32) && !Line::kRagged;
+constexpr int kSnapCheck = 4;
+
 template <typename T, typename Line, int SCHEME, int TPW, int WPE>
 void launch_mm_line(int nl, const DevSolve *S, const int *list, T *state, const T *dtab, const T *dtab2, const T *cst,
                     int model, double dt, const PersistArgs &pa, hipStream_t st)
 {
     constexpr int threads = MmShape<T, Line, TPW>::THREADS;
     dispatch_model(model, [&](auto MD) {
-        hipLaunchKernelGGL((k_mm<decltype(MD)::value, T, Line, SCHEME, TPW, WPE>), dim3(nl), dim3(threads), 0, st, S, list,
-                           state, dtab, dtab2, cst, dt, pa);
+        if constexpr (kHasSnap<T, Line, SCHEME>) {
+            if (pa.check <= kSnapCheck) {
+                hipLaunchKernelGGL((k_mm<decltype(MD)::value, T, Line, SCHEME, TPW, WPE, true>), dim3(nl), dim3(threads), 0,
+                                   st, S, list, state, dtab, dtab2, cst, dt, pa);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_mm<decltype(MD)::value, T, Line, SCHEME, TPW, WPE, false>), dim3(nl), dim3(threads), 0, st, S,
+                           list, state, dtab, dtab2, cst, dt, pa);
     });
 }
 

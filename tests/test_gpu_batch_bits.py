@@ -44,3 +44,27 @@ def test_alone_in_a_batch_and_at_every_evaluation(cil, model, dtype, scheme):
                                   scheme=scheme)
         for k in (0, 1, 2, 149, 299):
             assert torch.equal(many[k], runs[12][0][k % 3]), (n, k)
+
+
+@pytest.mark.parametrize("dtype", [torch.float64, torch.float32])
+@pytest.mark.parametrize("n", [32, 64])
+def test_evaluation_intervals_by_either_snapshot(cil, n, dtype):
+    """Runs evaluated up to four steps apart keep the stop rule's snapshot in registers, others in the state: the same
+    states, and at a common last step the same residual and status, also for a solve that is not finite."""
+    for model in (0, 2, 3):
+        p, nu, L, dt = MODELS[model]
+        base = cil.cil_homogeneous_state(model, p)
+        x = torch.tensor(cs.initial_conditions(base, n, 5, seed=n), dtype=dtype, device="cuda")
+        x[3, 0, 2, 1] = float("nan")
+        probs = cil.make_problems(n, L, nu, p, count=5)
+        runs = []
+        for check in (1, 2, 4, 5, 20):
+            st = x.clone()
+            rep = cil.cil_simulate_patterns(model, st, probs, dt, 20, check_every=check, polish=0, raise_on_nonfinite=False)
+            runs.append((st[[0, 1, 2, 4]], rep))
+        for st, rep in runs:
+            assert torch.equal(st, runs[-1][0])
+            assert list(rep["status"]) == [0, 0, 0, cil.CIL_SOLVE_NONFINITE, 0]
+            ok = [0, 1, 2, 4]
+            assert np.array_equal(rep["final_resid"][ok], runs[-1][1]["final_resid"][ok])
+            assert np.all(rep["steps_taken"][ok] == 20)
